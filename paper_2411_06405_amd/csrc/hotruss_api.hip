@@ -34,8 +34,8 @@ struct Plan {
   bool full = true;  // decomposition (false: support only)
   size_t off_ctl, off_eid, off_eu, off_ev, off_s1, off_s2, off_srem, off_upcnt, off_upoff,
       off_scan, off_minpart, off_sup, off_rho, off_R0, off_R1, off_L[HMAX + 1],
-      off_Dm[HMAX + 1], off_evl[HMAX + 1][2], off_itl[HMAX + 2], off_cix, off_len, off_tci,
-      off_teid, off_acct, off_ce;
+      off_Dm[HMAX + 1], off_evl[HMAX + 1][2], off_itl[HMAX + 2], off_cix, off_len, off_acct,
+      off_ce;
   size_t total = 0;
 };
 
@@ -85,8 +85,6 @@ bool make_plan(uint32_t n, uint64_t m, uint32_t h, const hoTuning* tune, bool fu
   p.off_rho = take(full ? 4 * m + 4 : 0);
   p.off_cix = take(full ? 8 * m + 4 : 0);
   p.off_len = take(full ? 4 * (size_t)n + 4 : 0);
-  p.off_tci = take(full ? 8 * m + 4 : 0);
-  p.off_teid = take(full ? 8 * m + 4 : 0);
   p.off_R0 = take(full ? 4 * m + 4 : 0);
   p.off_R1 = take(full ? 4 * m + 4 : 0);
   p.off_acct = take(full ? 6 * (4 * (size_t)n + 4) : 0);  // stats-mode work count
@@ -133,7 +131,7 @@ bool make_topo_plan(uint32_t n, uint64_t m, Plan* P, size_t* off_cc) {
   p.off_scan = take(4 * ((size_t)n / 1024 + 2));
   p.off_minpart = take(4 * MIN_PART);
   p.off_sup = take(4 * m + 4);
-  p.off_rho = p.off_R0 = p.off_R1 = p.off_cix = p.off_len = p.off_tci = p.off_teid = 0;
+  p.off_rho = p.off_R0 = p.off_R1 = p.off_cix = p.off_len = 0;
   p.off_acct = 0;
   p.off_ce = 0;
   for (uint32_t j = 0; j <= HMAX; ++j) {
@@ -204,8 +202,6 @@ Dev carve(const Plan& p, void* ws, const uint32_t* rp, const uint32_t* ci, uint3
     d.R[1] = (uint32_t*)at(p.off_R1);
     d.cix = (uint32_t*)at(p.off_cix);
     d.len = (uint32_t*)at(p.off_len);
-    d.tci = (uint32_t*)at(p.off_tci);
-    d.teid = (uint32_t*)at(p.off_teid);
     d.ce = (uint64_t*)at(p.off_ce);
     uint32_t* acct = (uint32_t*)at(p.off_acct);
     const size_t na = (size_t)p.n + 1;
@@ -356,15 +352,9 @@ void launch_step(const Dev* devs, uint32_t S, uint32_t hmax, const RoundGrid& g,
   hipLaunchKernelGGL(k_end, dim3(g.jump, S), dim3(T), 0, s, devs);
 }
 
-// Compact again once a tenth of the live edges have been peeled since the
-// last compaction (a compaction reads and writes the active slots once).
-uint32_t compact_next(uint32_t live) { return live - live / 10; }
-
 void launch_compact(const Dev& d, hipStream_t s) {
   const unsigned T = 256;
-  const unsigned g = grid_for(d.n, T / WAVE);
-  hipLaunchKernelGGL(k_compact_rows, dim3(g), dim3(T), 0, s, d);
-  hipLaunchKernelGGL(k_compact_commit, dim3(g), dim3(T), 0, s, d);
+  hipLaunchKernelGGL(k_compact, dim3(grid_for(d.n, T / 16)), dim3(T), 0, s, d);
 }
 
 hoStatus read_ctl(const Dev& d, Ctl* host, hipStream_t s) {
@@ -401,13 +391,13 @@ uint64_t recovery_sources(const Dev& d, const Ctl& c, uint32_t step) {
   const uint64_t nA = 2ull * c.nR;
   if (step <= d.h) {
     if (step == 2) return nA;
-    const uint64_t nB = c.ovf[step - 1][p] ? (uint64_t)d.n * d.W * 64
-                                           : std::min<uint64_t>(c.nev[step - 1][p], d.evcap);
+    const uint64_t nB = c.cnt[step - 1][p].ovf ? (uint64_t)d.n * d.W * 64
+                                           : std::min<uint64_t>(c.cnt[step - 1][p].nev, d.evcap);
     return nA + nB;
   }
-  if (c.ovf[d.h][p]) return (uint64_t)d.n * d.W * 64;
+  if (c.cnt[d.h][p].ovf) return (uint64_t)d.n * d.W * 64;
   if (d.h == 1) return nA;
-  return std::min<uint64_t>(c.nev[d.h][p], d.evcap);
+  return std::min<uint64_t>(c.cnt[d.h][p].nev, d.evcap);
 }
 
 // Re-run one step (2..h: level, h+1: support update) of the current round
@@ -434,7 +424,7 @@ hoStatus recover_step(const Dev& d, const RoundGrid& g, hipStream_t s, uint32_t 
     else hipLaunchKernelGGL(k_fill_support, dim3(fill_grid), dim3(T), 0, s, dp, lo, hi);
     HOCHK(tm.end(s, step <= d.h ? KT_LEVEL : KT_SUPPORT));
     HOCHK(read_ctl(d, &c, s));
-    if (c.iovf[list]) {
+    if (c.cnt[list][c.r & 1].iovf) {
       if (hi - lo == 1) return HO_ERR_INTERNAL;  // one source's items exceed the list
       win = std::max<uint64_t>(1, (hi - lo) / 2);
       continue;
@@ -1038,7 +1028,7 @@ hoStatus run_rounds_host(const Dev& d, const RoundGrid& g, hipStream_t s, bool t
     st = steps_host(d, g, s, 2, false, tm);
     if (st == HO_OK) st = read_ctl(d, &c, s);
     if (rlog && st == HO_OK) {
-      std::fprintf(rlog, "%u %u %u %u %u %u %llu", mid.r, mid.k, mid.jump, mid.nR, mid.nit[2],
+      std::fprintf(rlog, "%u %u %u %u %u %u %llu", mid.r, mid.k, mid.jump, mid.nR, mid.cnt[2][mid.r & 1].nit,
                    c.live, (unsigned long long)(c.events - before.events));
       for (uint32_t i = 0; i < NSTAT; ++i)
         std::fprintf(rlog, " %llu", (unsigned long long)(c.stat[i] - before.stat[i]));

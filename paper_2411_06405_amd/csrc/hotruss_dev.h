@@ -8,6 +8,7 @@ namespace hotruss {
 
 constexpr uint32_t HMAX = 16;            // largest hop threshold with its own ball level
 constexpr uint32_t ALIVE = 0xffffffffu;  // srem value of a slot whose edge is still in S
+constexpr uint32_t SUP_GONE = 0xffffffffu;   // sup value of a peeled edge
 constexpr uint32_t SLOT_GONE = 0x80000000u;  // in the low word of ce: the slot's edge is peeled
 constexpr int WAVE = 64;
 constexpr uint32_t CHUNK = 64;           // slots (or bitset words) per work item
@@ -43,6 +44,14 @@ __device__ inline uint32_t meta_extra(uint32_t m) { return (m >> 29) & 1u; }
 __device__ inline uint32_t meta_len(uint32_t m) { return (m >> 22) & 127u; }
 __device__ inline uint32_t meta_vstart(uint32_t m) { return m & ((1u << 22) - 1); }
 
+// List lengths of one level in a round of one parity (read as two 8-byte words).
+struct alignas(16) Cnt {
+  uint32_t nit;   // work items (level h+1: support items)
+  uint32_t iovf;  // work item list overflowed
+  uint32_t nev;   // ball-change events
+  uint32_t ovf;   // event list overflowed
+};
+
 // Device control block: the whole round state lives on the device so that
 // the round driver never needs the host between rounds.
 struct Ctl {
@@ -50,7 +59,6 @@ struct Ctl {
   uint32_t k;        // current level: edges with sup <= k-2 are peeled
   uint32_t r;        // index of the current peel round
   uint32_t nR;       // |R_r|, edges peeled in the current round
-  uint32_t nPush;    // edges whose support crossed k-2 during this round
   uint32_t live;     // edges still in S
   uint32_t levels;   // levels visited
   uint32_t done;     // decomposition finished (read by the host with halt)
@@ -59,10 +67,8 @@ struct Ctl {
   uint32_t jump;     // this round starts with a level jump
   uint64_t events;   // top-level ball-change events (statistics)
   uint64_t overflows;
-  uint32_t nev[HMAX + 1][2];  // events per level and round parity
-  uint32_t ovf[HMAX + 1][2];  // event list overflowed
-  uint32_t nit[HMAX + 2];     // work items per level (index h+1: support items)
-  uint32_t iovf[HMAX + 2];    // work item list overflowed
+  Cnt cnt[HMAX + 2][2];  // per level (h+1: support items) and round parity
+  uint32_t nPush[2];          // edges whose support crossed k-2 in a round of this parity
   uint32_t compactions;  // adjacency compactions done (statistics)
   uint32_t recovering;   // the host is re-running an overflowed step in windows
   // stats mode: method-level work count (support evaluations and bytes of the
@@ -70,7 +76,6 @@ struct Ctl {
   uint32_t acct_nch;     // vertices whose h-ball changed this round (listed)
   uint32_t acct_nv;      // ball builds of this round (listed)
   uint32_t acct_incomplete;  // an event list overflowed: the count is a lower bound
-  uint32_t pad[2];
   uint64_t acct_evals;
   uint64_t acct_bytes;
   uint64_t levents[HMAX + 1];  // ball-change events per level, all rounds
@@ -100,8 +105,6 @@ struct Dev {
   // slots are [rp[x], rp[x] + len[x]); slots past len[x] are dead.
   uint32_t* cix;        // private column ids [2m]
   uint32_t* len;        // active slots per row [n]
-  uint32_t* tci;        // compaction staging: column ids [2m]
-  uint32_t* teid;       // compaction staging: edge ids [2m]
   // The support update's view of a slot, one 8-byte load: low word the
   // neighbour id with SLOT_GONE set once the edge is peeled, high word the
   // edge id [2m] (same row layout as cix)
@@ -133,6 +136,10 @@ struct Dev {
   uint32_t* acct_vlist;
 };
 
+// Compact again once a tenth of the live edges have been peeled since the
+// last compaction (a compaction reads and writes the active slots once).
+__host__ __device__ inline uint32_t compact_next(uint32_t live) { return live - live / 10; }
+
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & (WAVE - 1); }
 
 __device__ __forceinline__ uint64_t slot_word(uint32_t e, uint32_t y, bool gone) {
@@ -153,24 +160,46 @@ __device__ __forceinline__ bool getbit(const uint64_t* base, uint32_t W, uint32_
   return (base[(size_t)x * W + (w >> 6)] >> (w & 63)) & 1ull;
 }
 
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
-  for (int o = WAVE / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
+// Wave-wide scans and reductions on DPP moves (row shifts inside the rows of
+// 16 lanes, then row broadcasts 15 and 31): six VALU steps of a few cycles
+// each, where a __shfl step goes through the LDS crossbar and takes over 50.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp(uint32_t old, uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xf, false);
+}
+
+// Inclusive prefix sum across the wave (all 64 lanes must call).
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+  v += dpp<0x111, 0xf>(0, v);  // row_shr:1, 2, 4, 8
+  v += dpp<0x112, 0xf>(0, v);
+  v += dpp<0x114, 0xf>(0, v);
+  v += dpp<0x118, 0xf>(0, v);
+  v += dpp<0x142, 0xa>(0, v);  // row_bcast:15 into rows 1 and 3
+  v += dpp<0x143, 0xc>(0, v);  // row_bcast:31 into rows 2 and 3
   return v;
 }
 
+__device__ __forceinline__ uint32_t wave_last(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, WAVE - 1);
+}
+
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return wave_last(wave_incl_scan(v)); }
+
 __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
-  for (int o = WAVE / 2; o > 0; o >>= 1) v = min(v, (uint32_t)__shfl_xor(v, o, WAVE));
-  return v;
+  constexpr uint32_t I = 0xffffffffu;
+  v = min(v, dpp<0x111, 0xf>(I, v));
+  v = min(v, dpp<0x112, 0xf>(I, v));
+  v = min(v, dpp<0x114, 0xf>(I, v));
+  v = min(v, dpp<0x118, 0xf>(I, v));
+  v = min(v, dpp<0x142, 0xa>(I, v));
+  v = min(v, dpp<0x143, 0xc>(I, v));
+  return wave_last(v);
 }
 
 // Exclusive prefix sum across the wave (all 64 lanes must call).
 __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t* total) {
-  uint32_t incl = v;
-  for (int o = 1; o < WAVE; o <<= 1) {
-    const uint32_t t = __shfl_up(incl, o, WAVE);
-    if ((int)lane_id() >= o) incl += t;
-  }
-  *total = __shfl(incl, WAVE - 1, WAVE);
+  const uint32_t incl = wave_incl_scan(v);
+  *total = wave_last(incl);
   return incl - v;
 }
 

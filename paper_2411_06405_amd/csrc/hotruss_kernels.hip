@@ -310,6 +310,16 @@ enum { ITEM_ROW = 0, ITEM_SLOTS = 1, ITEM_WORDS = 2 };
 
 __device__ __forceinline__ uint32_t chunks_of(uint32_t nv) { return (nv + CHUNK - 1) / CHUNK; }
 
+// Item number `chunk` of a group.
+template <int MODE>
+__device__ __forceinline__ Item make_item(uint32_t kind, uint32_t extra, uint32_t x, uint32_t y,
+                                          uint32_t base, uint32_t nv, uint32_t chunk) {
+  const uint32_t vs = chunk * CHUNK, len = min(CHUNK, nv - vs);
+  if (MODE == ITEM_ROW) return Item{x, y, base, item_meta(kind, extra, len, vs)};
+  if (MODE == ITEM_SLOTS) return Item{x, y, base + vs, item_meta(0, 0, len, 0)};
+  return Item{x, y, vs, item_meta(KIND_A_WORDS, 0, len, 0)};
+}
+
 // Lane 0 reserves `total` entries of a counter for the whole wave.
 __device__ __forceinline__ uint32_t reserve_wave(uint32_t* counter, uint32_t total) {
   uint32_t b = 0;
@@ -321,9 +331,16 @@ __device__ __forceinline__ uint32_t reserve_wave(uint32_t* counter, uint32_t tot
 // first + excl + cnt) of list `list` (excl: exclusive prefix of cnt over the
 // wave, total: the wave's sum; both from wave_excl_scan).
 template <int MODE>
-__device__ void emit_items_wave(const Dev& d, uint32_t list, uint32_t first, uint32_t total,
+__device__ void emit_items_wave(const Dev& d, uint32_t p, uint32_t list, uint32_t first, uint32_t total,
                                 uint32_t excl, uint32_t cnt, uint32_t kind, uint32_t extra,
                                 uint32_t x, uint32_t y, uint32_t base, uint32_t nv) {
+  if (!__ballot(cnt > 1)) {
+    // at most one item per lane (most rows fit one chunk): no owner to look up
+    const uint32_t idx = first + excl;
+    if (cnt && idx < d.itcap) d.itl[list][idx] = make_item<MODE>(kind, extra, x, y, base, nv, 0);
+    if (__ballot(cnt && idx >= d.itcap)) d.ctl->cnt[list][p].iovf = 1;
+    return;
+  }
   const uint32_t incl = excl + cnt;
   bool over = false;
   for (uint32_t t0 = 0; t0 < total; t0 += WAVE) {
@@ -339,45 +356,40 @@ __device__ void emit_items_wave(const Dev& d, uint32_t list, uint32_t first, uin
     const uint32_t ob = __shfl(base, own, WAVE), onv = __shfl(nv, own, WAVE);
     const uint32_t oex = __shfl(excl, own, WAVE);
     if (t < total) {
-      const uint32_t vs = (t - oex) * CHUNK;
-      const uint32_t len = min(CHUNK, onv - vs);
-      Item it;
-      if (MODE == ITEM_ROW) it = Item{ox, oy, ob, item_meta(kind, extra, len, vs)};
-      else if (MODE == ITEM_SLOTS) it = Item{ox, oy, ob + vs, item_meta(0, 0, len, 0)};
-      else it = Item{ox, oy, vs, item_meta(KIND_A_WORDS, 0, len, 0)};
       const uint32_t idx = first + t;
-      if (idx < d.itcap) d.itl[list][idx] = it;
+      if (idx < d.itcap)
+        d.itl[list][idx] = make_item<MODE>(kind, extra, ox, oy, ob, onv, t - oex);
       else over = true;
     }
   }
-  if (over) d.ctl->iovf[list] = 1;
+  if (over) d.ctl->cnt[list][p].iovf = 1;
 }
 
 // One group per lane with its own reservation.
 template <int MODE>
-__device__ void emit_group(const Dev& d, uint32_t list, uint32_t kind, uint32_t extra, uint32_t x,
-                           uint32_t y, uint32_t base, uint32_t nv) {
+__device__ void emit_group(const Dev& d, uint32_t p, uint32_t list, uint32_t kind, uint32_t extra,
+                           uint32_t x, uint32_t y, uint32_t base, uint32_t nv) {
   const uint32_t cnt = chunks_of(nv);
   uint32_t total;
   const uint32_t excl = wave_excl_scan(cnt, &total);
   if (!total) return;
-  const uint32_t first = reserve_wave(&d.ctl->nit[list], total);
-  emit_items_wave<MODE>(d, list, first, total, excl, cnt, kind, extra, x, y, base, nv);
+  const uint32_t first = reserve_wave(&d.ctl->cnt[list][p].nit, total);
+  emit_items_wave<MODE>(d, p, list, first, total, excl, cnt, kind, extra, x, y, base, nv);
 }
 
 // Support items of event (a -> w): the live edges (a,b), CHUNK slots per item.
-__device__ void emit_support_items(const Dev& d, bool active, uint32_t a, uint32_t w) {
+__device__ void emit_support_items(const Dev& d, uint32_t p, bool active, uint32_t a, uint32_t w) {
   uint32_t base = 0, deg = 0;
   if (active) {
     base = d.rp[a];
     deg = row_end(d, a) - base;
   }
-  emit_group<ITEM_SLOTS>(d, d.h + 1, 0, 0, a, w, base, deg);
+  emit_group<ITEM_SLOTS>(d, p, d.h + 1, 0, 0, a, w, base, deg);
 }
 
 // Items over z's old (j-1)-ball words for candidates (x, w), j >= 3.
-__device__ void emit_word_items(const Dev& d, uint32_t j, bool active, uint32_t x, uint32_t z) {
-  emit_group<ITEM_WORDS>(d, j, 0, 0, x, z, 0, active ? d.W : 0u);
+__device__ void emit_word_items(const Dev& d, uint32_t p, uint32_t j, bool active, uint32_t x, uint32_t z) {
+  emit_group<ITEM_WORDS>(d, p, j, 0, 0, x, z, 0, active ? d.W : 0u);
 }
 
 // ---- level-jump minimum ----------------------------------------------------
@@ -387,25 +399,18 @@ __device__ void emit_word_items(const Dev& d, uint32_t j, bool active, uint32_t 
 // the initial pass.
 __device__ void jump_partials(const Dev& d) {
   __shared__ uint32_t smin[4];
-  // four edges per thread in flight: both loads unconditional
-  uint32_t mn = 0xffffffffu;
+  // eight edges per thread in flight; peeled edges hold SUP_GONE
+  uint32_t mn = SUP_GONE;
   const uint32_t stride = gridDim.x * blockDim.x;
   uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-  for (; e + 3 * stride < d.m; e += 4 * stride) {
-    uint32_t tv[4], sv[4];
+  for (; e + 7 * stride < d.m; e += 8 * stride) {
+    uint32_t sv[8];
 #pragma unroll
-    for (uint32_t u = 0; u < 4; ++u) {
-      tv[u] = d.t[e + u * stride];
-      sv[u] = d.sup[e + u * stride];
-    }
+    for (uint32_t u = 0; u < 8; ++u) sv[u] = d.sup[e + u * stride];
 #pragma unroll
-    for (uint32_t u = 0; u < 4; ++u)
-      if (tv[u] == 0) mn = min(mn, sv[u]);
+    for (uint32_t u = 0; u < 8; ++u) mn = min(mn, sv[u]);
   }
-  for (; e < d.m; e += stride) {
-    const uint32_t tv = d.t[e], sv = d.sup[e];
-    if (tv == 0) mn = min(mn, sv);
-  }
+  for (; e < d.m; e += stride) mn = min(mn, d.sup[e]);
   mn = wave_min(mn);
   if (lane_id() == 0) smin[threadIdx.x / WAVE] = mn;
   __syncthreads();
@@ -426,6 +431,7 @@ __device__ void mark_edge(const Dev& d, const RoundCtx& rc, bool valid, uint32_t
   if (valid) {
     d.t[e] = rc.k;
     d.rho[e] = rc.r;
+    d.sup[e] = SUP_GONE;  // the level-jump scans read only this array
     const uint32_t q1 = d.s1[e], q2 = d.s2[e];
     d.srem[q1] = rc.r;
     d.srem[q2] = rc.r;
@@ -443,8 +449,8 @@ __device__ void mark_edge(const Dev& d, const RoundCtx& rc, bool valid, uint32_t
     d.evl[1][rc.p][2 * i + 1] = ((uint64_t)b << 32) | a;
   }
   if (d.h == 1) {
-    emit_support_items(d, valid, a, b);
-    emit_support_items(d, valid, b, a);
+    emit_support_items(d, rc.p, valid, a, b);
+    emit_support_items(d, rc.p, valid, b, a);
     return;
   }
   // level 2: a lost neighbour b (candidates (a, y), y in b's old neighbourhood,
@@ -466,15 +472,94 @@ __device__ void mark_edge(const Dev& d, const RoundCtx& rc, bool valid, uint32_t
   uint32_t t0, t1, t2, t3;
   const uint32_t e0 = wave_excl_scan(n0, &t0), e1 = wave_excl_scan(n1, &t1);
   const uint32_t e2 = wave_excl_scan(n2, &t2), e3 = wave_excl_scan(n3, &t3);
-  const uint32_t first = reserve_wave(&d.ctl->nit[2], t0 + t1 + t2 + t3);
-  emit_items_wave<ITEM_ROW>(d, 2, first, t0, e0, n0, KIND_A_SLOTS, 1, a, b, bb, v0);
-  emit_items_wave<ITEM_ROW>(d, 2, first + t0, t1, e1, n1, KIND_A_SLOTS, 1, b, a, ba, v1);
-  emit_items_wave<ITEM_ROW>(d, 2, first + t0 + t1, t2, e2, n2, KIND_B_SLOTS, 0, a, b, ba, v2);
-  emit_items_wave<ITEM_ROW>(d, 2, first + t0 + t1 + t2, t3, e3, n3, KIND_B_SLOTS, 0, b, a, bb,
+  const uint32_t first = reserve_wave(&d.ctl->cnt[2][rc.p].nit, t0 + t1 + t2 + t3);
+  emit_items_wave<ITEM_ROW>(d, rc.p, 2, first, t0, e0, n0, KIND_A_SLOTS, 1, a, b, bb, v0);
+  emit_items_wave<ITEM_ROW>(d, rc.p, 2, first + t0, t1, e1, n1, KIND_A_SLOTS, 1, b, a, ba, v1);
+  emit_items_wave<ITEM_ROW>(d, rc.p, 2, first + t0 + t1, t2, e2, n2, KIND_B_SLOTS, 0, a, b, ba, v2);
+  emit_items_wave<ITEM_ROW>(d, rc.p, 2, first + t0 + t1 + t2, t3, e3, n3, KIND_B_SLOTS, 0, b, a, bb,
                             v3);
   for (uint32_t j = 3; j <= d.h; ++j) {
-    emit_word_items(d, j, valid, a, b);
-    emit_word_items(d, j, valid, b, a);
+    emit_word_items(d, rc.p, j, valid, a, b);
+    emit_word_items(d, rc.p, j, valid, b, a);
+  }
+}
+
+// One peeled edge, by a whole wave (e the same in all lanes): no lane waits for
+// another's row, and the items need no owner search -- lane t writes item t.
+// Small rounds are bound by this chain of dependent loads and atomics, not by
+// bytes.
+__device__ void mark_edge_wave(const Dev& d, const RoundCtx& rc, uint32_t e, uint32_t i) {
+  const uint32_t lane = lane_id();
+  const uint32_t a = d.eu[e], b = d.ev[e], q1 = d.s1[e], q2 = d.s2[e];
+  const uint32_t ba = d.rp[a], da = d.len[a], bb = d.rp[b], db = d.len[b];
+  if (lane == 0) {
+    d.t[e] = rc.k;
+    d.rho[e] = rc.r;
+    d.sup[e] = SUP_GONE;
+    d.srem[q1] = rc.r;
+    d.srem[q2] = rc.r;
+    d.ce[q1] = slot_word(e, b, true);
+    d.ce[q2] = slot_word(e, a, true);
+    atomicAnd(&row(d.L[1], d.W, a)[b >> 6], ~(1ull << (b & 63)));
+    atomicAnd(&row(d.L[1], d.W, b)[a >> 6], ~(1ull << (a & 63)));
+    if (d.h == 1) {
+      atomicOr(&row(d.Dm[1], d.W, a)[b >> 6], 1ull << (b & 63));
+      atomicOr(&row(d.Dm[1], d.W, b)[a >> 6], 1ull << (a & 63));
+    }
+    d.evl[1][rc.p][2 * i] = ((uint64_t)a << 32) | b;
+    d.evl[1][rc.p][2 * i + 1] = ((uint64_t)b << 32) | a;
+  }
+  // the groups of mark_edge: at h = 1 the two support rows; else the four row
+  // groups of level 2, and per level j >= 3 the two ball rows' words
+  const uint32_t v0 = d.h == 1 ? da : db + 1, v1 = d.h == 1 ? db : da + 1;
+  const uint32_t n0 = chunks_of(v0), n1 = chunks_of(v1);
+  const uint32_t n2 = d.h == 1 ? 0 : chunks_of(da), n3 = d.h == 1 ? 0 : chunks_of(db);
+  const uint32_t nw = chunks_of(d.W), rows = n0 + n1 + n2 + n3;
+  uint32_t base = 0;
+  if (lane == 0 || lane + 2 <= d.h)  // lane l reserves the items of list l + 2
+    base = atomicAdd(&d.ctl->cnt[lane + 2][rc.p].nit, lane == 0 ? rows : 2 * nw);
+  const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)base, 0);
+  bool over = false;
+  for (uint32_t t = lane; t < rows; t += WAVE) {
+    Item it;
+    if (d.h == 1)
+      it = t < n0 ? make_item<ITEM_SLOTS>(0, 0, a, b, ba, v0, t)
+                  : make_item<ITEM_SLOTS>(0, 0, b, a, bb, v1, t - n0);
+    else if (t < n0) it = make_item<ITEM_ROW>(KIND_A_SLOTS, 1, a, b, bb, v0, t);
+    else if (t < n0 + n1) it = make_item<ITEM_ROW>(KIND_A_SLOTS, 1, b, a, ba, v1, t - n0);
+    else if (t < n0 + n1 + n2) it = make_item<ITEM_ROW>(KIND_B_SLOTS, 0, a, b, ba, da, t - n0 - n1);
+    else it = make_item<ITEM_ROW>(KIND_B_SLOTS, 0, b, a, bb, db, t - n0 - n1 - n2);
+    if (first + t < d.itcap) d.itl[2][first + t] = it;
+    else over = true;
+  }
+  if (over) d.ctl->cnt[2][rc.p].iovf = 1;
+  for (uint32_t j = 3; j <= d.h; ++j) {
+    const uint32_t at = __shfl(base, j - 2, WAVE);
+    over = false;
+    for (uint32_t t = lane; t < 2 * nw; t += WAVE) {
+      const Item it = t < nw ? make_item<ITEM_WORDS>(0, 0, a, b, 0, d.W, t)
+                             : make_item<ITEM_WORDS>(0, 0, b, a, 0, d.W, t - nw);
+      if (at + t < d.itcap) d.itl[j][at + t] = it;
+      else over = true;
+    }
+    if (over) d.ctl->cnt[j][rc.p].iovf = 1;
+  }
+}
+
+// Clear the change marks that the previous round (parity q) set at level j,
+// from its event list.  At levels j >= 2 every bit set now is from the
+// previous round (this round sets its own in the ball-change step, later), so
+// whole words are zeroed with plain stores; level 1 (h = 1 only) gets this
+// round's marks while this runs, so its old bits are cleared one by one.
+__device__ void clear_marks(const Dev& d, uint32_t j, uint32_t q, uint32_t ne, uint32_t first,
+                            uint32_t stride) {
+  uint64_t* D = d.Dm[j];
+  const uint64_t* E = d.evl[j][q];
+  for (uint32_t i = first; i < ne; i += stride) {
+    const uint64_t xw = *(E + i);
+    const uint32_t x = (uint32_t)(xw >> 32), w = (uint32_t)xw;
+    if (j >= 2) row(D, d.W, x)[w >> 6] = 0;
+    else atomicAnd(&row(D, d.W, x)[w >> 6], ~(1ull << (w & 63)));
   }
 }
 
@@ -504,8 +589,8 @@ k_mark(const Dev* __restrict__ devs) {
     }
     for (uint32_t base = wbase; base < d.m; base += wstride) {
       const uint32_t e = base + lane;
-      const uint32_t tv = e < d.m ? d.t[e] : 1u, sv = e < d.m ? d.sup[e] : 0xffffffffu;
-      const bool take = tv == 0 && sv <= rc.k - 2;
+      const uint32_t sv = e < d.m ? d.sup[e] : SUP_GONE;
+      const bool take = sv != SUP_GONE && sv <= rc.k - 2;
       if (!__ballot(take)) continue;  // nothing to peel in these 64 edges
       const uint32_t i = wave_reserve(&c->nR, take ? 1u : 0u);
       if (take) d.R[rc.p][i] = e;
@@ -514,11 +599,11 @@ k_mark(const Dev* __restrict__ devs) {
   } else {
     const uint32_t nR = c->nR;
     if (nR <= wstride / WAVE) {
-      // no more peeled edges than wavefronts: one edge per wavefront (lane 0
-      // holds it), so the 64 lanes share the writing of its work items --
-      // the rows of a hub endpoint are hundreds of items
+      // no more peeled edges than wavefronts: one edge per wavefront, so the
+      // 64 lanes share the writing of its work items -- the rows of a hub
+      // endpoint are hundreds of items
       const uint32_t i = wbase / WAVE;
-      if (i < nR) mark_edge(d, rc, lane == 0, lane == 0 ? d.R[rc.p][i] : 0, i);
+      if (i < nR) mark_edge_wave(d, rc, d.R[rc.p][i], i);
     } else {
       for (uint32_t base = wbase; base < nR; base += wstride) {
         const uint32_t i = base + lane;
@@ -527,31 +612,18 @@ k_mark(const Dev* __restrict__ devs) {
       }
     }
   }
-  // clear the change marks of the previous round: the whole array of a level
-  // whose event list overflowed, else the listed events.  At levels j >= 2 every bit set now is from
-  // the previous round (this round sets its own in k_level, later), so whole
-  // words are zeroed with plain stores; level 1 (h = 1 only) gets this
-  // round's marks in this launch, so its old bits are cleared one by one.
+  // the change marks of a level whose event list overflowed: its whole array
   for (uint32_t j = 2; j <= d.h; ++j) {
-    if (!c->ovf[j][q]) continue;
+    if (!c->cnt[j][q].ovf) continue;
     uint64_t* D = d.Dm[j];
     const size_t cnt = (size_t)d.n * d.W;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < cnt;
          i += (size_t)gridDim.x * blockDim.x)
       D[i] = 0;
   }
-  for (uint32_t j = 1; j <= d.h; ++j) {
-    uint64_t* D = d.Dm[j];
-    if (!D || c->ovf[j][q]) continue;
-    const uint32_t ne = c->nev[j][q];
-    const uint64_t* E = d.evl[j][q];
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < ne; i += wstride) {
-      const uint64_t xw = E[i];
-      const uint32_t x = (uint32_t)(xw >> 32), w = (uint32_t)xw;
-      if (j >= 2) row(D, d.W, x)[w >> 6] = 0;
-      else atomicAnd(&row(D, d.W, x)[w >> 6], ~(1ull << (w & 63)));
-    }
-  }
+  for (uint32_t j = 1; j <= d.h; ++j)
+    if (d.Dm[j] && !c->cnt[j][q].ovf)
+      clear_marks(d, j, q, c->cnt[j][q].nev, blockIdx.x * blockDim.x + threadIdx.x, wstride);
 }
 
 // ---- K3: ball-change events at level j >= 2 ----------------------------
@@ -602,90 +674,145 @@ __device__ uint32_t block_scan_cap(const uint32_t* v, uint32_t* out, uint32_t n,
   return tot;
 }
 
-// Level-j events.  Each workgroup turns its share of work items into
+// LDS of one workgroup of the ball-change step.  flag[] is all zero between
+// steps.
+template <uint32_t LV_THREADS, uint32_t LV_CAP>
+struct LevelLds {
+  // a candidate: the pair, the endpoint whose ball is probed, the other one's
+  // row, its first probe's number, and whether a witness was found
+  uint32_t x[LV_CAP], w[LV_CAP], b[LV_CAP], beg[LV_CAP], off[LV_CAP], flag[LV_CAP];
+  uint32_t dense[LV_DENSE];  // candidates tested by bitset rows (see the flush)
+  uint32_t ndense, busy[2];
+  unsigned long long fill;    // candidates (low half) and their probes (high half)
+  unsigned long long res[2];  // a drop pass's items (low half) and events (high half)
+  uint32_t bres[2];           // ... and where the workgroup's start
+  uint32_t stat[5];  // stats mode: items, slots, candidates, probes, drops
+};
+
+// Level-j events.  Each workgroup turns its share of the nit work items into
 // candidate pairs (quick filters: still in the j-ball, not directly
 // reachable), buffers them in LDS, then tests every buffered pair at once:
 // the pair's probes (the live neighbours y of its lower-degree endpoint a,
 // each checked against the other endpoint's (j-1)-ball) are laid out flat
 // over all threads of the workgroup.  Pairs with no witness leave the ball.
+// Most rounds give a workgroup a handful of pairs, and their time is the chain
+// of dependent loads and barriers, so a flush has as few of both as it can:
+// append() numbers the probes as pairs come, so no scan over the buffer; a
+// slot's liveness and neighbour are one word; list space is summed in LDS and
+// reserved by two lanes at once.  With the marking step's changes: Chung-Lu
+// 100k h = 2 287 -> 238 ms, R-MAT 16 h = 2 1,207 -> 1,003 ms, Chung-Lu 5,001
+// h = 3 288 -> 192 ms (there mostly the word-wise candidates) a decomposition.
+// wg of nwg workgroups call it together.
 template <uint32_t LV_THREADS, uint32_t LV_CAP>
-__global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ devs, uint32_t j) {
+__device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t nit, uint32_t wg,
+                           uint32_t nwg, LevelLds<LV_THREADS, LV_CAP>& s) {
   static_assert(LV_CAP >= 2 * LV_THREADS && LV_CAP % LV_THREADS == 0, "two emission steps fit");
   constexpr uint32_t LV_WAVES = LV_THREADS / WAVE;
-  const Dev& d = devs[blockIdx.y];
-  if (j > d.h) return;  // this slot's graph has fewer levels
-  __shared__ uint32_t cx[LV_CAP], cw[LV_CAP], cb[LV_CAP], cbeg[LV_CAP], cdeg[LV_CAP],
-      coff[LV_CAP];
-  __shared__ uint32_t cflag[LV_CAP];
-  __shared__ uint32_t cdense[LV_DENSE];  // candidates tested by bitset rows (see the flush)
-  __shared__ uint32_t s_count, s_busy[2], s_wsum[LV_WAVES], s_ndense;
-  __shared__ uint32_t s_wres[LV_WAVES][2], s_bres[2];  // per-wave and workgroup reservations
-  __shared__ uint32_t s_stat[5];  // stats mode: items, slots, candidates, probes, drops
+  uint32_t *cx = s.x, *cw = s.w, *cb = s.b, *cbeg = s.beg, *coff = s.off;
+  uint32_t *cflag = s.flag, *cdense = s.dense, *s_busy = s.busy;
   Ctl* c = d.ctl;
-  if (c->done) return;
-  if (c->halt) return;
-  // a round that peels every remaining edge leaves no ball or support that
-  // could matter: the decomposition ends with it
-  if (c->nR == c->live) return;
-  if (!c->recovering && (c->iovf[j] || (d.serial & 4u))) {
-    // work list overflowed (or forced): halt; the host re-runs this level in windows
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      c->halt = 1;
-      c->halt_step = j;
-      d.status[1] = 1;
-    }
-    return;
-  }
-  const RoundCtx rc = round_ctx(c);
-  const uint32_t nit = min(c->nit[j], d.itcap);
   const uint32_t wave = threadIdx.x / WAVE, lane = lane_id();
   // items are dealt to workgroups first, then to their waves, so a round
   // with few items still spreads its candidates (and their probes) over as
   // many CUs as it has items
-  const uint32_t stride = gridDim.x * LV_WAVES;
-  uint32_t it = wave * gridDim.x + blockIdx.x;
+  const uint32_t stride = nwg * LV_WAVES;
+  uint32_t it = wave * nwg + wg;
   const bool counting = d.spart != nullptr;
-  if (counting && threadIdx.x < 5) s_stat[threadIdx.x] = 0;
-  if (blockIdx.x >= nit) {  // whole workgroup idle
-    if (counting && threadIdx.x < 5) d.spart[threadIdx.x * STAT_GRID + blockIdx.x] = 0;
-    return;
-  }
+  if (wg >= nit) return;  // whole workgroup idle
   const uint64_t* Lj = d.L[j];
   const uint64_t* Lp = d.L[j - 1];
   const Item* items = d.itl[j];
   if (threadIdx.x == 0) {
-    s_count = 0;
+    s.fill = 0;
+    s.ndense = 0;
+    s.res[0] = s.res[1] = 0;
     s_busy[0] = s_busy[1] = 0;
   }
-  for (uint32_t i = threadIdx.x; i < LV_CAP; i += LV_THREADS) cflag[i] = 0;
-  uint32_t par = 0;
-  uint64_t wd = 0;       // KIND_A_WORDS: this lane's remaining ball word
+  uint32_t par = 0, pass = 0;
+  uint32_t next = wg;  // wave 0's next item
+  uint64_t wd = 0;       // KIND_A_WORDS: this lane's remaining candidates
+  uint32_t wbase = 0;    // ... and its word's first vertex
   bool inword = false;   // KIND_A_WORDS item in progress
+  uint32_t X = 0, Wv = 0;
+  // Append this wave's candidates (X, Wv) to the buffer.  The witness probes
+  // run over the endpoint with fewer active slots; a pair whose lower-degree
+  // endpoint has more of them than a ball row has words is tested on the
+  // bitset rows instead (see the flush).  One LDS atomic per wave reserves
+  // buffer entries (low half) and probe numbers (high half) together, so
+  // both ascend in the same order and the flush needs no scan.
+  auto append = [&](bool have, uint32_t bx, uint32_t dx, uint32_t bw, uint32_t dw) {
+    const uint64_t bal = __ballot(have);
+    if (!bal) return;
+    uint32_t deg = have ? min(dx, dw) : 0u, dslot = LV_DENSE;
+    const uint64_t bd = __ballot(deg > d.W);
+    if (bd) {
+      uint32_t at = 0;
+      if (lane == 0) at = atomicAdd(&s.ndense, (uint32_t)__popcll(bd));
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) +
+           (uint32_t)__popcll(bd & ((1ull << lane) - 1));
+      if (deg > d.W && at < LV_DENSE) {  // the rest keep their neighbour probes
+        dslot = at;
+        deg = 0;
+      }
+    }
+    uint32_t psum;
+    const uint32_t pex = wave_excl_scan(deg, &psum);
+    unsigned long long at = 0;
+    if (lane == 0)
+      at = atomicAdd(&s.fill, ((unsigned long long)psum << 32) | (uint32_t)__popcll(bal));
+    const uint32_t slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at) +
+                          (uint32_t)__popcll(bal & ((1ull << lane) - 1));
+    const uint32_t p0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) + pex;
+    if (have) {
+      cx[slot] = X;
+      cw[slot] = Wv;
+      cb[slot] = dx <= dw ? Wv : X;
+      cbeg[slot] = dx <= dw ? bx : bw;
+      coff[slot] = p0;
+      if (dslot < LV_DENSE) cdense[dslot] = slot;
+    }
+  };
   __syncthreads();
   while (true) {
-    // ---- one emission step per wave: at most one candidate per lane ----
-    bool have = false, examined = false, it_taken = false;
-    uint32_t X = 0, Wv = 0;
+    // ---- one emission step per wave: at most 64 candidates ----
+    uint32_t examined = 0;  // stats mode
+    bool it_taken = false;
+    uint32_t cands = 0;
     if (it < nit) {
       const Item I = items[it];
       const uint32_t kind = meta_kind(I.meta), len = meta_len(I.meta);
       if (kind == KIND_A_WORDS) {
+        // the candidates of a whole word at once: members of z's old
+        // (j-1)-ball that are in x's j-ball and not within j-1 hops of x
+        // (x itself is); four coalesced rows in place of two gathers per pair
         if (!inword) {
           wd = 0;
           if (lane < len) {
             const size_t o = (size_t)I.y * d.W + I.base + lane;
-            wd = d.L[j - 1][o] | d.Dm[j - 1][o];
+            const size_t ox = (size_t)I.x * d.W + I.base + lane;
+            const uint64_t old = *(Lp + o) | *(d.Dm[j - 1] + o);
+            wd = old & *(Lj + ox) & ~*(Lp + ox);
+            if (counting) examined = (uint32_t)__popcll(old);
           }
+          wbase = (I.base + lane) * 64;
           inword = true;
         }
-        if (wd) {
-          const uint32_t b = __ffsll((unsigned long long)wd) - 1;
-          wd &= wd - 1;
-          have = true;
-          X = I.x;
-          Wv = (I.base + lane) * 64 + b;
+        const uint32_t bx = d.rp[I.x], dx = d.len[I.x];
+        X = I.x;
+        while (true) {
+          const uint32_t now = (uint32_t)__popcll(__ballot(wd != 0));
+          if (!now || cands + now > WAVE) break;
+          const bool have = wd != 0;
+          uint32_t bw = 0, dw = 0;
+          if (have) {
+            Wv = wbase + (uint32_t)__ffsll((unsigned long long)wd) - 1;
+            wd &= wd - 1;
+            bw = d.rp[Wv];
+            dw = d.len[Wv];
+          }
+          append(have, bx, dx, bw, dw);
+          cands += now;
         }
-        examined = have;
         if (!__ballot(wd != 0)) {
           inword = false;
           it += stride;
@@ -694,7 +821,7 @@ __global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ de
       } else {
         const uint32_t extra = meta_extra(I.meta);
         const uint32_t v = meta_vstart(I.meta) + lane;
-        examined = lane < len;
+        bool have = false;
         if (lane < len) {
           if (extra && v == 0) {
             have = true;
@@ -702,99 +829,80 @@ __global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ de
             Wv = I.y;
           } else {
             const uint32_t q = I.base + v - extra;
-            const uint32_t sr = d.srem[q];
-            if (kind == KIND_A_SLOTS ? sr >= rc.r : sr > rc.r) {
+            // live after this round, or (KIND_A) peeled in it
+            const uint32_t sw = (uint32_t)*(d.ce + q), y2 = sw & ~SLOT_GONE;
+            if (!(sw & SLOT_GONE) || (kind == KIND_A_SLOTS && *(d.srem + q) == rc.r)) {
               have = true;
-              const uint32_t y2 = d.cix[q];
               X = (kind == KIND_A_SLOTS) ? I.x : y2;
               Wv = (kind == KIND_A_SLOTS) ? y2 : I.y;
             }
           }
         }
+        if (counting) examined = lane < len;
         it += stride;
         it_taken = true;
+        // quick filters: a real pair, still in the j-ball, not within j-1
+        // hops (both balls are symmetric, so both bits are read from the row
+        // of the smaller vertex, together with the two row extents)
+        uint32_t bx = 0, dx = 0, bw = 0, dw = 0;
+        have = have && X != Wv;
+        if (have) {
+          const size_t o = (size_t)min(X, Wv) * d.W + (max(X, Wv) >> 6);
+          const uint64_t sh = max(X, Wv) & 63;
+          const uint64_t wj = *(Lj + o), wp = *(Lp + o);
+          bx = d.rp[X];
+          dx = d.len[X];
+          bw = d.rp[Wv];
+          dw = d.len[Wv];
+          have = ((wj >> sh) & 1ull) && !((wp >> sh) & 1ull);
+        }
+        cands = (uint32_t)__popcll(__ballot(have));
+        append(have, bx, dx, bw, dw);
       }
     }
-    // quick filters: a real pair, still in the j-ball, not within j-1 hops
-    // (both balls are symmetric, so both bits are read from the row of the
-    // smaller vertex, together with the two row extents)
-    // the witness probes run over the endpoint with fewer active slots
-    uint32_t b = 0, beg = 0, deg = 0;
-    if (have) {
-      have = X != Wv;
-      if (have) {
-        const size_t o = (size_t)min(X, Wv) * d.W + (max(X, Wv) >> 6);
-        const uint64_t sh = max(X, Wv) & 63;
-        const uint64_t wj = Lj[o], wp = Lp[o];
-        const uint32_t bx = d.rp[X], dx = d.len[X];
-        const uint32_t bw = d.rp[Wv], dw = d.len[Wv];
-        b = dx <= dw ? Wv : X;
-        beg = dx <= dw ? bx : bw;
-        deg = dx <= dw ? dx : dw;
-        have = ((wj >> sh) & 1ull) && !((wp >> sh) & 1ull);
-      }
-    }
-    const uint64_t bal = __ballot(have);
     if (counting) {
-      const uint32_t nex = (uint32_t)__popcll(__ballot(examined));  // every lane votes
+      const uint32_t nex = wave_sum(examined);
       if (lane == 0) {
-        if (it_taken) atomicAdd(&s_stat[0], 1u);
-        atomicAdd(&s_stat[1], nex);
-        atomicAdd(&s_stat[2], (uint32_t)__popcll(bal));
+        if (it_taken) atomicAdd(&s.stat[0], 1u);
+        atomicAdd(&s.stat[1], nex);
+        atomicAdd(&s.stat[2], cands);
       }
     }
-    uint32_t slot = 0;
-    if (lane == 0 && bal) slot = atomicAdd(&s_count, (uint32_t)__popcll(bal));
-    slot = __shfl(slot, 0, WAVE) + (uint32_t)__popcll(bal & ((1ull << lane) - 1));
-    if (have) {
-      cx[slot] = X;
-      cw[slot] = Wv;
-      cb[slot] = b;
-      cbeg[slot] = beg;
-      cdeg[slot] = deg;
+    // more to emit: at level 2 an item takes one step, so wave 0's next item
+    // tells for the whole workgroup; above, the waves say so
+    bool busy;
+    next += stride;
+    if (j == 2) {
+      __syncthreads();  // appends visible
+      busy = next < nit;
+    } else {
+      if (lane == 0 && (it < nit || inword)) s_busy[par] = 1u;
+      __syncthreads();  // appends and flags visible
+      busy = s_busy[par] != 0;
+      par ^= 1;
+      if (threadIdx.x == 0) s_busy[par] = 0;
     }
-    __syncthreads();  // appends visible
-    if (lane == 0 && (it < nit || inword)) atomicOr(&s_busy[par], 1u);
-    __syncthreads();  // flags visible
-    const bool busy = s_busy[par] != 0;
-    const uint32_t n = s_count;
-    __syncthreads();  // everyone has read both before anyone changes them
-    if (threadIdx.x == 0) s_busy[par ^ 1] = 0;
-    par ^= 1;
+    const uint32_t n = (uint32_t)s.fill, total = (uint32_t)(s.fill >> 32);
+    const uint32_t ndense = min(s.ndense, LV_DENSE);
     if (n == 0 && !busy) break;
-    if (n + LV_THREADS <= LV_CAP && busy) continue;
-    // ---- flush: look for a witness of every buffered pair ----
-    // A pair whose lower-degree endpoint has more active slots than a ball
-    // row has words is tested on the bitset rows instead: the witnesses are
-    // exactly the members of L[1](low) & L[j-1](other) (L[1] holds the live
-    // closed neighbourhood, and low itself is not within j-1 hops of the
-    // other endpoint), so one wave ANDs the two rows and stops at the first
-    // non-zero word.  The other pairs' probes (a live neighbour y of the
-    // lower-degree endpoint, checked against the other's (j-1)-ball) are laid
-    // out flat over all threads of the workgroup.
-    if (threadIdx.x == 0) s_ndense = 0;
-    __syncthreads();
-    for (uint32_t base = 0; base < n; base += LV_THREADS) {
-      const uint32_t i = base + threadIdx.x;
-      const bool dense = i < n && cdeg[i] > d.W;
-      const uint64_t bd = __ballot(dense);  // one LDS reservation per wave
-      uint32_t at = 0;
-      if (lane == 0 && bd) at = atomicAdd(&s_ndense, (uint32_t)__popcll(bd));
-      at = __shfl(at, 0, WAVE) + (uint32_t)__popcll(bd & ((1ull << lane) - 1));
-      if (dense && at < LV_DENSE) {  // the rest keep their neighbour probes
-        cdense[at] = i;
-        cdeg[i] = 0;
-      }
+    if (n + LV_THREADS <= LV_CAP && busy) {
+      __syncthreads();  // everyone has read the counts before anyone appends
+      continue;
     }
-    __syncthreads();
-    const uint32_t total = block_scan_cap<LV_THREADS, LV_CAP>(cdeg, coff, n, s_wsum);
-    const uint32_t ndense = min(s_ndense, LV_DENSE);
-    if (counting && threadIdx.x == 0) s_stat[3] += total;
+    // ---- flush: look for a witness of every buffered pair ----
+    // The pairs' probes (a live neighbour y of the lower-degree endpoint,
+    // checked against the other's (j-1)-ball) are laid out flat over all
+    // threads of the workgroup.  A dense pair's witnesses are exactly the
+    // members of L[1](low) & L[j-1](other) (L[1] holds the live closed
+    // neighbourhood, and low itself is not within j-1 hops of the other
+    // endpoint): one wave ANDs the two rows and stops at the first non-zero
+    // word.
+    if (counting && threadIdx.x == 0) s.stat[3] += total;
     // four probes per thread in flight: owners found in LDS first, then all
     // slot loads, then all ball-word loads
     constexpr uint32_t PU = 4;
     for (uint32_t p0 = threadIdx.x; p0 < total; p0 += PU * LV_THREADS) {
-      uint32_t own[PU], q[PU], sr[PU], y[PU];
+      uint32_t own[PU], q[PU], y[PU];
       bool act[PU];
 #pragma unroll
       for (uint32_t u = 0; u < PU; ++u) {
@@ -809,13 +917,13 @@ __global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ de
         q[u] = cbeg[lo] + (pidx - coff[lo]);
       }
 #pragma unroll
-      for (uint32_t u = 0; u < PU; ++u) {
-        sr[u] = act[u] ? d.srem[q[u]] : 0u;
-        y[u] = act[u] ? d.cix[q[u]] : 0u;
-      }
+      for (uint32_t u = 0; u < PU; ++u) y[u] = act[u] ? (uint32_t)*(d.ce + q[u]) : SLOT_GONE;
 #pragma unroll
       for (uint32_t u = 0; u < PU; ++u)
-        if (act[u] && sr[u] > rc.r && getbit(Lp, d.W, cb[own[u]], y[u])) cflag[own[u]] = 1;
+        if (!(y[u] & SLOT_GONE)) {
+          const uint64_t word = *(row(Lp, d.W, cb[own[u]]) + (y[u] >> 6));
+          if ((word >> (y[u] & 63)) & 1ull) cflag[own[u]] = 1;
+        }
     }
     for (uint32_t k = wave; k < ndense; k += LV_WAVES) {
       const uint32_t i = cdense[k];
@@ -829,14 +937,14 @@ __global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ de
 #pragma unroll
         for (uint32_t u = 0; u < 4; ++u) {
           const uint32_t wi = w0 + u * WAVE + lane;
-          if (wi < d.W) any |= ra[wi] & rb[wi];
+          if (wi < d.W) any |= *(ra + wi) & *(rb + wi);
         }
         words += min(4 * WAVE, d.W - w0);
         found = __ballot(any != 0) != 0;
       }
       if (lane == 0) {
         if (found) cflag[i] = 1;
-        if (counting) atomicAdd(&s_stat[3], words);  // a word pair counts as one probe
+        if (counting) atomicAdd(&s.stat[3], words);  // a word pair counts as one probe
       }
     }
     __syncthreads();
@@ -844,18 +952,22 @@ __global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ de
     for (uint32_t base = 0; base < n; base += LV_THREADS) {
       const uint32_t i = base + threadIdx.x;
       const bool drop = i < n && !cflag[i];
-      uint32_t x = 0, w = 0;
+      uint32_t x = 0, w = 0, bx = 0, dx = 0, bw = 0, dw = 0;
       bool w1 = false, w2 = false;
       if (drop) {
         x = cx[i];
         w = cw[i];
-        const uint64_t bx = 1ull << (w & 63), bw = 1ull << (x & 63);
-        w1 = atomicAnd(&row(d.L[j], d.W, x)[w >> 6], ~bx) & bx;
-        w2 = atomicAnd(&row(d.L[j], d.W, w)[x >> 6], ~bw) & bw;
-        if (w1) atomicOr(&row(d.Dm[j], d.W, x)[w >> 6], bx);
-        if (w2) atomicOr(&row(d.Dm[j], d.W, w)[x >> 6], bw);
+        bx = d.rp[x];
+        dx = d.len[x];
+        bw = d.rp[w];
+        dw = d.len[w];
+        const uint64_t mx = 1ull << (w & 63), mw = 1ull << (x & 63);
+        w1 = atomicAnd(&row(d.L[j], d.W, x)[w >> 6], ~mx) & mx;
+        w2 = atomicAnd(&row(d.L[j], d.W, w)[x >> 6], ~mw) & mw;
+        if (w1) atomicOr(&row(d.Dm[j], d.W, x)[w >> 6], mx);
+        if (w2) atomicOr(&row(d.Dm[j], d.W, w)[x >> 6], mw);
       }
-      if (counting && (w1 || w2)) atomicAdd(&s_stat[4], (uint32_t)w1 + (uint32_t)w2);
+      if (counting && (w1 || w2)) atomicAdd(&s.stat[4], (uint32_t)w1 + (uint32_t)w2);
       // Follow-up work of both events: the events themselves, and items over
       // the row of each event's source -- the support update (j == h), else
       // the next level's candidates (y, w) over that row plus (x, w) itself.
@@ -864,40 +976,28 @@ __global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ de
       // with drops.
       const uint32_t extra = j == d.h ? 0u : 1u;
       const uint32_t list = j == d.h ? d.h + 1 : j + 1;
-      uint32_t bx = 0, nx = 0, bw = 0, nw = 0;
-      if (w1) {
-        bx = d.rp[x];
-        nx = row_end(d, x) - bx + extra;
-      }
-      if (w2) {
-        bw = d.rp[w];
-        nw = row_end(d, w) - bw + extra;
-      }
+      const uint32_t nx = w1 ? dx + extra : 0, nw = w2 ? dw + extra : 0;
       const uint32_t c1 = chunks_of(nx), c2 = chunks_of(nw);
       const uint32_t ne = (uint32_t)w1 + (uint32_t)w2;
       uint32_t t1, t2, te;
       const uint32_t e1 = wave_excl_scan(c1, &t1), e2 = wave_excl_scan(c2, &t2);
       const uint32_t ee = wave_excl_scan(ne, &te);
-      if (lane == 0) {
-        s_wres[wave][0] = t1 + t2;
-        s_wres[wave][1] = te;
-      }
+      unsigned long long off = 0;
+      if (lane == 0 && te)
+        off = atomicAdd(&s.res[pass], ((unsigned long long)te << 32) | (t1 + t2));
       __syncthreads();
-      if (threadIdx.x == 0) {
-        uint32_t ti = 0, tv = 0;
-        for (uint32_t v = 0; v < LV_WAVES; ++v) {
-          ti += s_wres[v][0];
-          tv += s_wres[v][1];
-        }
-        s_bres[0] = ti ? atomicAdd(&d.ctl->nit[list], ti) : 0u;
-        s_bres[1] = tv ? atomicAdd(&d.ctl->nev[j][rc.p], tv) : 0u;
+      if (threadIdx.x < 2) {
+        const unsigned long long sum = s.res[pass];
+        const uint32_t v = threadIdx.x ? (uint32_t)(sum >> 32) : (uint32_t)sum;
+        uint32_t* at = threadIdx.x ? &c->cnt[j][rc.p].nev : &c->cnt[list][rc.p].nit;
+        s.bres[threadIdx.x] = v ? atomicAdd(at, v) : 0u;
+        s.res[pass ^ 1] = 0;
       }
+      pass ^= 1;
       __syncthreads();
-      uint32_t ifirst = s_bres[0], efirst = s_bres[1];
-      for (uint32_t v = 0; v < wave; ++v) {
-        ifirst += s_wres[v][0];
-        efirst += s_wres[v][1];
-      }
+      const uint32_t ifirst = s.bres[0] + (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)off);
+      const uint32_t efirst =
+          s.bres[1] + (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(off >> 32));
       {
         const uint64_t exw = ((uint64_t)x << 32) | w, ewx = ((uint64_t)w << 32) | x;
         const uint32_t slot = efirst + ee;
@@ -906,68 +1006,80 @@ __global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ de
           if (slot + k < d.evcap) d.evl[j][rc.p][slot + k] = (k || !w1) ? ewx : exw;
           else over = true;
         }
-        if (over) d.ctl->ovf[j][rc.p] = 1;
+        if (over) c->cnt[j][rc.p].ovf = 1;
       }
       if (j == d.h) {
         // support items carry the slot base of their chunk
-        emit_items_wave<ITEM_SLOTS>(d, list, ifirst, t1, e1, c1, 0, 0, x, w, bx, nx);
-        emit_items_wave<ITEM_SLOTS>(d, list, ifirst + t1, t2, e2, c2, 0, 0, w, x, bw, nw);
+        emit_items_wave<ITEM_SLOTS>(d, rc.p, list, ifirst, t1, e1, c1, 0, 0, x, w, bx, nx);
+        emit_items_wave<ITEM_SLOTS>(d, rc.p, list, ifirst + t1, t2, e2, c2, 0, 0, w, x, bw, nw);
       } else {
-        emit_items_wave<ITEM_ROW>(d, list, ifirst, t1, e1, c1, KIND_B_SLOTS, 1, x, w, bx, nx);
-        emit_items_wave<ITEM_ROW>(d, list, ifirst + t1, t2, e2, c2, KIND_B_SLOTS, 1, w, x, bw,
+        emit_items_wave<ITEM_ROW>(d, rc.p, list, ifirst, t1, e1, c1, KIND_B_SLOTS, 1, x, w, bx, nx);
+        emit_items_wave<ITEM_ROW>(d, rc.p, list, ifirst + t1, t2, e2, c2, KIND_B_SLOTS, 1, w, x, bw,
                                   nw);
       }
-      __syncthreads();  // s_wres and s_bres are reused by the next pass
     }
-    __syncthreads();
     for (uint32_t i = threadIdx.x; i < n; i += LV_THREADS) cflag[i] = 0;
-    if (threadIdx.x == 0) s_count = 0;
+    if (threadIdx.x == 0) {
+      s.fill = 0;
+      s.ndense = 0;
+    }
     __syncthreads();
     if (!busy) break;
   }
-  if (counting) {
+}
+
+template <uint32_t LV_THREADS, uint32_t LV_CAP>
+__global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ devs, uint32_t j) {
+  __shared__ LevelLds<LV_THREADS, LV_CAP> s;
+  const Dev& d = devs[blockIdx.y];
+  if (j > d.h) return;  // this slot's graph has fewer levels
+  Ctl* c = d.ctl;
+  if (c->done) return;
+  if (c->halt) return;
+  // a round that peels every remaining edge leaves no ball or support that
+  // could matter: the decomposition ends with it
+  if (c->nR == c->live) return;
+  const RoundCtx rc = round_ctx(c);
+  if (!c->recovering && (c->cnt[j][rc.p].iovf || (d.serial & 4u))) {
+    // work list overflowed (or forced): halt; the host re-runs this level in windows
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      c->halt = 1;
+      c->halt_step = j;
+      d.status[1] = 1;
+    }
+    return;
+  }
+  for (uint32_t i = threadIdx.x; i < LV_CAP; i += LV_THREADS) s.flag[i] = 0;
+  if (threadIdx.x < 5) s.stat[threadIdx.x] = 0;
+  __syncthreads();
+  level_step<LV_THREADS, LV_CAP>(d, rc, j, min(c->cnt[j][rc.p].nit, d.itcap), blockIdx.x,
+                                        gridDim.x, s);
+  if (d.spart) {
     __syncthreads();
-    if (threadIdx.x < 5) d.spart[threadIdx.x * STAT_GRID + blockIdx.x] = s_stat[threadIdx.x];
+    if (threadIdx.x < 5) d.spart[threadIdx.x * STAT_GRID + blockIdx.x] = s.stat[threadIdx.x];
   }
 }
+
 
 // ---- K4: support update --------------------------------------------------
 // Top-level event (a -> w): every live edge (a,b) that had w as a common
 // h-neighbour loses it.  Old/new rule: w counts against (a,b) if it was in
 // b's old ball when a < b, and in b's new ball when a > b (see the header).
-__global__ void __launch_bounds__(256) k_support(const Dev* __restrict__ devs) {
-  const Dev& d = devs[blockIdx.y];
-  Ctl* c = d.ctl;
-  if (c->done) return;
-  const uint32_t list = d.h + 1;
-  if (c->halt) return;
-  if (c->nR == c->live) return;  // the last round: nothing left to update
-  if (!c->recovering && (c->iovf[list] || (d.serial & 8u))) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      c->halt = 1;
-      c->halt_step = list;
-      d.status[1] = 1;
-    }
-    return;
-  }
-  const RoundCtx rc = round_ctx(c);
-  const uint32_t nit = min(c->nit[list], d.itcap);
-  const uint32_t lane = lane_id(), wpb = blockDim.x / WAVE;
-  __shared__ uint32_t s_stat[3];  // stats mode: items, slots, hits
-  const bool counting = d.spart != nullptr;
-  if (counting) {
-    if (threadIdx.x < 3) s_stat[threadIdx.x] = 0;
-    __syncthreads();
-  }
+// wg of nwg workgroups of `wpb` waves call it together; stat: stats mode only.
+template <uint32_t U>
+__device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint32_t wg,
+                             uint32_t nwg, uint32_t wpb, uint32_t* stat) {
+  const uint32_t lane = lane_id();
   const uint64_t* Lh = d.L[d.h];
   const uint64_t* Dh = d.Dm[d.h];
   uint32_t* Rn = d.R[rc.p ^ 1];
-  const Item* items = d.itl[list];
-  const uint32_t stride = gridDim.x * wpb;
+  const Item* items = d.itl[d.h + 1];
+  uint32_t* nPush = &d.ctl->nPush[rc.p];
+  const uint32_t stride = nwg * wpb;
   // Items are dealt to workgroups first, then to their waves.  Each wave
-  // takes two items per step (its items it and it + stride), and the step's
+  // takes U items per step (its items it, it + stride, ...), and the step's
   // successors and their slots (state, neighbour, edge id) load while the
-  // current pair's ball words and support atomics are in flight: more memory
+  // current items' ball words and support atomics are in flight: more memory
   // operations outstanding per wave than one item's dependent chain.
   // a slot is one 8-byte word: neighbour b (with SLOT_GONE once the edge is
   // peeled, i.e. not alive after this round) and edge id e
@@ -982,7 +1094,7 @@ __global__ void __launch_bounds__(256) k_support(const Dev* __restrict__ devs) {
     if (i < nit) {
       S.I = items[i];
       if (lane < meta_len(S.I.meta)) {
-        const uint64_t w = d.ce[S.I.base + lane];
+        const uint64_t w = *(d.ce + S.I.base + lane);
         S.b = (uint32_t)w;
         S.e = (uint32_t)(w >> 32);
       }
@@ -992,36 +1104,80 @@ __global__ void __launch_bounds__(256) k_support(const Dev* __restrict__ devs) {
   auto hit_of = [&](const Slot& S) -> bool {
     if (S.b & SLOT_GONE) return false;
     const size_t o = (size_t)S.I.y * d.W + (S.b >> 6);
-    uint64_t word = Lh[o];
-    if (S.I.x < S.b) word |= Dh[o];
+    uint64_t word = *(Lh + o);
+    if (S.I.x < S.b) word |= *(Dh + o);
     return (word >> (S.b & 63)) & 1ull;
   };
-  uint32_t it = (threadIdx.x / WAVE) * gridDim.x + blockIdx.x;
-  Slot A, B;
-  fetch(it, A);
-  fetch(it + stride, B);
+  uint32_t it = (threadIdx.x / WAVE) * nwg + wg;
+  Slot A[U];
+#pragma unroll
+  for (uint32_t u = 0; u < U; ++u) fetch(it + u * stride, A[u]);
   while (it < nit) {
-    const bool ha = hit_of(A), hb = hit_of(B);
-    Slot A2, B2;
-    fetch(it + 2 * stride, A2);
-    fetch(it + 3 * stride, B2);
-    const bool pa = ha && atomicSub(&d.sup[A.e], 1u) == rc.k - 1;
-    const bool pb = hb && atomicSub(&d.sup[B.e], 1u) == rc.k - 1;
-    const uint32_t slot = wave_reserve(&c->nPush, (uint32_t)pa + (uint32_t)pb);
-    if (pa) Rn[slot] = A.e;
-    if (pb) Rn[slot + (uint32_t)pa] = B.e;
-    if (counting) {
-      const uint32_t hits = (uint32_t)__popcll(__ballot(ha)) + (uint32_t)__popcll(__ballot(hb));
+    bool hit[U], push[U];
+    uint32_t e[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      hit[u] = hit_of(A[u]);
+      e[u] = A[u].e;
+    }
+    if (stat) {
+      uint32_t hits = 0, slots = 0, taken = 0;
+      for (uint32_t u = 0; u < U; ++u) {
+        hits += (uint32_t)__popcll(__ballot(hit[u]));
+        slots += meta_len(A[u].I.meta);
+        taken += it + u * stride < nit;
+      }
       if (lane == 0) {
-        atomicAdd(&s_stat[0], 1u + (it + stride < nit ? 1u : 0u));
-        atomicAdd(&s_stat[1], meta_len(A.I.meta) + meta_len(B.I.meta));
-        atomicAdd(&s_stat[2], hits);
+        atomicAdd(&stat[0], taken);
+        atomicAdd(&stat[1], slots);
+        atomicAdd(&stat[2], hits);
       }
     }
-    A = A2;
-    B = B2;
-    it += 2 * stride;
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) fetch(it + (U + u) * stride, A[u]);
+    bool any = false;
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      push[u] = hit[u] && atomicSub(&d.sup[e[u]], 1u) == rc.k - 1;
+      any |= push[u];
+    }
+    if (__ballot(any)) {
+      uint32_t mine = 0;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) mine += push[u];
+      uint32_t slot = wave_reserve(nPush, mine);
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u)
+        if (push[u]) Rn[slot++] = e[u];
+    }
+    it += U * stride;
   }
+}
+
+__global__ void __launch_bounds__(256) k_support(const Dev* __restrict__ devs) {
+  const Dev& d = devs[blockIdx.y];
+  Ctl* c = d.ctl;
+  if (c->done) return;
+  const uint32_t list = d.h + 1;
+  if (c->halt) return;
+  if (c->nR == c->live) return;  // the last round: nothing left to update
+  const RoundCtx rc = round_ctx(c);
+  if (!c->recovering && (c->cnt[list][rc.p].iovf || (d.serial & 8u))) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      c->halt = 1;
+      c->halt_step = list;
+      d.status[1] = 1;
+    }
+    return;
+  }
+  __shared__ uint32_t s_stat[3];  // stats mode: items, slots, hits
+  const bool counting = d.spart != nullptr;
+  if (counting) {
+    if (threadIdx.x < 3) s_stat[threadIdx.x] = 0;
+    __syncthreads();
+  }
+  support_step<2>(d, rc, min(c->cnt[list][rc.p].nit, d.itcap), blockIdx.x, gridDim.x,
+                      blockDim.x / WAVE, counting ? s_stat : nullptr);
   if (counting) {
     __syncthreads();
     if (threadIdx.x < 3) d.spart[(5 + threadIdx.x) * STAT_GRID + blockIdx.x] = s_stat[threadIdx.x];
@@ -1048,6 +1204,12 @@ __global__ void k_stats_fold(const Dev* __restrict__ dp, uint32_t first, uint32_
     d.ctl->stat[threadIdx.x] += acc[threadIdx.x];
 }
 
+// The counters of one round parity back to zero.
+__device__ __forceinline__ void reset_parity(Ctl* c, uint32_t h, uint32_t q) {
+  for (uint32_t j = 1; j <= h + 1; ++j) c->cnt[j][q] = Cnt{0, 0, 0, 0};
+  c->nPush[q] = 0;
+}
+
 // ---- K5: end of round ------------------------------------------------------
 // One thread closes the round (counters, next round's peel set and level-jump
 // flag).  When the round pushed no edge, the next round starts with a level
@@ -1061,33 +1223,27 @@ __global__ void __launch_bounds__(256) k_end(const Dev* __restrict__ devs) {
   // one decision per workgroup, taken before its closing thread (workgroup 0)
   // changes anything, so that every thread of it takes the same branch
   __shared__ uint32_t s_mode;  // 0 close only, 1 minimum and close, 2 nothing
-  if (threadIdx.x == 0) s_mode = (c->done || c->halt) ? 2u : (c->nPush == 0 ? 1u : 0u);
+  if (threadIdx.x == 0) s_mode = (c->done || c->halt) ? 2u : (c->nPush[c->r & 1] == 0 ? 1u : 0u);
   __syncthreads();
   const uint32_t mode = s_mode;
   if (mode == 2) return;
   if (mode == 1) jump_partials(d);
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
   const uint32_t p = c->r & 1, q = p ^ 1;
-  c->nev[1][p] = 2 * c->nR;  // level-1 events: both directions of every peeled edge
-  c->events += c->nev[d.h][p];
-  for (uint32_t j = 1; j <= d.h; ++j) c->levents[j] += c->nev[j][p];
-  c->jump = c->nPush == 0;
+  const uint32_t pushed = c->nPush[p];
+  c->cnt[1][p].nev = 2 * c->nR;  // level-1 events: both directions of every peeled edge
+  c->events += c->cnt[d.h][p].nev;
+  for (uint32_t j = 1; j <= d.h; ++j) c->levents[j] += c->cnt[j][p].nev;
   uint32_t any = 0;
-  for (uint32_t j = 1; j <= d.h; ++j) {
-    any |= c->ovf[j][p];
-    c->nev[j][q] = 0;
-    c->ovf[j][q] = 0;
-  }
-  for (uint32_t j = 0; j <= d.h + 1; ++j) {
-    any |= c->iovf[j];
-    c->nit[j] = 0;
-    c->iovf[j] = 0;
-  }
+  for (uint32_t j = 1; j <= d.h + 1; ++j) any |= c->cnt[j][p].ovf | c->cnt[j][p].iovf;
+  // the other parity's counters, for the next round (this round's stay: the
+  // next one clears the change marks they list and peels the edges it pushed)
+  reset_parity(c, d.h, q);
   c->overflows += any ? 1 : 0;
   c->live -= c->nR;
   c->r += 1;
-  c->nR = c->nPush;
-  c->nPush = 0;
+  c->nR = pushed;
+  c->jump = pushed == 0;
   d.status[2] = c->live;
   if (c->live == 0) {
     c->done = 1;
@@ -1116,20 +1272,20 @@ __global__ void k_post_init(Dev d) {
 // the bits of the level-(j-1) change marks (row-major, 64 per word).
 
 // Follow-up items of the event (x -> w) at list `list` (all lanes call).
-__device__ __forceinline__ void fill_event_items(const Dev& d, uint32_t list, bool support,
+__device__ __forceinline__ void fill_event_items(const Dev& d, uint32_t p, uint32_t list, bool support,
                                                  bool has, uint32_t x, uint32_t w) {
   uint32_t bx = 0, nx = 0;
   if (has) {
     bx = d.rp[x];
     nx = d.len[x] + (support ? 0u : 1u);
   }
-  if (support) emit_group<ITEM_SLOTS>(d, list, 0, 0, x, w, bx, nx);
-  else emit_group<ITEM_ROW>(d, list, KIND_B_SLOTS, 1, x, w, bx, nx);
+  if (support) emit_group<ITEM_SLOTS>(d, p, list, 0, 0, x, w, bx, nx);
+  else emit_group<ITEM_ROW>(d, p, list, KIND_B_SLOTS, 1, x, w, bx, nx);
 }
 
 // Change-mark bits [blo, bhi) of level jm as events (x -> w): follow-up
 // items at `list` (support items when `support`).
-__device__ void fill_from_marks(const Dev& d, uint32_t jm, uint32_t list, bool support,
+__device__ void fill_from_marks(const Dev& d, uint32_t p, uint32_t jm, uint32_t list, bool support,
                                 uint64_t blo, uint64_t bhi) {
   if (blo >= bhi) return;
   const uint64_t wlo = blo / 64, whi = (bhi + 63) / 64;
@@ -1153,7 +1309,7 @@ __device__ void fill_from_marks(const Dev& d, uint32_t jm, uint32_t list, bool s
         w = word * 64 + (uint32_t)(__ffsll((unsigned long long)wd) - 1);
         wd &= wd - 1;
       }
-      fill_event_items(d, list, support, has, x, w);
+      fill_event_items(d, p, list, support, has, x, w);
     }
   }
 }
@@ -1179,7 +1335,7 @@ __device__ void fill_from_list(const Dev& d, uint32_t je, bool removals, uint32_
         w = (uint32_t)xw;
       }
     }
-    fill_event_items(d, list, support, has, x, w);
+    fill_event_items(d, p, list, support, has, x, w);
   }
 }
 
@@ -1215,17 +1371,17 @@ __global__ void __launch_bounds__(256) k_fill_level(const Dev* __restrict__ dp, 
       const uint32_t n0 = chunks_of(v0), n1 = chunks_of(v1);
       uint32_t t0, t1;
       const uint32_t e0 = wave_excl_scan(n0, &t0), e1 = wave_excl_scan(n1, &t1);
-      const uint32_t first = reserve_wave(&d.ctl->nit[2], t0 + t1);
-      emit_items_wave<ITEM_ROW>(d, 2, first, t0, e0, n0, KIND_A_SLOTS, 1, x, z, bz, v0);
-      emit_items_wave<ITEM_ROW>(d, 2, first + t0, t1, e1, n1, KIND_B_SLOTS, 0, x, z, bx, v1);
+      const uint32_t first = reserve_wave(&d.ctl->cnt[2][rc.p].nit, t0 + t1);
+      emit_items_wave<ITEM_ROW>(d, rc.p, 2, first, t0, e0, n0, KIND_A_SLOTS, 1, x, z, bz, v0);
+      emit_items_wave<ITEM_ROW>(d, rc.p, 2, first + t0, t1, e1, n1, KIND_B_SLOTS, 0, x, z, bx, v1);
     } else {
-      emit_word_items(d, j, a, x, z);  // (x, w), w in z's old (j-1)-ball
+      emit_word_items(d, rc.p, j, a, x, z);  // (x, w), w in z's old (j-1)-ball
     }
   }
   // the level-(j-1) events (x -> w): (y, w), y a live neighbour of x, and (x, w)
   if (j == 2 || hi <= nA) return;
   const uint64_t blo = lo > nA ? lo - nA : 0, bhi = hi - nA;
-  if (c->ovf[j - 1][rc.p]) fill_from_marks(d, j - 1, j, false, blo, bhi);
+  if (c->cnt[j - 1][rc.p].ovf) fill_from_marks(d, rc.p, j - 1, j, false, blo, bhi);
   else fill_from_list(d, j - 1, false, rc.p, j, false, blo, bhi);
 }
 
@@ -1236,7 +1392,7 @@ __global__ void __launch_bounds__(256) k_fill_support(const Dev* __restrict__ dp
   const Dev& d = *dp;
   const Ctl* c = d.ctl;
   const RoundCtx rc = round_ctx(c);
-  if (c->ovf[d.h][rc.p]) fill_from_marks(d, d.h, d.h + 1, true, lo, hi);
+  if (c->cnt[d.h][rc.p].ovf) fill_from_marks(d, rc.p, d.h, d.h + 1, true, lo, hi);
   else fill_from_list(d, d.h, d.h == 1, rc.p, d.h + 1, true, lo, hi);
 }
 
@@ -1244,8 +1400,8 @@ __global__ void __launch_bounds__(256) k_fill_support(const Dev* __restrict__ dp
 __global__ void k_window_begin(const Dev* __restrict__ dp, uint32_t list) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
   Ctl* c = dp->ctl;
-  c->nit[list] = 0;
-  c->iovf[list] = 0;
+  c->cnt[list][c->r & 1].nit = 0;
+  c->cnt[list][c->r & 1].iovf = 0;
   c->halt = 0;
   c->recovering = 1;
   dp->status[1] = 0;
@@ -1256,49 +1412,53 @@ __global__ void k_recovery_end(const Dev* __restrict__ dp) {
   dp->ctl->recovering = 0;
 }
 
-// ---- adjacency compaction (between rounds, host-triggered) --------------
+// ---- adjacency compaction (between rounds) -------------------------------
 // Keep each row's live slots at its front, in order, so that later rounds
-// scan only live ones.  Runs only at a round boundary of a running slot:
-// both kernels see the same (finished / halted) state and do nothing then.
-__global__ void __launch_bounds__(256) k_compact_rows(Dev d) {
-  const Ctl* c = d.ctl;
-  if (c->done || c->halt) return;
-  const uint32_t lane = lane_id(), wpb = blockDim.x / WAVE;
-  for (uint32_t x = blockIdx.x * wpb + threadIdx.x / WAVE; x < d.n; x += gridDim.x * wpb) {
-    const uint32_t beg = d.rp[x], n = d.len[x];
+// scan only live ones.  Sixteen lanes per row, four rows per wave: most rows
+// are short, and what bounds the step is the chain of dependent loads per row,
+// not bytes.  In place: a chunk's slots are read before any is written, and
+// slots only move to the front, never past a chunk still to be read.
+__device__ void compact_rows(const Dev& d, uint32_t wave, uint32_t nwaves) {
+  constexpr uint32_t G = 16;
+  const uint32_t g = lane_id() / G, sub = lane_id() & (G - 1);
+  for (uint32_t x0 = wave * (WAVE / G); x0 < d.n; x0 += nwaves * (WAVE / G)) {
+    const uint32_t x = x0 + g;
+    const uint32_t beg = x < d.n ? d.rp[x] : 0, n = x < d.n ? d.len[x] : 0;
     uint32_t kept = 0;
-    for (uint32_t i0 = 0; i0 < n; i0 += WAVE) {
-      const uint32_t i = i0 + lane;
-      const bool live = i < n && d.srem[beg + i] == ALIVE;
-      const uint64_t bal = __ballot(live);
-      if (live) {
-        const uint32_t pos = kept + (uint32_t)__popcll(bal & ((1ull << lane) - 1));
-        d.tci[beg + pos] = d.cix[beg + i];
-        d.teid[beg + pos] = d.eid[beg + i];
+    for (uint32_t i0 = 0; __ballot(i0 < n); i0 += G) {
+      const uint32_t i = i0 + sub, q = beg + i;
+      uint64_t w = SLOT_GONE;
+      uint32_t y = 0, e = 0;
+      if (i < n) {
+        w = *(d.ce + q);
+        y = d.cix[q];
+        e = (uint32_t)(w >> 32);
       }
-      kept += (uint32_t)__popcll(bal);
+      const bool live = !((uint32_t)w & SLOT_GONE);
+      const uint32_t bal = (uint32_t)(__ballot(live) >> (g * G)) & ((1u << G) - 1);
+      const uint32_t at = kept + (uint32_t)__popc(bal & ((1u << sub) - 1));
+      if (live && at != i) {
+        const uint32_t z = beg + at;
+        d.cix[z] = y;
+        d.eid[z] = e;
+        d.srem[z] = ALIVE;
+        d.ce[z] = w;
+        if (y > x) d.s1[e] = z;
+        else d.s2[e] = z;
+      }
+      kept += (uint32_t)__popc(bal);
     }
-    if (lane == 0) d.len[x] = kept;
+    if (x < d.n && sub == 0 && kept != n) d.len[x] = kept;
   }
 }
 
-__global__ void __launch_bounds__(256) k_compact_commit(Dev d) {
+// Host-driven rounds: runs only at a round boundary of a running slot.
+__global__ void __launch_bounds__(256) k_compact(Dev d) {
   Ctl* c = d.ctl;
   if (c->done || c->halt) return;
   if (blockIdx.x == 0 && threadIdx.x == 0) c->compactions += 1;
-  const uint32_t lane = lane_id(), wpb = blockDim.x / WAVE;
-  for (uint32_t x = blockIdx.x * wpb + threadIdx.x / WAVE; x < d.n; x += gridDim.x * wpb) {
-    const uint32_t beg = d.rp[x], n = d.len[x];
-    for (uint32_t i = lane; i < n; i += WAVE) {
-      const uint32_t q = beg + i, y = d.tci[q], e = d.teid[q];
-      d.cix[q] = y;
-      d.eid[q] = e;
-      d.srem[q] = ALIVE;
-      d.ce[q] = slot_word(e, y, false);
-      if (y > x) d.s1[e] = q;
-      else d.s2[e] = q;
-    }
-  }
+  compact_rows(d, blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE,
+               gridDim.x * (blockDim.x / WAVE));
 }
 
 // Private adjacency copy and full rows, before the first round.
@@ -1426,11 +1586,11 @@ __global__ void __launch_bounds__(256) k_acct_round1(const Dev* __restrict__ dp)
     atomicSub(&d.acct_deg[(i & 1) ? d.ev[e] : d.eu[e]], 1u);
   }
   const bool from_removals = d.h == 1;
-  if (!from_removals && c->ovf[d.h][rc.p]) {
+  if (!from_removals && c->cnt[d.h][rc.p].ovf) {
     if (tid == 0) c->acct_incomplete = 1;
     return;
   }
-  const uint32_t ne = from_removals ? 2 * nR : min(c->nev[d.h][rc.p], d.evcap);
+  const uint32_t ne = from_removals ? 2 * nR : min(c->cnt[d.h][rc.p].nev, d.evcap);
   for (uint32_t i = tid; i < ne; i += stride) {
     uint32_t x;
     if (from_removals) {
