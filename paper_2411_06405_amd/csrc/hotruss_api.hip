@@ -32,10 +32,11 @@ struct Plan {
   uint32_t n = 0, h = 0, W = 0, evcap = 0, itcap = 0;
   uint64_t m = 0;
   bool full = true;  // decomposition (false: support only)
+  bool renumber = false;  // vertices renumbered by degree
   size_t off_ctl, off_eid, off_eu, off_ev, off_s1, off_s2, off_srem, off_upcnt, off_upoff,
       off_scan, off_minpart, off_sup, off_rho, off_R0, off_R1, off_L[HMAX + 1],
       off_Dm[HMAX + 1], off_evl[HMAX + 1][2], off_itl[HMAX + 2], off_cix, off_len, off_acct,
-      off_ce;
+      off_ce, off_perm, off_inv, off_rp, off_oe, off_ne, off_t;
   size_t total = 0;
 };
 
@@ -48,14 +49,22 @@ uint32_t clamp_cap(uint64_t want, uint64_t lo, uint64_t hi) {
   return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(want, lo), hi);
 }
 
+// Renumbering pays once a ball row is many cache lines and rows are read in
+// work items (h >= 2): R-MAT 18 h = 2 5.46 -> 4.96 s, the h-support of R-MAT 17
+// 11.1 -> 8.8 ms.  BA 12,345 (1.5 KiB a row) lost 5%, Chung-Lu 100k at h = 1 4%.
+constexpr uint32_t RENUMBER_MIN_N = 32768;
+
+// may_renumber false: the smaller layout, for a graph that the memory at hand
+// does not hold otherwise (and for the H-index method, which reads the caller's).
 bool make_plan(uint32_t n, uint64_t m, uint32_t h, const hoTuning* tune, bool full, Plan* P,
-               uint64_t cap_factor = 128) {
+               uint64_t cap_factor = 128, bool may_renumber = true) {
   if (h == 0 || m >= (1ull << 31) || n == 0xffffffffu) return false;
   if (n > 1 && h > n - 1) h = n - 1;  // any h beyond n-1 is the same as n-1
   if (h == 0) h = 1;
   if (h > HMAX) return false;
   Plan p;
   p.n = n; p.m = m; p.h = h; p.full = full;
+  p.renumber = may_renumber && h >= 2 && n >= RENUMBER_MIN_N;
   p.W = words_per_row(n);
   // Lists are sized so that a round rarely overflows them (a round that does
   // re-runs the overflowed step from the host in windows that fit).
@@ -83,7 +92,13 @@ bool make_plan(uint32_t n, uint64_t m, uint32_t h, const hoTuning* tune, bool fu
   p.off_minpart = take(4 * MIN_PART);
   p.off_sup = take(4 * m + 4);
   p.off_rho = take(full ? 4 * m + 4 : 0);
-  p.off_cix = take(full ? 8 * m + 4 : 0);
+  p.off_cix = take(full || p.renumber ? 8 * m + 4 : 0);
+  p.off_perm = take(p.renumber ? 4 * (size_t)n + 4 : 0);
+  p.off_inv = take(p.renumber ? 4 * (size_t)n + 4 : 0);
+  p.off_rp = take(p.renumber ? 4 * ((size_t)n + 1) : 0);
+  p.off_oe = take(p.renumber ? 4 * m + 4 : 0);
+  p.off_ne = take(p.renumber ? 4 * m + 4 : 0);
+  p.off_t = take(p.renumber && full ? 4 * m + 4 : 0);
   p.off_len = take(full ? 4 * (size_t)n + 4 : 0);
   p.off_R0 = take(full ? 4 * m + 4 : 0);
   p.off_R1 = take(full ? 4 * m + 4 : 0);
@@ -131,6 +146,7 @@ bool make_topo_plan(uint32_t n, uint64_t m, Plan* P, size_t* off_cc) {
   p.off_scan = take(4 * ((size_t)n / 1024 + 2));
   p.off_minpart = take(4 * MIN_PART);
   p.off_sup = take(4 * m + 4);
+  p.off_perm = p.off_inv = p.off_rp = p.off_oe = p.off_ne = p.off_t = 0;
   p.off_rho = p.off_R0 = p.off_R1 = p.off_cix = p.off_len = 0;
   p.off_acct = 0;
   p.off_ce = 0;
@@ -173,7 +189,17 @@ Dev carve(const Plan& p, void* ws, const uint32_t* rp, const uint32_t* ci, uint3
   auto at = [&](size_t off) { return (void*)(base + off); };
   Dev d;
   memset(&d, 0, sizeof d);
+  d.orp = rp; d.oci = ci;
   d.rp = rp; d.ci = ci;
+  if (p.renumber) {
+    d.perm = (uint32_t*)at(p.off_perm);
+    d.inv = (uint32_t*)at(p.off_inv);
+    d.oe = (uint32_t*)at(p.off_oe);
+    d.ne = (uint32_t*)at(p.off_ne);
+    d.rp = (const uint32_t*)at(p.off_rp);
+    d.cix = (uint32_t*)at(p.off_cix);
+    d.ci = d.cix;
+  }
   d.n = p.n; d.m = (uint32_t)p.m; d.h = p.h; d.W = p.W;
   d.nnz = (uint32_t)(2 * p.m);
   d.evcap = p.evcap;
@@ -195,8 +221,11 @@ Dev carve(const Plan& p, void* ws, const uint32_t* rp, const uint32_t* ci, uint3
   d.spart = nullptr;  // set in stats mode
   d.status = nullptr;
   d.sup = (uint32_t*)at(p.off_sup);
-  d.t = t;
-  d.rho = rho ? rho : (p.full ? (uint32_t*)at(p.off_rho) : nullptr);
+  d.out_t = t;
+  d.out_rho = rho;
+  const bool own = p.renumber && p.full;
+  d.t = own ? (uint32_t*)at(p.off_t) : t;
+  d.rho = rho && !own ? rho : (p.full ? (uint32_t*)at(p.off_rho) : nullptr);
   if (p.full) {
     d.R[0] = (uint32_t*)at(p.off_R0);
     d.R[1] = (uint32_t*)at(p.off_R1);
@@ -250,24 +279,49 @@ struct EventGuard {
   } while (0)
 
 // Canonical edge ids, ball build and initial h-support into out_sup.
+// Exclusive prefix sum of up_cnt.
+void run_scan(const Dev& d, uint32_t* out, hipStream_t s) {
+  const uint32_t nb = (d.n + 1023) / 1024;
+  hipLaunchKernelGGL(k_scan1, dim3(nb ? nb : 1), dim3(256), 0, s, d.up_cnt, out, d.scan_tmp, d.n);
+  hipLaunchKernelGGL(k_scan2, dim3(1), dim3(64), 0, s, d.scan_tmp, nb);
+  hipLaunchKernelGGL(k_scan3, dim3(grid_for(d.n, 256)), dim3(256), 0, s, out, d.scan_tmp, d.n);
+}
+
 // CSR validation and canonical edge ids (slot <-> edge maps).
 void run_topology(const Dev& d, hipStream_t s) {
   const unsigned T = 256;
-  hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(64), 0, s, d.ctl, d.m);
+  hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(256), 0, s, d.ctl, d.n, d.W, d.m);
   hipLaunchKernelGGL(k_check_rowptr, dim3(grid_for(d.n + 1, T)), dim3(T), 0, s, d);
   hipLaunchKernelGGL(k_row_upper, dim3(grid_for(d.n, T / WAVE)), dim3(T), 0, s, d);
-  const uint32_t nb = (d.n + 1023) / 1024;
-  hipLaunchKernelGGL(k_scan1, dim3(nb ? nb : 1), dim3(256), 0, s, d.up_cnt, d.up_off,
-                     d.scan_tmp, d.n);
-  hipLaunchKernelGGL(k_scan2, dim3(1), dim3(64), 0, s, d.scan_tmp, nb);
-  hipLaunchKernelGGL(k_scan3, dim3(grid_for(d.n, T)), dim3(T), 0, s, d.up_off, d.scan_tmp, d.n);
+  run_scan(d, d.up_off, s);
   hipLaunchKernelGGL(k_edge_ids, dim3(grid_for(d.n, T / WAVE)), dim3(T), 0, s, d);
+}
+
+// The renumbered adjacency (d.perm set).
+void run_renumber(const Dev& d, hipStream_t s) {
+  const unsigned tiles = (d.n + DEG_TILE - 1) / DEG_TILE;
+  hipLaunchKernelGGL(k_degree_count, dim3(tiles), dim3(256), 0, s, d);
+  hipLaunchKernelGGL(k_degree_starts, dim3(1), dim3(256), 0, s, d);
+  hipLaunchKernelGGL(k_degree_place, dim3(tiles), dim3(256), 0, s, d);
+  run_scan(d, const_cast<uint32_t*>(d.rp), s);
+  hipLaunchKernelGGL(k_rows_lower, dim3(grid_for(d.n, 4)), dim3(256), 0, s, d);
+  run_scan(d, d.up_off, s);
+  hipLaunchKernelGGL(k_rows_long, dim3(grid_for(d.n, 64, 2)), dim3(1024), 0, s, d);
+  hipLaunchKernelGGL(k_rows_short, dim3(grid_for(d.n, 4)), dim3(256), 0, s, d);
+  if (d.ce) hipLaunchKernelGGL(k_rows_edges, dim3(grid_for(d.nnz, 256)), dim3(256), 0, s, d);
 }
 
 hoStatus run_init(const Dev& d, uint32_t* out_sup, const hoTuning* tune, hipStream_t s,
                   hipEvent_t sup0 = nullptr, hipEvent_t sup1 = nullptr) {
   const unsigned T = 256;
   run_topology(d, s);
+  if (d.perm) run_renumber(d, s);
+  // change marks first: what the first round reads is then still in the
+  // memory-side cache, which this would sweep
+  for (uint32_t j = 1; j <= d.h; ++j)
+    if (d.Dm[j])
+      hipLaunchKernelGGL(k_clear_rows, dim3(grid_for((size_t)d.n * d.W, T)), dim3(T), 0, s, d,
+                         d.Dm[j]);
   const size_t lds = (size_t)d.W * 8;
   const unsigned rows_grid = grid_for(d.n, 1, 64);
   hipLaunchKernelGGL(k_build_L1, dim3(rows_grid), dim3(T), lds, s, d);
@@ -279,14 +333,15 @@ hoStatus run_init(const Dev& d, uint32_t* out_sup, const hoTuning* tune, hipStre
   if (!epw) epw = d.W <= 8 ? 16 : d.W <= 32 ? 4 : 1;
   if (sup0) HIPCHK(hipEventRecord(sup0, s));
   const bool wide = tune && tune->word_bits == 128;
+  const bool by_caller = out_sup != d.sup;  // the rounds keep supports by own edge number
 #define HO_SUPINIT(G)                                                                       \
   do {                                                                                      \
     if (wide)                                                                               \
       hipLaunchKernelGGL((k_support_init<G, 2>), dim3(grid_for(d.m, T / G)), dim3(T), 0, s, \
-                         d, out_sup);                                                       \
+                         d, out_sup, by_caller);                                            \
     else                                                                                    \
       hipLaunchKernelGGL((k_support_init<G, 1>), dim3(grid_for(d.m, T / G)), dim3(T), 0, s, \
-                         d, out_sup);                                                       \
+                         d, out_sup, by_caller);                                            \
   } while (0)
   if (epw >= 16) HO_SUPINIT(4);
   else if (epw >= 8) HO_SUPINIT(8);
@@ -297,6 +352,11 @@ hoStatus run_init(const Dev& d, uint32_t* out_sup, const hoTuning* tune, hipStre
   if (sup1) HIPCHK(hipEventRecord(sup1, s));
   HIPCHK(hipGetLastError());
   return HO_OK;
+}
+
+// A finished graph's outputs.
+void launch_outputs(const Dev& d, hipStream_t s) {
+  if (d.ne && d.m) hipLaunchKernelGGL(k_outputs, dim3(grid_for(d.m, 256)), dim3(256), 0, s, d);
 }
 
 // Launch geometry of the round kernels (x: workgroups per slot).
@@ -388,14 +448,14 @@ struct StepTimer {
 // Recovery sources of a step (see k_fill_level / k_fill_support).
 uint64_t recovery_sources(const Dev& d, const Ctl& c, uint32_t step) {
   const uint32_t p = c.r & 1;
-  const uint64_t nA = 2ull * c.nR;
+  const uint64_t nA = 2ull * c.nRc.v;
   if (step <= d.h) {
     if (step == 2) return nA;
-    const uint64_t nB = c.cnt[step - 1][p].ovf ? (uint64_t)d.n * d.W * 64
+    const uint64_t nB = c.cnt[step - 1][p].ovf ? (uint64_t)c.nact * d.W * 64
                                            : std::min<uint64_t>(c.cnt[step - 1][p].nev, d.evcap);
     return nA + nB;
   }
-  if (c.cnt[d.h][p].ovf) return (uint64_t)d.n * d.W * 64;
+  if (c.cnt[d.h][p].ovf) return (uint64_t)c.nact * d.W * 64;
   if (d.h == 1) return nA;
   return std::min<uint64_t>(c.cnt[d.h][p].nev, d.evcap);
 }
@@ -729,6 +789,9 @@ class Engine {
 
   size_t need_bytes(uint32_t n, uint64_t m, uint32_t h, const hoTuning* tune, Plan* p) const {
     if (!make_plan(n, m, h, tune, true, p, cap_factor)) return 0;
+    if (p->total > bytes - engine_header_bytes(S) &&
+        !make_plan(n, m, h, tune, true, p, cap_factor, false))
+      return 0;
     return p->total;
   }
 
@@ -780,13 +843,8 @@ class Engine {
   hoStatus start_slot(const Dev& d, const hoTuning* tune, hipEvent_t sup0 = nullptr,
                       hipEvent_t sup1 = nullptr) {
     const unsigned T = 256;
-    hipLaunchKernelGGL(k_fill32, dim3(grid_for(d.m, T)), dim3(T), 0, s, d.t, (size_t)d.m, 0u);
-    for (uint32_t j = 1; j <= d.h; ++j)
-      if (d.Dm[j])
-        hipLaunchKernelGGL(k_fill64, dim3(grid_for((size_t)d.n * d.W, T)), dim3(T), 0, s, d.Dm[j],
-                           (size_t)d.n * d.W, 0ull);
     HOCHK(run_init(d, d.sup, tune, s, sup0, sup1));
-    hipLaunchKernelGGL(k_init_rows, dim3(grid_for(d.nnz, T)), dim3(T), 0, s, d);
+    if (!d.perm) hipLaunchKernelGGL(k_init_rows, dim3(grid_for(d.nnz, T)), dim3(T), 0, s, d);
     const size_t i = (size_t)(d.self - devs_d);
     dev_h[i] = d;
     HIPCHK(hipMemcpyAsync(d.self, &dev_h[i], sizeof(Dev), hipMemcpyHostToDevice, s));
@@ -862,6 +920,7 @@ class Engine {
       Request& r = reqs[ri];
       r.state = 2;
       r.result = sw[0] == 2 ? HO_ERR_BAD_CSR : HO_OK;
+      if (sw[0] == 1) launch_outputs(slot_dev[i], s);
       // park the slot before its memory can be handed to another request:
       // replays already in flight still read the old, finished control block
       if (hipMemcpyAsync(devs_d + i, &idle_h[i], sizeof(Dev), hipMemcpyHostToDevice, s) !=
@@ -1028,7 +1087,7 @@ hoStatus run_rounds_host(const Dev& d, const RoundGrid& g, hipStream_t s, bool t
     st = steps_host(d, g, s, 2, false, tm);
     if (st == HO_OK) st = read_ctl(d, &c, s);
     if (rlog && st == HO_OK) {
-      std::fprintf(rlog, "%u %u %u %u %u %u %llu", mid.r, mid.k, mid.jump, mid.nR, mid.cnt[2][mid.r & 1].nit,
+      std::fprintf(rlog, "%u %u %u %u %u %u %llu", mid.r, mid.k, mid.jump, mid.nRc.v, mid.cnt[2][mid.r & 1].nit,
                    c.live, (unsigned long long)(c.events - before.events));
       for (uint32_t i = 0; i < NSTAT; ++i)
         std::fprintf(rlog, " %llu", (unsigned long long)(c.stat[i] - before.stat[i]));
@@ -1071,7 +1130,7 @@ void* scratch_base(int dev) {
 
 // Bytes of scratch a decomposition of (n, m, h) takes (0: invalid arguments).
 size_t noalloc_bytes(uint32_t n, uint64_t m, uint32_t h, Plan* p) {
-  if (!make_plan(n, m, h, nullptr, true, p, 16)) return 0;
+  if (!make_plan(n, m, h, nullptr, true, p, 16, false)) return 0;
   return up(sizeof(Dev)) + up(4ull * HO_STATUS_WORDS) + p->total;
 }
 
@@ -1099,7 +1158,7 @@ struct HxPlan {
 
 bool make_hx_plan(uint32_t n, uint64_t m, uint32_t h, HxPlan* out) {
   HxPlan q;
-  if (!make_plan(n, m, h, nullptr, false, &q.p)) return false;
+  if (!make_plan(n, m, h, nullptr, false, &q.p, 128, false)) return false;
   size_t o = q.p.total - ALIGN;
   auto take = [&](size_t bytes) { size_t r = o; o += up(bytes); return r; };
   const size_t W = q.p.W;
@@ -1233,6 +1292,7 @@ hoStatus hoTrussDecompose(const uint32_t* row_ptr, const uint32_t* col_idx, uint
       HIPCHK(hipGetLastError());
     }
     HOCHK(run_rounds_host(d, g, stream, stats, out.kernel_ms, out.kernel_launches));
+    launch_outputs(d, stream);
   } else {
     HOCHK(eng.run());
     if (eng.reqs[id].state != 2) return HO_ERR_INTERNAL;
@@ -1294,13 +1354,8 @@ hoStatus hoTrussDecomposeNoAlloc(const uint32_t* row_ptr, const uint32_t* col_id
   // the array keeps the previous call's contents: every buffer that must
   // start at a known value is written before it is read
   hipLaunchKernelGGL(k_fill32, dim3(1), dim3(64), 0, stream, status, (size_t)HO_STATUS_WORDS, 0u);
-  hipLaunchKernelGGL(k_fill32, dim3(grid_for(d.m, T)), dim3(T), 0, stream, d.t, (size_t)d.m, 0u);
-  for (uint32_t j = 1; j <= d.h; ++j)
-    if (d.Dm[j])
-      hipLaunchKernelGGL(k_fill64, dim3(grid_for((size_t)d.n * d.W, T)), dim3(T), 0, stream,
-                         d.Dm[j], (size_t)d.n * d.W, 0ull);
   HOCHK(run_init(d, d.sup, nullptr, stream));
-  hipLaunchKernelGGL(k_init_rows, dim3(grid_for(d.nnz, T)), dim3(T), 0, stream, d);
+  if (!d.perm) hipLaunchKernelGGL(k_init_rows, dim3(grid_for(d.nnz, T)), dim3(T), 0, stream, d);
   // the descriptor goes to the device from a host stack copy (staged by the
   // runtime, so the copy is complete when the call returns)
   HIPCHK(hipMemcpyAsync(dself, &d, sizeof(Dev), hipMemcpyHostToDevice, stream));
@@ -1312,6 +1367,7 @@ hoStatus hoTrussDecomposeNoAlloc(const uint32_t* row_ptr, const uint32_t* col_id
   if (c.err) return HO_ERR_BAD_CSR;
   hoStats out{};
   HOCHK(run_rounds_host(d, g, stream, false, out.kernel_ms, out.kernel_launches));
+  launch_outputs(d, stream);
   HOCHK(read_ctl(d, &c, stream));
   if (c.err) return HO_ERR_BAD_CSR;
   if (!c.done) return HO_ERR_INTERNAL;

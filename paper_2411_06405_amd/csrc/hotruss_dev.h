@@ -13,6 +13,7 @@ constexpr uint32_t SLOT_GONE = 0x80000000u;  // in the low word of ce: the slot'
 constexpr int WAVE = 64;
 constexpr uint32_t CHUNK = 64;           // slots (or bitset words) per work item
 constexpr uint32_t MIN_PART = 1024;      // partial-minimum slots of the level-jump reduction
+constexpr uint32_t DEG_BUCKETS = 256;    // degree classes of the renumbering
 constexpr uint32_t NSTAT = 8;            // work counters kept in stats mode
 constexpr uint32_t STAT_GRID = 8192;     // most workgroups a counted kernel may use
 
@@ -44,21 +45,31 @@ __device__ inline uint32_t meta_extra(uint32_t m) { return (m >> 29) & 1u; }
 __device__ inline uint32_t meta_len(uint32_t m) { return (m >> 22) & 127u; }
 __device__ inline uint32_t meta_vstart(uint32_t m) { return m & ((1u << 22) - 1); }
 
-// List lengths of one level in a round of one parity (read as two 8-byte words).
-struct alignas(16) Cnt {
+// List lengths of one level in a round of one parity.  Items and events have a
+// cache line each, and so have the other counters that many wavefronts add to:
+// device-scope atomics on one line serialise at about 11 ns each (with the
+// peel-set and item counters on one line, the first marking of Chung-Lu 100k
+// h = 1 took 690 us instead of 275).
+struct alignas(128) Cnt {
   uint32_t nit;   // work items (level h+1: support items)
   uint32_t iovf;  // work item list overflowed
-  uint32_t nev;   // ball-change events
+  alignas(128) uint32_t nev;  // ball-change events
   uint32_t ovf;   // event list overflowed
+};
+
+struct alignas(128) LineCounter {
+  uint32_t v;
 };
 
 // Device control block: the whole round state lives on the device so that
 // the round driver never needs the host between rounds.
 struct Ctl {
   uint32_t err;
+  uint32_t nact;     // rows in use: vertices from nact on are isolated (renumbered graphs)
+  uint32_t words;    // words of a bitset row that can hold a vertex below nact (even)
+  uint32_t nlong;    // renumbered graphs: rows of 64 slots or more (they come first)
   uint32_t k;        // current level: edges with sup <= k-2 are peeled
   uint32_t r;        // index of the current peel round
-  uint32_t nR;       // |R_r|, edges peeled in the current round
   uint32_t live;     // edges still in S
   uint32_t levels;   // levels visited
   uint32_t done;     // decomposition finished (read by the host with halt)
@@ -68,7 +79,8 @@ struct Ctl {
   uint64_t events;   // top-level ball-change events (statistics)
   uint64_t overflows;
   Cnt cnt[HMAX + 2][2];  // per level (h+1: support items) and round parity
-  uint32_t nPush[2];          // edges whose support crossed k-2 in a round of this parity
+  LineCounter nRc;       // |R_r|, edges peeled in the current round
+  LineCounter nPushc[2];          // edges whose support crossed k-2 in a round of this parity
   uint32_t compactions;  // adjacency compactions done (statistics)
   uint32_t recovering;   // the host is re-running an overflowed step in windows
   // stats mode: method-level work count (support evaluations and bytes of the
@@ -76,6 +88,7 @@ struct Ctl {
   uint32_t acct_nch;     // vertices whose h-ball changed this round (listed)
   uint32_t acct_nv;      // ball builds of this round (listed)
   uint32_t acct_incomplete;  // an event list overflowed: the count is a lower bound
+  uint32_t bucket[DEG_BUCKETS];  // vertices per degree bucket, then where each starts
   uint64_t acct_evals;
   uint64_t acct_bytes;
   uint64_t levents[HMAX + 1];  // ball-change events per level, all rounds
@@ -85,8 +98,19 @@ struct Ctl {
 
 // Everything a kernel needs, passed by value.
 struct Dev {
+  const uint32_t* orp;  // the caller's row_ptr [n+1]
+  const uint32_t* oci;  // the caller's col_idx [2m]
+  // The adjacency that everything after the validation works on: the
+  // caller's, or (perm set) the same graph with its vertices renumbered by
+  // descending degree.
   const uint32_t* rp;   // row_ptr [n+1]
-  const uint32_t* ci;   // col_idx [2m]
+  const uint32_t* ci;   // col_idx [2m] (as built; see cix)
+  uint32_t* perm;       // renumbering: caller's vertex -> vertex [n], or null
+  uint32_t* inv;        // ... and back [n]
+  // Renumbered graphs have their own edge numbers too (see place_slot): own
+  // number -> caller's [m], and back.  The outputs are written by the caller's.
+  uint32_t* oe;
+  uint32_t* ne;
   uint32_t n, m, h, W;  // W: 64-bit words per bitset row (padded)
   uint32_t nnz;
   uint32_t evcap;       // capacity of each level>=2 event list
@@ -94,7 +118,7 @@ struct Dev {
   uint32_t nminpart;    // blocks of the level-jump minimum kernel
   uint32_t serial;      // testing: bit 2 forces the windowed re-run of every level step,
                         // bit 3 of every support step, bit 4 compacts rows at every chance
-  uint32_t* eid;        // slot -> edge id           [2m]
+  uint32_t* eid;        // caller's slot -> edge id   [2m]
   uint32_t* eu;         // edge id -> lower endpoint  [m]
   uint32_t* ev;         // edge id -> upper endpoint  [m]
   uint32_t* s1;         // edge id -> slot in row eu  [m]
@@ -114,8 +138,10 @@ struct Dev {
   uint32_t* scan_tmp;   // block sums for the scan
   uint32_t* minpart;    // per-block minima of the level-jump reduction
   uint32_t* sup;        // current h-support of every edge [m]
-  uint32_t* t;          // output trussness (0 while live) [m]
-  uint32_t* rho;        // output peel round [m]
+  uint32_t* t;          // trussness [m]
+  uint32_t* rho;        // peel round [m]
+  uint32_t* out_t;      // the caller's outputs (renumbered graphs: written at the end)
+  uint32_t* out_rho;    // (may be null)
   uint32_t* R[2];       // peel lists by round parity [m]
   uint64_t* L[HMAX + 1];   // L[j]: closed j-hop balls, n rows of W words
   uint64_t* Dm[HMAX + 1];  // Dm[j]: pairs that left the j-ball this round
@@ -139,6 +165,12 @@ struct Dev {
 // Compact again once a tenth of the live edges have been peeled since the
 // last compaction (a compaction reads and writes the active slots once).
 __host__ __device__ inline uint32_t compact_next(uint32_t live) { return live - live / 10; }
+
+// Workgroups are dealt to the eight XCDs in turn; this numbering gives each XCD
+// consecutive numbers, so that neighbouring work items share an L2.
+__device__ __forceinline__ uint32_t xcd_first(uint32_t b, uint32_t grid) {
+  return grid % 8 == 0 ? (b & 7) * (grid / 8) + (b >> 3) : b;
+}
 
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & (WAVE - 1); }
 

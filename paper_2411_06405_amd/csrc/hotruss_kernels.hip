@@ -37,10 +37,13 @@ __global__ void k_fill32(uint32_t* __restrict__ p, size_t cnt, uint32_t v) {
     p[i] = v;
 }
 
-__global__ void k_init_ctl(Ctl* ctl, uint32_t m) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    uint32_t* w = reinterpret_cast<uint32_t*>(ctl);
-    for (uint32_t i = 0; i < sizeof(Ctl) / 4; ++i) w[i] = 0;
+__global__ void k_init_ctl(Ctl* ctl, uint32_t n, uint32_t words, uint32_t m) {
+  uint32_t* w = reinterpret_cast<uint32_t*>(ctl);
+  for (uint32_t i = threadIdx.x; i < sizeof(Ctl) / 4; i += blockDim.x) w[i] = 0;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    ctl->nact = n;
+    ctl->words = words;
     ctl->k = 2;
     ctl->jump = 1;  // nothing pushed yet: the first round jumps to min sup + 2
     ctl->live = m;
@@ -55,9 +58,9 @@ __global__ void k_check_rowptr(Dev d) {
   for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x <= d.n;
        x += gridDim.x * blockDim.x) {
     uint32_t bad = 0;
-    if (x == 0 && d.rp[0] != 0) bad |= ERR_ROWPTR;
-    if (x == d.n && d.rp[d.n] != d.nnz) bad |= ERR_COUNT;
-    if (x < d.n && d.rp[x] > d.rp[x + 1]) bad |= ERR_ROWPTR;
+    if (x == 0 && d.orp[0] != 0) bad |= ERR_ROWPTR;
+    if (x == d.n && d.orp[d.n] != d.nnz) bad |= ERR_COUNT;
+    if (x < d.n && d.orp[x] > d.orp[x + 1]) bad |= ERR_ROWPTR;
     if (bad) atomicOr(&d.ctl->err, bad);
   }
 }
@@ -69,13 +72,13 @@ __global__ void k_row_upper(Dev d) {
   const uint32_t lane = lane_id();
   const uint32_t wpb = blockDim.x / WAVE;
   for (uint32_t x = blockIdx.x * wpb + threadIdx.x / WAVE; x < d.n; x += gridDim.x * wpb) {
-    const uint32_t beg = d.rp[x], end = d.rp[x + 1];
+    const uint32_t beg = d.orp[x], end = d.orp[x + 1];
     uint32_t cnt = 0, bad = 0;
     for (uint32_t j = beg + lane; j < end; j += WAVE) {
-      const uint32_t y = d.ci[j];
+      const uint32_t y = d.oci[j];
       if (y >= d.n) bad |= ERR_COL;
       if (y == x) bad |= ERR_LOOP;
-      if (j > beg && d.ci[j - 1] >= y) bad |= ERR_ORDER;
+      if (j > beg && d.oci[j - 1] >= y) bad |= ERR_ORDER;
       cnt += (y > x && y < d.n);
     }
     cnt = wave_sum(cnt);
@@ -116,12 +119,13 @@ __global__ void __launch_bounds__(256) k_scan1(const uint32_t* __restrict__ in,
 }
 
 __global__ void __launch_bounds__(64) k_scan2(uint32_t* bsum, uint32_t nb) {
-  if (threadIdx.x != 0) return;
   uint32_t run = 0;
-  for (uint32_t i = 0; i < nb; ++i) {
-    uint32_t t = bsum[i];
-    bsum[i] = run;
-    run += t;
+  for (uint32_t i0 = 0; i0 < nb; i0 += WAVE) {
+    const uint32_t i = i0 + threadIdx.x, v = i < nb ? bsum[i] : 0u;
+    uint32_t tot;
+    const uint32_t ex = wave_excl_scan(v, &tot);
+    if (i < nb) bsum[i] = run + ex;
+    run += tot;
   }
 }
 
@@ -132,7 +136,8 @@ __global__ void k_scan3(uint32_t* __restrict__ out, const uint32_t* __restrict__
 }
 
 // Canonical edge ids (upper-triangle CSR order), endpoints and slots; every
-// lower slot (x,y), y < x, finds its partner (y,x) by binary search.
+// lower slot (x,y), y < x, finds its partner (y,x) by binary search.  A graph
+// that is renumbered gets its endpoints and slots from place_slot.
 __global__ void k_edge_ids(Dev d) {
   if (d.ctl->err) return;
   const uint32_t lane = lane_id();
@@ -142,28 +147,209 @@ __global__ void k_edge_ids(Dev d) {
     if (tot != d.m) atomicOr(&d.ctl->err, ERR_COUNT);
   }
   for (uint32_t x = blockIdx.x * wpb + threadIdx.x / WAVE; x < d.n; x += gridDim.x * wpb) {
-    const uint32_t beg = d.rp[x], end = d.rp[x + 1];
+    const uint32_t beg = d.orp[x], end = d.orp[x + 1];
     const uint32_t fu = end - d.up_cnt[x];
     for (uint32_t j = beg + lane; j < end; j += WAVE) {
-      const uint32_t y = d.ci[j];
-      d.srem[j] = ALIVE;
+      const uint32_t y = d.oci[j];
+      if (!d.perm) d.srem[j] = ALIVE;
       if (y > x) {
         const uint32_t e = d.up_off[x] + (j - fu);
         if (e >= d.m) { atomicOr(&d.ctl->err, ERR_COUNT); continue; }
-        d.eid[j] = e; d.eu[e] = x; d.ev[e] = y; d.s1[e] = j;
+        d.eid[j] = e;
+        if (!d.perm) { d.eu[e] = x; d.ev[e] = y; d.s1[e] = j; }
       } else {
-        uint32_t lo = d.rp[y + 1] - d.up_cnt[y], hi = d.rp[y + 1];
+        uint32_t lo = d.orp[y + 1] - d.up_cnt[y], hi = d.orp[y + 1];
         const uint32_t first = lo;
         while (lo < hi) {
           const uint32_t mid = (lo + hi) >> 1;
-          if (d.ci[mid] < x) lo = mid + 1; else hi = mid;
+          if (d.oci[mid] < x) lo = mid + 1; else hi = mid;
         }
-        if (lo == d.rp[y + 1] || d.ci[lo] != x) { atomicOr(&d.ctl->err, ERR_ASYM); continue; }
+        if (lo == d.orp[y + 1] || d.oci[lo] != x) { atomicOr(&d.ctl->err, ERR_ASYM); continue; }
         const uint32_t e = d.up_off[y] + (lo - first);
         if (e >= d.m) { atomicOr(&d.ctl->err, ERR_COUNT); continue; }
-        d.eid[j] = e; d.s2[e] = j;
+        d.eid[j] = e;
+        if (!d.perm) d.s2[e] = j;
       }
     }
+  }
+}
+
+// ---------------------------------------------- renumbering by degree
+// A work item reads, for 64 neighbours b of one vertex, the word of some ball
+// row that holds b: 8 of the row's n/8 bytes each, so what bounds it is how
+// many cache lines the 64 lanes touch.  In most graphs a few vertices hold
+// most of the edges; numbered first, and with each row's slots in ascending
+// order, the 64 words of an item fall into a few lines at the row's start,
+// and those lines stay in the caches from item to item.  Isolated vertices
+// come last and get no rows (a quarter of an R-MAT graph's).  The order is by
+// degree class, eight classes per octave; inside a class any order does.
+// Results do not depend on the numbering: edge ids, and with them every
+// output, come from the caller's CSR.
+__device__ __forceinline__ uint32_t degree_bucket(uint32_t deg) {
+  if (deg == 0) return DEG_BUCKETS - 1;
+  const uint32_t e = 31u - (uint32_t)__clz(deg);
+  return DEG_BUCKETS - 2 - min(DEG_BUCKETS - 2, e * 8 + (uint32_t)((((uint64_t)deg << 3) >> e) & 7u));
+}
+
+constexpr uint32_t DEG_TILE = 1024;  // vertices per workgroup of the two passes
+
+__global__ void __launch_bounds__(256) k_degree_count(Dev d) {
+  __shared__ uint32_t h[DEG_BUCKETS];
+  if (d.ctl->err) return;
+  h[threadIdx.x] = 0;
+  __syncthreads();
+  for (uint32_t i = 0; i < DEG_TILE; i += 256) {
+    const uint32_t x = blockIdx.x * DEG_TILE + i + threadIdx.x;
+    if (x < d.n) atomicAdd(&h[degree_bucket(d.orp[x + 1] - d.orp[x])], 1u);
+  }
+  __syncthreads();
+  if (h[threadIdx.x]) atomicAdd(&d.ctl->bucket[threadIdx.x], h[threadIdx.x]);
+}
+
+// Where each class starts; rows and words in use.
+__global__ void __launch_bounds__(256) k_degree_starts(Dev d) {
+  __shared__ uint32_t ws[4];
+  if (d.ctl->err) return;
+  const uint32_t v = d.ctl->bucket[threadIdx.x], wave = threadIdx.x / WAVE;
+  const uint32_t incl = wave_incl_scan(v);
+  if (lane_id() == WAVE - 1) ws[wave] = incl;
+  __syncthreads();
+  uint32_t start = incl - v;
+  for (uint32_t w = 0; w < wave; ++w) start += ws[w];
+  d.ctl->bucket[threadIdx.x] = start;
+  if (threadIdx.x == degree_bucket(63)) d.ctl->nlong = start;
+  if (threadIdx.x == DEG_BUCKETS - 1) {
+    d.ctl->nact = start;
+    d.ctl->words = max(2u, (start + 127) / 128 * 2);
+    const_cast<uint32_t*>(d.rp)[d.n] = d.nnz;
+  }
+}
+
+// New ids, and the degrees in their order (into up_cnt, free by now).
+__global__ void __launch_bounds__(256) k_degree_place(Dev d) {
+  __shared__ uint32_t h[DEG_BUCKETS], base[DEG_BUCKETS];
+  if (d.ctl->err) return;
+  h[threadIdx.x] = 0;
+  __syncthreads();
+  uint32_t b[DEG_TILE / 256], r[DEG_TILE / 256], deg[DEG_TILE / 256];
+#pragma unroll
+  for (uint32_t i = 0; i < DEG_TILE / 256; ++i) {
+    const uint32_t x = blockIdx.x * DEG_TILE + i * 256 + threadIdx.x;
+    deg[i] = x < d.n ? d.orp[x + 1] - d.orp[x] : 0;
+    b[i] = degree_bucket(deg[i]);
+    r[i] = x < d.n ? atomicAdd(&h[b[i]], 1u) : 0;
+  }
+  __syncthreads();
+  if (h[threadIdx.x]) base[threadIdx.x] = atomicAdd(&d.ctl->bucket[threadIdx.x], h[threadIdx.x]);
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < DEG_TILE / 256; ++i) {
+    const uint32_t x = blockIdx.x * DEG_TILE + i * 256 + threadIdx.x;
+    if (x >= d.n) continue;
+    const uint32_t y = base[b[i]] + r[i];
+    d.perm[x] = y;
+    d.inv[y] = x;
+    d.up_cnt[y] = deg[i];
+    if (d.len) d.len[y] = deg[i];
+  }
+}
+
+// Lower slots (neighbour below the row vertex) of every row in the new order.
+__global__ void __launch_bounds__(256) k_rows_lower(Dev d) {
+  if (d.ctl->err) return;
+  const uint32_t lane = lane_id(), wpb = blockDim.x / WAVE, nact = d.ctl->nact;
+  for (uint32_t x = blockIdx.x * wpb + threadIdx.x / WAVE; x < nact; x += gridDim.x * wpb) {
+    const uint32_t o = d.inv[x], beg = d.orp[o], end = d.orp[o + 1];
+    uint32_t c = 0;
+    for (uint32_t q = beg + lane; q < end; q += WAVE) c += d.perm[d.oci[q]] < x;
+    c = wave_sum(c);
+    if (lane == 0) d.up_cnt[x] = c;
+  }
+}
+
+// Slot `at` of row x holds neighbour y by the caller's edge e.  Edges are
+// numbered along the lower slots of the rows: what the support update hits in
+// a row is mostly its hub neighbours, which are below the row vertex, and the
+// atomics of neighbouring lanes on neighbouring edges are one request
+// (device-scope atomics all go to memory: 48,000 requests a round on R-MAT 16
+// h = 2 by the caller's numbers, 290,000 numbered along the upper slots).
+__device__ __forceinline__ void place_slot(const Dev& d, uint32_t x, uint32_t at, uint32_t y,
+                                           uint32_t e) {
+  const uint32_t q = d.rp[x] + at;
+  d.cix[q] = y;
+  if (y < x) {
+    const uint32_t own = d.up_off[x] + at;
+    d.ne[e] = own;
+    d.oe[own] = e;
+    d.eu[own] = y;
+    d.ev[own] = x;
+    if (d.ce) d.s2[own] = q;
+  }
+  if (d.ce) {
+    d.ce[q] = slot_word(e, y, false);  // the caller's number, until k_rows_edges
+    d.srem[q] = ALIVE;
+  }
+}
+
+// Rows of fewer than 64 slots, one wave each: a lane's place is the number of
+// lanes with a smaller neighbour.
+__global__ void __launch_bounds__(256) k_rows_short(Dev d) {
+  if (d.ctl->err) return;
+  const uint32_t lane = lane_id(), wpb = blockDim.x / WAVE, nact = d.ctl->nact;
+  for (uint32_t x = d.ctl->nlong + blockIdx.x * wpb + threadIdx.x / WAVE; x < nact;
+       x += gridDim.x * wpb) {
+    const uint32_t o = d.inv[x], beg = d.orp[o], deg = d.orp[o + 1] - beg;
+    const uint32_t y = lane < deg ? d.perm[d.oci[beg + lane]] : 0xffffffffu;
+    const uint32_t e = lane < deg ? d.eid[beg + lane] : 0;
+    uint32_t at = 0;
+    for (uint32_t i = 0; i < deg; ++i)
+      at += (uint32_t)__builtin_amdgcn_readlane((int)y, (int)i) < y;
+    if (lane < deg) place_slot(d, x, at, y, e);
+  }
+}
+
+// Longer rows, one workgroup each: counted and placed by ranges of the
+// neighbour id (1,024 of them: a ball row's word or a few), any order inside
+// a range, the slots below x apart from those above.
+__global__ void __launch_bounds__(1024) k_rows_long(Dev d) {
+  __shared__ uint32_t h[1024], ws[16], mid;
+  if (d.ctl->err) return;
+  uint32_t shift = 0;
+  while ((d.n - 1) >> shift >= 1024) ++shift;
+  const uint32_t nlong = d.ctl->nlong, wave = threadIdx.x / WAVE;
+  for (uint32_t x = blockIdx.x; x < nlong; x += gridDim.x) {
+    const uint32_t o = d.inv[x], beg = d.orp[o], end = d.orp[o + 1];
+    const uint32_t low = d.up_cnt[x];
+    h[threadIdx.x] = 0;
+    __syncthreads();
+    for (uint32_t q = beg + threadIdx.x; q < end; q += 1024)
+      atomicAdd(&h[d.perm[d.oci[q]] >> shift], 1u);
+    __syncthreads();
+    const uint32_t v = h[threadIdx.x], incl = wave_incl_scan(v);
+    if (lane_id() == WAVE - 1) ws[wave] = incl;
+    __syncthreads();
+    uint32_t start = incl - v;
+    for (uint32_t w = 0; w < wave; ++w) start += ws[w];
+    h[threadIdx.x] = start;
+    if (threadIdx.x == 0) mid = low;  // slots above x of x's own range start here
+    __syncthreads();
+    for (uint32_t q = beg + threadIdx.x; q < end; q += 1024) {
+      const uint32_t y = d.perm[d.oci[q]], r = y >> shift;
+      const uint32_t at = atomicAdd(r == x >> shift && y > x ? &mid : &h[r], 1u);
+      place_slot(d, x, at, y, d.eid[q]);
+    }
+    __syncthreads();
+  }
+}
+
+// Own edge numbers in place of the caller's; the lower endpoints' slots.
+__global__ void __launch_bounds__(256) k_rows_edges(Dev d) {
+  if (d.ctl->err) return;
+  for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < d.nnz; q += gridDim.x * blockDim.x) {
+    const uint64_t w = d.ce[q];
+    const uint32_t y = (uint32_t)w, own = d.ne[(uint32_t)(w >> 32)];
+    d.ce[q] = slot_word(own, y, false);
+    if (d.ev[own] == y) d.s1[own] = q;
   }
 }
 
@@ -173,9 +359,10 @@ __global__ void k_edge_ids(Dev d) {
 __global__ void __launch_bounds__(256) k_build_L1(Dev d) {
   extern __shared__ uint64_t srow[];
   if (d.ctl->err) return;
+  const uint32_t nact = d.ctl->nact, words = d.ctl->words;
   uint64_t* L1 = d.L[1];
-  for (uint32_t x = blockIdx.x; x < d.n; x += gridDim.x) {
-    for (uint32_t i = threadIdx.x; i < d.W; i += blockDim.x) srow[i] = 0;
+  for (uint32_t x = blockIdx.x; x < nact; x += gridDim.x) {
+    for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) srow[i] = 0;
     __syncthreads();
     if (threadIdx.x == 0) atomicOr(&srow[x >> 6], 1ull << (x & 63));
     for (uint32_t j = d.rp[x] + threadIdx.x; j < d.rp[x + 1]; j += blockDim.x) {
@@ -184,7 +371,7 @@ __global__ void __launch_bounds__(256) k_build_L1(Dev d) {
     }
     __syncthreads();
     uint64_t* out = row(L1, d.W, x);
-    for (uint32_t i = threadIdx.x; i < d.W; i += blockDim.x) out[i] = srow[i];
+    for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) out[i] = srow[i];
     __syncthreads();
   }
 }
@@ -199,12 +386,13 @@ __global__ void __launch_bounds__(256) k_build_L2(Dev d, uint32_t dthr) {
   extern __shared__ uint64_t srow[];
   __shared__ uint32_t s_fsum;
   if (d.ctl->err) return;
+  const uint32_t nact = d.ctl->nact, words = d.ctl->words;
   const uint32_t lane = lane_id(), wv = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
   const uint64_t* L1 = d.L[1];
-  for (uint32_t x = blockIdx.x; x < d.n; x += gridDim.x) {
+  for (uint32_t x = blockIdx.x; x < nact; x += gridDim.x) {
     const uint32_t beg = d.rp[x], end = d.rp[x + 1];
     if (threadIdx.x == 0) s_fsum = 0;
-    for (uint32_t i = threadIdx.x; i < d.W; i += blockDim.x) srow[i] = 0;
+    for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) srow[i] = 0;
     __syncthreads();
     uint32_t fs = 0;
     for (uint32_t q = beg + threadIdx.x; q < end; q += blockDim.x) {
@@ -214,9 +402,9 @@ __global__ void __launch_bounds__(256) k_build_L2(Dev d, uint32_t dthr) {
     fs = wave_sum(fs);
     if (lane == 0 && fs) atomicAdd(&s_fsum, fs);
     __syncthreads();
-    const bool dense = (uint64_t)s_fsum * 16 > (uint64_t)dthr * (end - beg + 1) * d.W;
+    const bool dense = (uint64_t)s_fsum * 16 > (uint64_t)dthr * (end - beg + 1) * words;
     if (dense) {
-      for (uint32_t i = threadIdx.x; i < d.W; i += blockDim.x) {
+      for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) {
         uint64_t acc = L1[(size_t)x * d.W + i];
         for (uint32_t q = beg; q < end; ++q) acc |= L1[(size_t)d.ci[q] * d.W + i];
         srow[i] = acc;
@@ -234,7 +422,7 @@ __global__ void __launch_bounds__(256) k_build_L2(Dev d, uint32_t dthr) {
     }
     __syncthreads();
     uint64_t* out = row(d.L[2], d.W, x);
-    for (uint32_t i = threadIdx.x; i < d.W; i += blockDim.x) out[i] = srow[i];
+    for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) out[i] = srow[i];
     __syncthreads();
   }
 }
@@ -243,11 +431,12 @@ __global__ void __launch_bounds__(256) k_build_L2(Dev d, uint32_t dthr) {
 // (B(x,j) = union over z in N[x] of B(z,j-1)); each thread owns a set of words.
 __global__ void __launch_bounds__(256) k_build_Lj(Dev d, uint32_t j) {
   if (d.ctl->err) return;
+  const uint32_t nact = d.ctl->nact, words = d.ctl->words;
   const uint64_t* P = d.L[j - 1];
   uint64_t* O = d.L[j];
-  for (uint32_t x = blockIdx.x; x < d.n; x += gridDim.x) {
+  for (uint32_t x = blockIdx.x; x < nact; x += gridDim.x) {
     const uint32_t beg = d.rp[x], end = d.rp[x + 1];
-    for (uint32_t i = threadIdx.x; i < d.W; i += blockDim.x) {
+    for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) {
       uint64_t acc = P[(size_t)x * d.W + i];
       for (uint32_t q = beg; q < end; ++q) acc |= P[(size_t)d.ci[q] * d.W + i];
       O[(size_t)x * d.W + i] = acc;
@@ -255,16 +444,24 @@ __global__ void __launch_bounds__(256) k_build_Lj(Dev d, uint32_t j) {
   }
 }
 
+// Change marks of every row in use, before the first round.
+__global__ void k_clear_rows(Dev d, uint64_t* __restrict__ p) {
+  const size_t cnt = (size_t)d.ctl->nact * d.W;
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < cnt;
+       i += (size_t)gridDim.x * blockDim.x)
+    p[i] = 0;
+}
+
 // Initial h-support of every edge: |L[h](u) & L[h](v)| - 2 (Def. 3).
 // G lanes cooperate on one edge; each lane loads V 64-bit words at a time
 // (V = 1: 64-bit loads, V = 2: 128-bit loads; rows are 64-byte aligned).
 template <int G, int V>
-__global__ void __launch_bounds__(256) k_support_init(Dev d, uint32_t* __restrict__ out) {
+__global__ void __launch_bounds__(256) k_support_init(Dev d, uint32_t* __restrict__ out, bool by_caller) {
   if (d.ctl->err) return;
   const uint64_t* Lh = d.L[d.h];
   const uint32_t sub = threadIdx.x & (G - 1);
   const uint32_t gpb = blockDim.x / G;
-  const uint32_t nv = d.W / V;  // W is a multiple of 8
+  const uint32_t nv = d.ctl->words / V;  // an even number of words
   for (uint32_t e = blockIdx.x * gpb + threadIdx.x / G; e < d.m; e += gridDim.x * gpb) {
     const uint64_t* a = Lh + (size_t)d.eu[e] * d.W;
     const uint64_t* b = Lh + (size_t)d.ev[e] * d.W;
@@ -280,7 +477,7 @@ __global__ void __launch_bounds__(256) k_support_init(Dev d, uint32_t* __restric
       for (uint32_t i = sub; i < nv; i += G) c += __popcll(a[i] & b[i]);
     }
     for (int o = G / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, WAVE);
-    if (sub == 0) out[e] = c - 2;
+    if (sub == 0) out[by_caller && d.oe ? d.oe[e] : e] = c - 2;
   }
 }
 
@@ -389,7 +586,7 @@ __device__ void emit_support_items(const Dev& d, uint32_t p, bool active, uint32
 
 // Items over z's old (j-1)-ball words for candidates (x, w), j >= 3.
 __device__ void emit_word_items(const Dev& d, uint32_t p, uint32_t j, bool active, uint32_t x, uint32_t z) {
-  emit_group<ITEM_WORDS>(d, p, j, 0, 0, x, z, 0, active ? d.W : 0u);
+  emit_group<ITEM_WORDS>(d, p, j, 0, 0, x, z, 0, active ? d.ctl->words : 0u);
 }
 
 // ---- level-jump minimum ----------------------------------------------------
@@ -425,6 +622,117 @@ __global__ void __launch_bounds__(256) k_first_min(const Dev* __restrict__ devs)
   jump_partials(d);
 }
 
+// One direction of a wave's pairs that leave a ball: bit `col` of row `row`, for
+// the lanes with `drop`.  Neighbouring lanes hold neighbouring columns of one
+// row (a work item's pairs share a vertex), so runs of lanes on the same word
+// are merged into one atomic: atomics on one cache line serialise at about
+// 11 ns each wherever they come from, and with the hubs numbered first a
+// row's pairs share a few lines (R-MAT 16 h = 2, renumbered: k_level 39 us a
+// round without the merge, 17 us with it and the eight-lane dealing below).
+struct Run {
+  uint64_t upto, bit;  // bits of the run up to this lane; this lane's own
+  size_t o;            // the word
+  uint32_t last;       // the run's last lane, which does its atomics
+  bool twice;          // an earlier lane of the run has the same pair
+};
+
+__device__ __forceinline__ Run word_runs(uint32_t W, uint32_t row_, uint32_t col, bool drop) {
+  const uint32_t lane = lane_id(), word = col >> 6;
+  Run R;
+  R.bit = drop ? 1ull << (col & 63) : 0ull;
+  R.o = (size_t)row_ * W + word;
+  // a lane starts a run unless it is on its left neighbour's word
+  const uint32_t pr = dpp<0x138, 0xf>(~row_, row_), pw = dpp<0x138, 0xf>(~word, word);  // wave_shr:1
+  const bool head = lane == 0 || pr != row_ || pw != word;
+  // inclusive OR inside the runs
+  uint32_t lo = (uint32_t)R.bit, hi = (uint32_t)(R.bit >> 32), fl = head;
+  auto step = [&](uint32_t plo, uint32_t phi, uint32_t pf) {
+    if (!fl) {
+      lo |= plo;
+      hi |= phi;
+      fl = pf;
+    }
+  };
+  step(dpp<0x111, 0xf>(0, lo), dpp<0x111, 0xf>(0, hi), dpp<0x111, 0xf>(0, fl));
+  step(dpp<0x112, 0xf>(0, lo), dpp<0x112, 0xf>(0, hi), dpp<0x112, 0xf>(0, fl));
+  step(dpp<0x114, 0xf>(0, lo), dpp<0x114, 0xf>(0, hi), dpp<0x114, 0xf>(0, fl));
+  step(dpp<0x118, 0xf>(0, lo), dpp<0x118, 0xf>(0, hi), dpp<0x118, 0xf>(0, fl));
+  step(dpp<0x142, 0xa>(0, lo), dpp<0x142, 0xa>(0, hi), dpp<0x142, 0xa>(0, fl));
+  step(dpp<0x143, 0xc>(0, lo), dpp<0x143, 0xc>(0, hi), dpp<0x143, 0xc>(0, fl));
+  R.upto = ((uint64_t)hi << 32) | lo;
+  const uint64_t before =
+      ((uint64_t)dpp<0x138, 0xf>(0, hi) << 32) | dpp<0x138, 0xf>(0, lo);
+  R.twice = !head && (before & R.bit);
+  const uint64_t heads = __ballot(head);
+  const uint64_t later = lane == 63 ? 0ull : heads >> (lane + 1);
+  R.last = later ? lane + (uint32_t)__ffsll((unsigned long long)later) - 1 : 63u;
+  return R;
+}
+
+// Pairs {x, w} leave a ball, for the lanes with `drop`: both bits are cleared in
+// L and set in D.  *xw, *wx: this lane cleared w in x's row, x in w's (one lane
+// only, should two hold the same pair).  All lanes of the wave call it; the
+// atomics of both directions are in flight together.  merge: by runs, for
+// renumbered graphs.
+__device__ __forceinline__ void clear_pairs(uint64_t* __restrict__ L, uint64_t* __restrict__ D,
+                                            uint32_t W, uint32_t x, uint32_t w, bool drop,
+                                            bool merge, bool* xw, bool* wx) {
+  auto clear = [&](size_t o, uint64_t bits) -> uint64_t {
+    return atomicAnd(reinterpret_cast<unsigned long long*>(L + o), ~(unsigned long long)bits) & bits;
+  };
+  auto mark = [&](size_t o, uint64_t bits) {
+    if (bits) atomicOr(reinterpret_cast<unsigned long long*>(D + o), (unsigned long long)bits);
+  };
+  if (!merge) {
+    uint64_t oa = 0, ob = 0;
+    if (drop) {
+      const size_t pa = (size_t)x * W + (w >> 6), pb = (size_t)w * W + (x >> 6);
+      oa = clear(pa, 1ull << (w & 63));
+      ob = clear(pb, 1ull << (x & 63));
+      mark(pa, oa);
+      mark(pb, ob);
+    }
+    *xw = oa != 0;
+    *wx = ob != 0;
+    return;
+  }
+  const uint32_t lane = lane_id();
+  const Run A = word_runs(W, x, w, drop), B = word_runs(W, w, x, drop);
+  const bool da = A.last == lane && A.upto, db = B.last == lane && B.upto;
+  uint64_t oa = 0, ob = 0;
+  if (da) oa = clear(A.o, A.upto);
+  if (db) ob = clear(B.o, B.upto);
+  if (da) mark(A.o, oa);
+  if (db) mark(B.o, ob);
+  auto at = [&](uint64_t v, uint32_t l) {
+    return ((uint64_t)(uint32_t)__shfl((uint32_t)(v >> 32), l, WAVE) << 32) |
+           (uint32_t)__shfl((uint32_t)v, l, WAVE);
+  };
+  const uint64_t ra = at(oa, A.last), rb = at(ob, B.last);  // all lanes take part
+  *xw = !A.twice && (ra & A.bit);
+  *wx = !B.twice && (rb & B.bit);
+}
+
+// The same for peeled edges {x, w} and level 1, where every edge is listed once
+// and nothing depends on what the atomics return (a marking kernel that waits
+// for them takes 2.6 times as long in the largest rounds).  D: only at h = 1.
+__device__ __forceinline__ void clear_edges(uint64_t* __restrict__ L, uint64_t* __restrict__ D,
+                                            uint32_t W, uint32_t x, uint32_t w, bool valid,
+                                            bool merge) {
+  auto clear = [&](size_t o, uint64_t bits) {
+    atomicAnd(reinterpret_cast<unsigned long long*>(L + o), ~(unsigned long long)bits);
+    if (D) atomicOr(reinterpret_cast<unsigned long long*>(D + o), (unsigned long long)bits);
+  };
+  if (merge) {
+    const Run A = word_runs(W, x, w, valid), B = word_runs(W, w, x, valid);
+    if (A.last == lane_id() && A.upto) clear(A.o, A.upto);
+    if (B.last == lane_id() && B.upto) clear(B.o, B.upto);
+  } else if (valid) {
+    clear((size_t)x * W + (w >> 6), 1ull << (w & 63));
+    clear((size_t)w * W + (x >> 6), 1ull << (x & 63));
+  }
+}
+
 // ---- K2: peel R (level jump: collect it first), level-1 events, items ----
 __device__ void mark_edge(const Dev& d, const RoundCtx& rc, bool valid, uint32_t e, uint32_t i) {
   uint32_t a = 0, b = 0;
@@ -439,15 +747,10 @@ __device__ void mark_edge(const Dev& d, const RoundCtx& rc, bool valid, uint32_t
     b = d.ev[e];
     d.ce[q1] = slot_word(e, b, true);
     d.ce[q2] = slot_word(e, a, true);
-    atomicAnd(&row(d.L[1], d.W, a)[b >> 6], ~(1ull << (b & 63)));
-    atomicAnd(&row(d.L[1], d.W, b)[a >> 6], ~(1ull << (a & 63)));
-    if (d.h == 1) {
-      atomicOr(&row(d.Dm[1], d.W, a)[b >> 6], 1ull << (b & 63));
-      atomicOr(&row(d.Dm[1], d.W, b)[a >> 6], 1ull << (a & 63));
-    }
     d.evl[1][rc.p][2 * i] = ((uint64_t)a << 32) | b;
     d.evl[1][rc.p][2 * i + 1] = ((uint64_t)b << 32) | a;
   }
+  clear_edges(d.L[1], d.h == 1 ? d.Dm[1] : nullptr, d.W, a, b, valid, d.perm != nullptr);
   if (d.h == 1) {
     emit_support_items(d, rc.p, valid, a, b);
     emit_support_items(d, rc.p, valid, b, a);
@@ -514,7 +817,7 @@ __device__ void mark_edge_wave(const Dev& d, const RoundCtx& rc, uint32_t e, uin
   const uint32_t v0 = d.h == 1 ? da : db + 1, v1 = d.h == 1 ? db : da + 1;
   const uint32_t n0 = chunks_of(v0), n1 = chunks_of(v1);
   const uint32_t n2 = d.h == 1 ? 0 : chunks_of(da), n3 = d.h == 1 ? 0 : chunks_of(db);
-  const uint32_t nw = chunks_of(d.W), rows = n0 + n1 + n2 + n3;
+  const uint32_t words = d.ctl->words, nw = chunks_of(words), rows = n0 + n1 + n2 + n3;
   uint32_t base = 0;
   if (lane == 0 || lane + 2 <= d.h)  // lane l reserves the items of list l + 2
     base = atomicAdd(&d.ctl->cnt[lane + 2][rc.p].nit, lane == 0 ? rows : 2 * nw);
@@ -537,8 +840,8 @@ __device__ void mark_edge_wave(const Dev& d, const RoundCtx& rc, uint32_t e, uin
     const uint32_t at = __shfl(base, j - 2, WAVE);
     over = false;
     for (uint32_t t = lane; t < 2 * nw; t += WAVE) {
-      const Item it = t < nw ? make_item<ITEM_WORDS>(0, 0, a, b, 0, d.W, t)
-                             : make_item<ITEM_WORDS>(0, 0, b, a, 0, d.W, t - nw);
+      const Item it = t < nw ? make_item<ITEM_WORDS>(0, 0, a, b, 0, words, t)
+                             : make_item<ITEM_WORDS>(0, 0, b, a, 0, words, t - nw);
       if (at + t < d.itcap) d.itl[j][at + t] = it;
       else over = true;
     }
@@ -592,12 +895,12 @@ k_mark(const Dev* __restrict__ devs) {
       const uint32_t sv = e < d.m ? d.sup[e] : SUP_GONE;
       const bool take = sv != SUP_GONE && sv <= rc.k - 2;
       if (!__ballot(take)) continue;  // nothing to peel in these 64 edges
-      const uint32_t i = wave_reserve(&c->nR, take ? 1u : 0u);
+      const uint32_t i = wave_reserve(&c->nRc.v, take ? 1u : 0u);
       if (take) d.R[rc.p][i] = e;
       mark_edge(d, rc, take, e, i);
     }
   } else {
-    const uint32_t nR = c->nR;
+    const uint32_t nR = c->nRc.v;
     if (nR <= wstride / WAVE) {
       // no more peeled edges than wavefronts: one edge per wavefront, so the
       // 64 lanes share the writing of its work items -- the rows of a hub
@@ -616,7 +919,7 @@ k_mark(const Dev* __restrict__ devs) {
   for (uint32_t j = 2; j <= d.h; ++j) {
     if (!c->cnt[j][q].ovf) continue;
     uint64_t* D = d.Dm[j];
-    const size_t cnt = (size_t)d.n * d.W;
+    const size_t cnt = (size_t)c->nact * d.W;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < cnt;
          i += (size_t)gridDim.x * blockDim.x)
       D[i] = 0;
@@ -642,6 +945,7 @@ k_mark(const Dev* __restrict__ devs) {
 // candidates per step, and a flush per step would dominate their time.
 constexpr uint32_t LV_WIDE_THREADS = 1024, LV_WIDE_CAP = 2048;    // single graph
 constexpr uint32_t LV_NARROW_THREADS = 256, LV_NARROW_CAP = 1024; // batched slots
+constexpr uint32_t LV_FIRST = 32;  // witness probes of a pair before it is looked at again
 constexpr uint32_t LV_DENSE = 256; // of those, most tested on bitset rows per flush
 
 // Block-wide exclusive scan of v[0..n) (n <= LV_CAP) into out; returns the total.
@@ -680,10 +984,12 @@ template <uint32_t LV_THREADS, uint32_t LV_CAP>
 struct LevelLds {
   // a candidate: the pair, the endpoint whose ball is probed, the other one's
   // row, its first probe's number, and whether a witness was found
-  uint32_t x[LV_CAP], w[LV_CAP], b[LV_CAP], beg[LV_CAP], off[LV_CAP], flag[LV_CAP];
+  uint32_t x[LV_CAP], w[LV_CAP], b[LV_CAP], beg[LV_CAP], deg[LV_CAP], off[LV_CAP], flag[LV_CAP];
+  uint16_t rest[LV_CAP];     // candidates with probes left after the first few
   uint32_t dense[LV_DENSE];  // candidates tested by bitset rows (see the flush)
-  uint32_t ndense, busy[2];
-  unsigned long long fill;    // candidates (low half) and their probes (high half)
+  uint32_t ndense, longrow, busy[2];
+  unsigned long long fill;    // candidates (low half) and their first probes (high half)
+  unsigned long long more;    // rest[] (low half) and its probes (high half)
   unsigned long long res[2];  // a drop pass's items (low half) and events (high half)
   uint32_t bres[2];           // ... and where the workgroup's start
   uint32_t stat[5];  // stats mode: items, slots, candidates, probes, drops
@@ -708,10 +1014,10 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
                            uint32_t nwg, LevelLds<LV_THREADS, LV_CAP>& s) {
   static_assert(LV_CAP >= 2 * LV_THREADS && LV_CAP % LV_THREADS == 0, "two emission steps fit");
   constexpr uint32_t LV_WAVES = LV_THREADS / WAVE;
-  uint32_t *cx = s.x, *cw = s.w, *cb = s.b, *cbeg = s.beg, *coff = s.off;
+  uint32_t *cx = s.x, *cw = s.w, *cb = s.b, *cbeg = s.beg, *cdeg = s.deg, *coff = s.off;
   uint32_t *cflag = s.flag, *cdense = s.dense, *s_busy = s.busy;
   Ctl* c = d.ctl;
-  const uint32_t wave = threadIdx.x / WAVE, lane = lane_id();
+  const uint32_t wave = threadIdx.x / WAVE, lane = lane_id(), words = c->words;
   // items are dealt to workgroups first, then to their waves, so a round
   // with few items still spreads its candidates (and their probes) over as
   // many CUs as it has items
@@ -724,39 +1030,30 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
   const Item* items = d.itl[j];
   if (threadIdx.x == 0) {
     s.fill = 0;
+    s.more = 0;
+    s.longrow = 0;
     s.ndense = 0;
     s.res[0] = s.res[1] = 0;
     s_busy[0] = s_busy[1] = 0;
   }
   uint32_t par = 0, pass = 0;
   uint32_t next = wg;  // wave 0's next item
+  const bool merge = d.perm != nullptr;
   uint64_t wd = 0;       // KIND_A_WORDS: this lane's remaining candidates
   uint32_t wbase = 0;    // ... and its word's first vertex
   bool inword = false;   // KIND_A_WORDS item in progress
   uint32_t X = 0, Wv = 0;
   // Append this wave's candidates (X, Wv) to the buffer.  The witness probes
-  // run over the endpoint with fewer active slots; a pair whose lower-degree
-  // endpoint has more of them than a ball row has words is tested on the
-  // bitset rows instead (see the flush).  One LDS atomic per wave reserves
-  // buffer entries (low half) and probe numbers (high half) together, so
-  // both ascend in the same order and the flush needs no scan.
+  // run over the endpoint with fewer active slots.  One LDS atomic per wave
+  // reserves buffer entries (low half) and first-probe numbers (high half)
+  // together, so both ascend in the same order and the flush needs no scan.
   auto append = [&](bool have, uint32_t bx, uint32_t dx, uint32_t bw, uint32_t dw) {
     const uint64_t bal = __ballot(have);
     if (!bal) return;
-    uint32_t deg = have ? min(dx, dw) : 0u, dslot = LV_DENSE;
-    const uint64_t bd = __ballot(deg > d.W);
-    if (bd) {
-      uint32_t at = 0;
-      if (lane == 0) at = atomicAdd(&s.ndense, (uint32_t)__popcll(bd));
-      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) +
-           (uint32_t)__popcll(bd & ((1ull << lane) - 1));
-      if (deg > d.W && at < LV_DENSE) {  // the rest keep their neighbour probes
-        dslot = at;
-        deg = 0;
-      }
-    }
+    const uint32_t deg = have ? min(dx, dw) : 0u;
     uint32_t psum;
-    const uint32_t pex = wave_excl_scan(deg, &psum);
+    const uint32_t pex = wave_excl_scan(min(deg, LV_FIRST), &psum);
+    if (__ballot(deg > LV_FIRST) && lane == 0) s.longrow = 1;
     unsigned long long at = 0;
     if (lane == 0)
       at = atomicAdd(&s.fill, ((unsigned long long)psum << 32) | (uint32_t)__popcll(bal));
@@ -768,8 +1065,8 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
       cw[slot] = Wv;
       cb[slot] = dx <= dw ? Wv : X;
       cbeg[slot] = dx <= dw ? bx : bw;
+      cdeg[slot] = deg;
       coff[slot] = p0;
-      if (dslot < LV_DENSE) cdense[dslot] = slot;
     }
   };
   __syncthreads();
@@ -842,13 +1139,15 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
         it += stride;
         it_taken = true;
         // quick filters: a real pair, still in the j-ball, not within j-1
-        // hops (both balls are symmetric, so both bits are read from the row
-        // of the smaller vertex, together with the two row extents)
+        // hops.  Balls are symmetric: both bits are read from the row of the
+        // vertex that the item's pairs share, where the lanes' ascending
+        // neighbours lie in few cache lines, together with the row extents.
         uint32_t bx = 0, dx = 0, bw = 0, dw = 0;
         have = have && X != Wv;
         if (have) {
-          const size_t o = (size_t)min(X, Wv) * d.W + (max(X, Wv) >> 6);
-          const uint64_t sh = max(X, Wv) & 63;
+          const uint32_t at = kind == KIND_A_SLOTS ? Wv : X;
+          const size_t o = (size_t)(kind == KIND_A_SLOTS ? X : Wv) * d.W + (at >> 6);
+          const uint64_t sh = at & 63;
           const uint64_t wj = *(Lj + o), wp = *(Lp + o);
           bx = d.rp[X];
           dx = d.len[X];
@@ -883,7 +1182,7 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
       if (threadIdx.x == 0) s_busy[par] = 0;
     }
     const uint32_t n = (uint32_t)s.fill, total = (uint32_t)(s.fill >> 32);
-    const uint32_t ndense = min(s.ndense, LV_DENSE);
+    const bool longrow = s.longrow != 0;
     if (n == 0 && !busy) break;
     if (n + LV_THREADS <= LV_CAP && busy) {
       __syncthreads();  // everyone has read the counts before anyone appends
@@ -892,81 +1191,129 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
     // ---- flush: look for a witness of every buffered pair ----
     // The pairs' probes (a live neighbour y of the lower-degree endpoint,
     // checked against the other's (j-1)-ball) are laid out flat over all
-    // threads of the workgroup.  A dense pair's witnesses are exactly the
-    // members of L[1](low) & L[j-1](other) (L[1] holds the live closed
-    // neighbourhood, and low itself is not within j-1 hops of the other
-    // endpoint): one wave ANDs the two rows and stops at the first non-zero
-    // word.
+    // threads of the workgroup: the first LV_FIRST of every pair, then the rest
+    // of the pairs without a witness so far.  Rows have their hubs first, so
+    // most pairs that have a witness show one early, and long rows are
+    // scanned for few others.
     if (counting && threadIdx.x == 0) s.stat[3] += total;
     // four probes per thread in flight: owners found in LDS first, then all
     // slot loads, then all ball-word loads
-    constexpr uint32_t PU = 4;
-    for (uint32_t p0 = threadIdx.x; p0 < total; p0 += PU * LV_THREADS) {
-      uint32_t own[PU], q[PU], y[PU];
-      bool act[PU];
+    auto probe = [&](uint32_t cnt, uint32_t probes, uint32_t skip, auto&& who) {
+      constexpr uint32_t PU = 4;
+      for (uint32_t p0 = threadIdx.x; p0 < probes; p0 += PU * LV_THREADS) {
+        uint32_t own[PU], q[PU], y[PU];
+        bool act[PU];
 #pragma unroll
-      for (uint32_t u = 0; u < PU; ++u) {
-        const uint32_t pidx = p0 + u * LV_THREADS;
-        uint32_t lo = 0, hi = n;
-        while (hi - lo > 1) {
-          const uint32_t mid = (lo + hi) >> 1;
-          if (coff[mid] <= pidx) lo = mid; else hi = mid;
+        for (uint32_t u = 0; u < PU; ++u) {
+          const uint32_t pidx = p0 + u * LV_THREADS;
+          uint32_t lo = 0, hi = cnt;
+          while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (coff[mid] <= pidx) lo = mid; else hi = mid;
+          }
+          own[u] = who(lo);
+          act[u] = pidx < probes && !cflag[own[u]];
+          q[u] = cbeg[own[u]] + skip + (pidx - coff[lo]);
         }
-        own[u] = lo;
-        act[u] = pidx < total && !cflag[lo];
-        q[u] = cbeg[lo] + (pidx - coff[lo]);
-      }
 #pragma unroll
-      for (uint32_t u = 0; u < PU; ++u) y[u] = act[u] ? (uint32_t)*(d.ce + q[u]) : SLOT_GONE;
+        for (uint32_t u = 0; u < PU; ++u)
+          y[u] = act[u] ? (uint32_t)*(d.ce + q[u]) : SLOT_GONE;
 #pragma unroll
-      for (uint32_t u = 0; u < PU; ++u)
-        if (!(y[u] & SLOT_GONE)) {
-          const uint64_t word = *(row(Lp, d.W, cb[own[u]]) + (y[u] >> 6));
-          if ((word >> (y[u] & 63)) & 1ull) cflag[own[u]] = 1;
-        }
-    }
-    for (uint32_t k = wave; k < ndense; k += LV_WAVES) {
-      const uint32_t i = cdense[k];
-      const uint32_t hi = cb[i], lo = (hi == cx[i]) ? cw[i] : cx[i];
-      const uint64_t* ra = row(d.L[1], d.W, lo);
-      const uint64_t* rb = row(Lp, d.W, hi);
-      uint32_t words = 0;
-      bool found = false;
-      for (uint32_t w0 = 0; w0 < d.W && !found; w0 += 4 * WAVE) {
-        uint64_t any = 0;
-#pragma unroll
-        for (uint32_t u = 0; u < 4; ++u) {
-          const uint32_t wi = w0 + u * WAVE + lane;
-          if (wi < d.W) any |= *(ra + wi) & *(rb + wi);
-        }
-        words += min(4 * WAVE, d.W - w0);
-        found = __ballot(any != 0) != 0;
+        for (uint32_t u = 0; u < PU; ++u)
+          if (!(y[u] & SLOT_GONE)) {
+            const uint64_t word = *(row(Lp, d.W, cb[own[u]]) + (y[u] >> 6));
+            if ((word >> (y[u] & 63)) & 1ull) cflag[own[u]] = 1;
+          }
       }
-      if (lane == 0) {
-        if (found) cflag[i] = 1;
-        if (counting) atomicAdd(&s.stat[3], words);  // a word pair counts as one probe
-      }
-    }
+    };
+    probe(n, total, 0, [](uint32_t i) { return i; });
     __syncthreads();
+    // Pairs with probes left.  Where that is many for the words of a ball row,
+    // one wave ANDs two rows instead, to the first non-zero word: the
+    // witnesses are exactly the members of L[1](low) & L[j-1](other) (L[1]
+    // holds the live closed neighbourhood, and low itself is not within j-1
+    // hops of the other endpoint).  A probe gathers one word, the rows come
+    // 64 words a load: the AND pays from a quarter of the words on.
+    if (longrow) {
+      for (uint32_t b0 = 0; b0 < n; b0 += LV_THREADS) {
+        const uint32_t i = b0 + threadIdx.x;
+        uint32_t left = i < n && !cflag[i] && cdeg[i] > LV_FIRST ? cdeg[i] - LV_FIRST : 0u;
+        if (!__ballot(left != 0)) continue;
+        const bool big = left > words / 4;
+        const uint64_t bd = __ballot(big);
+        if (bd) {
+          uint32_t at = 0;
+          if (lane == 0) at = atomicAdd(&s.ndense, (uint32_t)__popcll(bd));
+          at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) +
+               (uint32_t)__popcll(bd & ((1ull << lane) - 1));
+          if (big && at < LV_DENSE) {  // the others keep their neighbour probes
+            cdense[at] = i;
+            left = 0;
+          }
+        }
+        const uint64_t bl = __ballot(left != 0);
+        uint32_t psum;
+        const uint32_t pex = wave_excl_scan(left, &psum);
+        unsigned long long at = 0;
+        if (lane == 0) at = atomicAdd(&s.more, ((unsigned long long)psum << 32) | (uint32_t)__popcll(bl));
+        const uint32_t slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at) +
+                              (uint32_t)__popcll(bl & ((1ull << lane) - 1));
+        const uint32_t p0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) + pex;
+        if (left) {
+          s.rest[slot] = (uint16_t)i;
+          coff[slot] = p0;
+        }
+      }
+      __syncthreads();
+      const uint32_t nrest = (uint32_t)s.more, left_total = (uint32_t)(s.more >> 32);
+      const uint32_t ndense = min(s.ndense, LV_DENSE);
+      if (counting && threadIdx.x == 0) s.stat[3] += left_total;
+      probe(nrest, left_total, LV_FIRST, [&](uint32_t i) { return (uint32_t)s.rest[i]; });
+      for (uint32_t k = wave; k < ndense; k += LV_WAVES) {
+        const uint32_t i = cdense[k];
+        const uint32_t hi = cb[i], lo = (hi == cx[i]) ? cw[i] : cx[i];
+        const uint64_t* ra = row(d.L[1], d.W, lo);
+        const uint64_t* rb = row(Lp, d.W, hi);
+        uint32_t nread = 0;
+        bool found = false;
+        for (uint32_t w0 = 0; w0 < words && !found; w0 += 4 * WAVE) {
+          uint64_t any = 0;
+  #pragma unroll
+          for (uint32_t u = 0; u < 4; ++u) {
+            const uint32_t wi = w0 + u * WAVE + lane;
+            if (wi < words) any |= *(ra + wi) & *(rb + wi);
+          }
+          nread += min(4 * WAVE, words - w0);
+          found = __ballot(any != 0) != 0;
+        }
+        if (lane == 0) {
+          if (found) cflag[i] = 1;
+          if (counting) atomicAdd(&s.stat[3], nread);  // a word pair counts as one probe
+        }
+      }
+      __syncthreads();
+    }
     // ---- pairs without a witness leave the j-ball (both directions) ----
+    // Eight neighbouring pairs to a wave, the next eight to the next wave: the
+    // pairs of one item are often all hubs, with hundreds of follow-up items
+    // that one wave would write alone, and eight are enough to merge atomics.
     for (uint32_t base = 0; base < n; base += LV_THREADS) {
-      const uint32_t i = base + threadIdx.x;
+      const uint32_t i =
+          base + (merge ? ((lane >> 3) * LV_WAVES + wave) * 8 + (lane & 7) : threadIdx.x);
       const bool drop = i < n && !cflag[i];
       uint32_t x = 0, w = 0, bx = 0, dx = 0, bw = 0, dw = 0;
-      bool w1 = false, w2 = false;
-      if (drop) {
+      if (i < n) {
         x = cx[i];
         w = cw[i];
+      }
+      if (drop) {
         bx = d.rp[x];
         dx = d.len[x];
         bw = d.rp[w];
         dw = d.len[w];
-        const uint64_t mx = 1ull << (w & 63), mw = 1ull << (x & 63);
-        w1 = atomicAnd(&row(d.L[j], d.W, x)[w >> 6], ~mx) & mx;
-        w2 = atomicAnd(&row(d.L[j], d.W, w)[x >> 6], ~mw) & mw;
-        if (w1) atomicOr(&row(d.Dm[j], d.W, x)[w >> 6], mx);
-        if (w2) atomicOr(&row(d.Dm[j], d.W, w)[x >> 6], mw);
       }
+      bool w1 = false, w2 = false;
+      if (__ballot(drop)) clear_pairs(d.L[j], d.Dm[j], d.W, x, w, drop, merge, &w1, &w2);
       if (counting && (w1 || w2)) atomicAdd(&s.stat[4], (uint32_t)w1 + (uint32_t)w2);
       // Follow-up work of both events: the events themselves, and items over
       // the row of each event's source -- the support update (j == h), else
@@ -1021,6 +1368,8 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
     for (uint32_t i = threadIdx.x; i < n; i += LV_THREADS) cflag[i] = 0;
     if (threadIdx.x == 0) {
       s.fill = 0;
+      s.longrow = 0;
+      s.more = 0;
       s.ndense = 0;
     }
     __syncthreads();
@@ -1038,7 +1387,7 @@ __global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ de
   if (c->halt) return;
   // a round that peels every remaining edge leaves no ball or support that
   // could matter: the decomposition ends with it
-  if (c->nR == c->live) return;
+  if (c->nRc.v == c->live) return;
   const RoundCtx rc = round_ctx(c);
   if (!c->recovering && (c->cnt[j][rc.p].iovf || (d.serial & 4u))) {
     // work list overflowed (or forced): halt; the host re-runs this level in windows
@@ -1074,11 +1423,21 @@ __device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint
   const uint64_t* Dh = d.Dm[d.h];
   uint32_t* Rn = d.R[rc.p ^ 1];
   const Item* items = d.itl[d.h + 1];
-  uint32_t* nPush = &d.ctl->nPush[rc.p];
-  const uint32_t stride = nwg * wpb;
-  // Items are dealt to workgroups first, then to their waves.  Each wave
-  // takes U items per step (its items it, it + stride, ...), and the step's
-  // successors and their slots (state, neighbour, edge id) load while the
+  uint32_t* nPush = &d.ctl->nPushc[rc.p].v;
+  // Items are dealt in blocks of up to four: neighbours in the list share the
+  // event's target (whose ball row then stays in this CU's L1) or its source
+  // row, and waves next to each other share an XCD's L2; longer blocks leave
+  // waves with only long rows.  Rounds with fewer items than waves deal them
+  // to workgroups first.
+  const bool flip = d.perm != nullptr;
+  const uint32_t waves = nwg * wpb, wave = threadIdx.x / WAVE;
+  const uint32_t sh = nit <= waves ? 0 : nit <= 2 * waves ? 1 : 2;  // log2 of the block
+  const uint32_t wid = sh == 0 ? wave * nwg + wg : xcd_first(wg, nwg) * wpb + wave;
+  // this wave's s-th item
+  auto item_at = [&](uint32_t s) {
+    return ((wid + (s >> sh) * waves) << sh) + (s & ((1u << sh) - 1));
+  };
+  // U items per step; the step's successors and their slots load while the
   // current items' ball words and support atomics are in flight: more memory
   // operations outstanding per wave than one item's dependent chain.
   // a slot is one 8-byte word: neighbour b (with SLOT_GONE once the edge is
@@ -1087,10 +1446,11 @@ __device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint
     Item I;
     uint32_t b, e;
   };
-  auto fetch = [&](uint32_t i, Slot& S) {
-    S.I = Item{0, 0, 0, 0};
+  auto fetch = [&](uint32_t s, Slot& S) {
+    S.I = Item{0, 0, ~0u, 0};
     S.b = SLOT_GONE;
     S.e = 0;
+    const uint32_t i = item_at(s);
     if (i < nit) {
       S.I = items[i];
       if (lane < meta_len(S.I.meta)) {
@@ -1100,32 +1460,36 @@ __device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint
       }
     }
   };
-  // w in b's old ball when the event's source a < b, in its new ball when a > b
+  // w in b's old ball when the event's source a < b, in its new ball when
+  // a > b; the other way round in renumbered graphs: the long rows are the
+  // hubs', which come first, and then need the new ball only (the other side
+  // reads the change marks too)
   auto hit_of = [&](const Slot& S) -> bool {
     if (S.b & SLOT_GONE) return false;
     const size_t o = (size_t)S.I.y * d.W + (S.b >> 6);
     uint64_t word = *(Lh + o);
-    if (S.I.x < S.b) word |= *(Dh + o);
+    if ((S.I.x < S.b) != flip) word |= *(Dh + o);
     return (word >> (S.b & 63)) & 1ull;
   };
-  uint32_t it = (threadIdx.x / WAVE) * nwg + wg;
   Slot A[U];
 #pragma unroll
-  for (uint32_t u = 0; u < U; ++u) fetch(it + u * stride, A[u]);
-  while (it < nit) {
-    bool hit[U], push[U];
-    uint32_t e[U];
+  for (uint32_t u = 0; u < U; ++u) fetch(u, A[u]);
+  uint32_t acc = 0;  // lost by this lane's edge to the items so far of the same slots
+  for (uint32_t it = 0; item_at(it) < nit; it += U) {
+    bool hit[U];
+    uint32_t e[U], base[U + 1], dec[U];
 #pragma unroll
     for (uint32_t u = 0; u < U; ++u) {
       hit[u] = hit_of(A[u]);
       e[u] = A[u].e;
+      base[u] = A[u].I.base;
     }
     if (stat) {
       uint32_t hits = 0, slots = 0, taken = 0;
       for (uint32_t u = 0; u < U; ++u) {
+        taken += item_at(it + u) < nit;
         hits += (uint32_t)__popcll(__ballot(hit[u]));
         slots += meta_len(A[u].I.meta);
-        taken += it + u * stride < nit;
       }
       if (lane == 0) {
         atomicAdd(&stat[0], taken);
@@ -1134,23 +1498,28 @@ __device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint
       }
     }
 #pragma unroll
-    for (uint32_t u = 0; u < U; ++u) fetch(it + (U + u) * stride, A[u]);
-    bool any = false;
+    for (uint32_t u = 0; u < U; ++u) fetch(it + U + u, A[u]);
+    base[U] = A[0].I.base;
+    // items over the same slots (events of one source) are charged together
 #pragma unroll
     for (uint32_t u = 0; u < U; ++u) {
-      push[u] = hit[u] && atomicSub(&d.sup[e[u]], 1u) == rc.k - 1;
-      any |= push[u];
+      acc += hit[u];
+      dec[u] = base[u] == base[u + 1] ? 0u : acc;
+      if (base[u] != base[u + 1]) acc = 0;
     }
-    if (__ballot(any)) {
-      uint32_t mine = 0;
+    uint32_t push = 0;
 #pragma unroll
-      for (uint32_t u = 0; u < U; ++u) mine += push[u];
-      uint32_t slot = wave_reserve(nPush, mine);
+    for (uint32_t u = 0; u < U; ++u)
+      if (dec[u]) {
+        const uint32_t old = atomicSub(&d.sup[e[u]], dec[u]);
+        push |= (uint32_t)(old > rc.k - 2 && old - dec[u] <= rc.k - 2) << u;
+      }
+    if (__ballot(push != 0)) {
+      uint32_t slot = wave_reserve(nPush, (uint32_t)__popc(push));
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u)
-        if (push[u]) Rn[slot++] = e[u];
+        if ((push >> u) & 1u) Rn[slot++] = e[u];
     }
-    it += U * stride;
   }
 }
 
@@ -1160,7 +1529,7 @@ __global__ void __launch_bounds__(256) k_support(const Dev* __restrict__ devs) {
   if (c->done) return;
   const uint32_t list = d.h + 1;
   if (c->halt) return;
-  if (c->nR == c->live) return;  // the last round: nothing left to update
+  if (c->nRc.v == c->live) return;  // the last round: nothing left to update
   const RoundCtx rc = round_ctx(c);
   if (!c->recovering && (c->cnt[list][rc.p].iovf || (d.serial & 8u))) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1206,32 +1575,36 @@ __global__ void k_stats_fold(const Dev* __restrict__ dp, uint32_t first, uint32_
 
 // The counters of one round parity back to zero.
 __device__ __forceinline__ void reset_parity(Ctl* c, uint32_t h, uint32_t q) {
-  for (uint32_t j = 1; j <= h + 1; ++j) c->cnt[j][q] = Cnt{0, 0, 0, 0};
-  c->nPush[q] = 0;
+  for (uint32_t j = 1; j <= h + 1; ++j) {
+    Cnt& n = c->cnt[j][q];
+    n.nit = n.iovf = n.nev = n.ovf = 0;
+  }
+  c->nPushc[q].v = 0;
 }
 
 // ---- K5: end of round ------------------------------------------------------
 // One thread closes the round (counters, next round's peel set and level-jump
 // flag).  When the round pushed no edge, the next round starts with a level
 // jump, and every workgroup computes its share of the live minimum now.  A
-// workgroup may read the push count after the closing thread reset it: it
-// then computes a minimum that nobody reads, which is harmless, and it never
-// skips one that is needed (the count is only ever reset to zero).
+// workgroup may look while the closing thread is at work, or after it: so it
+// asks whether either parity's push count is zero.  This round's count is not
+// written here, so a needed minimum is never skipped; one computed because the
+// other count is zero is read by nobody.
 __global__ void __launch_bounds__(256) k_end(const Dev* __restrict__ devs) {
   const Dev& d = devs[blockIdx.y];
   Ctl* c = d.ctl;
   // one decision per workgroup, taken before its closing thread (workgroup 0)
   // changes anything, so that every thread of it takes the same branch
   __shared__ uint32_t s_mode;  // 0 close only, 1 minimum and close, 2 nothing
-  if (threadIdx.x == 0) s_mode = (c->done || c->halt) ? 2u : (c->nPush[c->r & 1] == 0 ? 1u : 0u);
+  if (threadIdx.x == 0) s_mode = (c->done || c->halt) ? 2u : (c->nPushc[0].v == 0 || c->nPushc[1].v == 0 ? 1u : 0u);
   __syncthreads();
   const uint32_t mode = s_mode;
   if (mode == 2) return;
   if (mode == 1) jump_partials(d);
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
   const uint32_t p = c->r & 1, q = p ^ 1;
-  const uint32_t pushed = c->nPush[p];
-  c->cnt[1][p].nev = 2 * c->nR;  // level-1 events: both directions of every peeled edge
+  const uint32_t pushed = c->nPushc[p].v;
+  c->cnt[1][p].nev = 2 * c->nRc.v;  // level-1 events: both directions of every peeled edge
   c->events += c->cnt[d.h][p].nev;
   for (uint32_t j = 1; j <= d.h; ++j) c->levents[j] += c->cnt[j][p].nev;
   uint32_t any = 0;
@@ -1240,14 +1613,27 @@ __global__ void __launch_bounds__(256) k_end(const Dev* __restrict__ devs) {
   // next one clears the change marks they list and peels the edges it pushed)
   reset_parity(c, d.h, q);
   c->overflows += any ? 1 : 0;
-  c->live -= c->nR;
+  c->live -= c->nRc.v;
   c->r += 1;
-  c->nR = pushed;
+  c->nRc.v = pushed;
   c->jump = pushed == 0;
   d.status[2] = c->live;
   if (c->live == 0) {
     c->done = 1;
     d.status[0] = 1;
+  }
+}
+
+// A finished graph's outputs in the caller's edge order (renumbered graphs).
+// Written here and not as edges are peeled: neighbouring own numbers are far
+// apart in the caller's order, and scattered stores to lines that other XCDs
+// are writing too cost more than this pass (Chung-Lu 100k h = 1: the marking
+// of the largest round 740 us with them, 274 us without).
+__global__ void __launch_bounds__(256) k_outputs(Dev d) {
+  for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < d.m; e += gridDim.x * blockDim.x) {
+    const uint32_t own = d.ne[e];
+    d.out_t[e] = d.t[own];
+    if (d.out_rho) d.out_rho[e] = d.rho[own];
   }
 }
 
@@ -1344,7 +1730,7 @@ __global__ void __launch_bounds__(256) k_fill_level(const Dev* __restrict__ dp, 
   const Dev& d = *dp;
   const Ctl* c = d.ctl;
   const RoundCtx rc = round_ctx(c);
-  const uint64_t nA = 2ull * c->nR;
+  const uint64_t nA = 2ull * c->nRc.v;
   // the directed removals x-lost-z
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   const uint64_t ahi = min(hi, nA);
@@ -1440,7 +1826,6 @@ __device__ void compact_rows(const Dev& d, uint32_t wave, uint32_t nwaves) {
       if (live && at != i) {
         const uint32_t z = beg + at;
         d.cix[z] = y;
-        d.eid[z] = e;
         d.srem[z] = ALIVE;
         d.ce[z] = w;
         if (y > x) d.s1[e] = z;
@@ -1511,7 +1896,7 @@ __device__ uint64_t acct_build(const Dev& d, uint32_t x, uint32_t r, uint64_t li
       if (d.srem[q] > r) f += 8 + 4ull * d.acct_deg[d.cix[q]];
   } else if (d.h >= 3) {
     const uint64_t* B = row(d.L[d.h - 1], d.W, x);
-    for (uint32_t i = lane; i < d.W; i += WAVE) {
+    for (uint32_t i = lane; i < d.ctl->words; i += WAVE) {
       uint64_t wd = B[i];
       if (i == (x >> 6)) wd &= ~(1ull << (x & 63));  // x itself is counted above
       while (wd) {
@@ -1534,8 +1919,9 @@ __global__ void __launch_bounds__(256) k_acct_init(const Dev* __restrict__ dp) {
   for (uint32_t x = blockIdx.x * wpb + threadIdx.x / WAVE; x < d.n; x += gridDim.x * wpb) {
     const uint64_t* B = row(d.L[d.h], d.W, x);
     uint32_t c = 0;
-    for (uint32_t i = lane; i < d.W; i += WAVE) c += (uint32_t)__popcll(B[i]);
-    c = wave_sum(c);
+    if (x < d.ctl->nact)
+      for (uint32_t i = lane; i < d.ctl->words; i += WAVE) c += (uint32_t)__popcll(B[i]);
+    c = max(1u, wave_sum(c));  // an isolated vertex's ball holds itself
     if (lane == 0) {
       d.acct_ball[x] = c - 1;
       d.acct_deg[x] = d.rp[x + 1] - d.rp[x];
@@ -1568,7 +1954,7 @@ __global__ void __launch_bounds__(256) k_acct_start(const Dev* __restrict__ dp) 
 // True when this round leaves edges for the count (not finished, not the
 // round that removes everything).
 __device__ __forceinline__ bool acct_round_counts(const Ctl* c) {
-  return !c->done && !c->halt && !c->err && c->nR < c->live;
+  return !c->done && !c->halt && !c->err && c->nRc.v < c->live;
 }
 
 // Round, step 1: degrees after the removals; vertices whose h-ball changed
@@ -1580,7 +1966,7 @@ __global__ void __launch_bounds__(256) k_acct_round1(const Dev* __restrict__ dp)
   if (!acct_round_counts(c)) return;
   const RoundCtx rc = round_ctx(c);
   const uint32_t stride = gridDim.x * blockDim.x, tid = blockIdx.x * blockDim.x + threadIdx.x;
-  const uint32_t nR = c->nR;
+  const uint32_t nR = c->nRc.v;
   for (uint32_t i = tid; i < 2 * nR; i += stride) {
     const uint32_t e = d.R[rc.p][i >> 1];
     atomicSub(&d.acct_deg[(i & 1) ? d.ev[e] : d.eu[e]], 1u);
@@ -1630,7 +2016,7 @@ __global__ void __launch_bounds__(256) k_acct_round2(const Dev* __restrict__ dp)
       bytes += sx + acct_s(d, b) + 4;
     }
   }
-  const uint32_t nR = c->nR;
+  const uint32_t nR = c->nRc.v;
   for (uint32_t k = wid; k < 2 * nR; k += nw) {
     const uint32_t e = d.R[rc.p][k >> 1];
     const uint32_t z = (k & 1) ? d.ev[e] : d.eu[e];
@@ -1645,7 +2031,7 @@ __global__ void __launch_bounds__(256) k_acct_round2(const Dev* __restrict__ dp)
     } else if (d.h >= 3) {
       const uint64_t* B = row(d.L[d.h - 1], d.W, z);
       const uint64_t* D = row(d.Dm[d.h - 1], d.W, z);
-      for (uint32_t i = lane; i < d.W; i += WAVE) {
+      for (uint32_t i = lane; i < d.ctl->words; i += WAVE) {
         uint64_t wd = B[i] | D[i];
         while (wd) {
           claim(i * 64 + (uint32_t)(__ffsll((unsigned long long)wd) - 1));
@@ -1670,7 +2056,7 @@ __global__ void __launch_bounds__(256) k_acct_round3(const Dev* __restrict__ dp)
   if (!acct_round_counts(c) || c->acct_incomplete) return;
   const RoundCtx rc = round_ctx(c);
   const uint32_t wpb = blockDim.x / WAVE;
-  const uint64_t live_m = c->live - c->nR;
+  const uint64_t live_m = c->live - c->nRc.v;
   uint64_t bytes = 0;
   const uint32_t nv = c->acct_nv;
   for (uint32_t k = blockIdx.x * wpb + threadIdx.x / WAVE; k < nv; k += gridDim.x * wpb)
