@@ -15,9 +15,10 @@
 #include "../../include/hotruss.h"
 #include "hotruss_dev.h"
 #include "hotruss_kernels.hip"
+#include "hotruss_team.hip"
 #include "hotruss_hindex.hip"
 
-// status words per engine slot: {done, halt, live edges, unused}
+// status words per engine slot: {done, halt, live edges, round}
 #define HO_STATUS_WORDS 4
 
 namespace hotruss {
@@ -26,7 +27,7 @@ namespace {
 
 constexpr size_t ALIGN = 256;
 constexpr size_t MAX_LDS_ROW = 64 * 1024;  // one bitset row per workgroup in LDS
-size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
+constexpr size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Plan {
   uint32_t n = 0, h = 0, W = 0, evcap = 0, itcap = 0;
@@ -403,18 +404,31 @@ void launch_level(const Dev* devs, uint32_t S, const RoundGrid& g, hipStream_t s
                        dim3(LV_NARROW_THREADS), 0, s, devs, j);
 }
 
-void launch_step(const Dev* devs, uint32_t S, uint32_t hmax, const RoundGrid& g, hipStream_t s) {
+void launch_compact(const Dev& d, hipStream_t s) {
+  const unsigned T = 256;
+  hipLaunchKernelGGL(k_compact, dim3(grid_for(d.n, T / 16)), dim3(T), 0, s, d);
+}
+
+// Up to where a team takes a step (both sides measured: see TeamLimits).
+TeamLimits team_limits(uint32_t S, uint32_t rounds) {
+  return S > 1 ? TeamLimits{rounds, 4096, 4096, 32768} : TeamLimits{rounds, 4096, 1024, 16384};
+}
+
+// plan: room for the list of running slots (more than one slot only).
+void launch_team(const Dev* devs, uint32_t S, uint32_t* plan, const TeamLimits& lim, hipStream_t s) {
+  if (S > 1) hipLaunchKernelGGL(k_team_plan, dim3(1), dim3(1024), 0, s, devs, S, plan);
+  hipLaunchKernelGGL(k_team, dim3(std::max(8, num_cu() / 8 * 8)), dim3(TEAM_THREADS), 0, s, devs,
+                     S > 1 ? plan : nullptr, lim);
+}
+
+// A round, or what the team kernel left of it, by the whole chip.
+void launch_round(const Dev* devs, uint32_t S, uint32_t hmax, const RoundGrid& g, hipStream_t s,
+                  bool after_team) {
   const unsigned T = 256;
   hipLaunchKernelGGL(k_mark, dim3(g.mark, S), dim3(T), 0, s, devs);
   for (uint32_t j = 2; j <= hmax; ++j)
     launch_level(devs, S, g, s, j);
-  hipLaunchKernelGGL(k_support, dim3(g.support, S), dim3(T), 0, s, devs);
-  hipLaunchKernelGGL(k_end, dim3(g.jump, S), dim3(T), 0, s, devs);
-}
-
-void launch_compact(const Dev& d, hipStream_t s) {
-  const unsigned T = 256;
-  hipLaunchKernelGGL(k_compact, dim3(grid_for(d.n, T / 16)), dim3(T), 0, s, d);
+  hipLaunchKernelGGL(k_support, dim3(g.support, S), dim3(T), 0, s, devs, after_team ? 1u : 0u);
 }
 
 hoStatus read_ctl(const Dev& d, Ctl* host, hipStream_t s) {
@@ -491,7 +505,7 @@ hoStatus recover_step(const Dev& d, const RoundGrid& g, hipStream_t s, uint32_t 
     }
     HOCHK(tm.begin(s));
     if (step <= d.h) launch_level(dp, 1, g, s, step);
-    else hipLaunchKernelGGL(k_support, dim3(g.support), dim3(T), 0, s, dp);
+    else hipLaunchKernelGGL(k_support, dim3(g.support), dim3(T), 0, s, dp, 0u);
     HOCHK(tm.end(s, step <= d.h ? KT_LEVEL : KT_SUPPORT));
     if (d.spart) {
       if (step <= d.h) hipLaunchKernelGGL(k_stats_fold, dim3(1), dim3(256), 0, s, dp, 0u, 5u, g.level);
@@ -506,11 +520,12 @@ hoStatus recover_step(const Dev& d, const RoundGrid& g, hipStream_t s, uint32_t 
 }
 
 // Run one slot's round steps from `from` on (2..h: level j, h+1: support
-// update) and end the round, from the host; a step whose list kernel halts on
+// update), from the host, and end the round (end_phase < 0: leave that to the
+// team kernel; else what the next round starts with); a step whose list kernel halts on
 // an overflowed work list (or every step from `from` when recover_first) is
 // re-run in windows by recover_step.
 hoStatus steps_host(const Dev& d, const RoundGrid& g, hipStream_t s, uint32_t from,
-                    bool recover_first, StepTimer& tm) {
+                    bool recover_first, StepTimer& tm, int end_phase) {
   const unsigned T = 256;
   const Dev* dp = d.self;
   Ctl c;
@@ -519,7 +534,7 @@ hoStatus steps_host(const Dev& d, const RoundGrid& g, hipStream_t s, uint32_t fr
     if (!recover) {
       HOCHK(tm.begin(s));
       if (step <= d.h) launch_level(dp, 1, g, s, step);
-      else hipLaunchKernelGGL(k_support, dim3(g.support), dim3(T), 0, s, dp);
+      else hipLaunchKernelGGL(k_support, dim3(g.support), dim3(T), 0, s, dp, 0u);
       HOCHK(tm.end(s, step <= d.h ? KT_LEVEL : KT_SUPPORT));
       if (d.spart) {
         if (step <= d.h) hipLaunchKernelGGL(k_stats_fold, dim3(1), dim3(256), 0, s, dp, 0u, 5u, g.level);
@@ -538,9 +553,11 @@ hoStatus steps_host(const Dev& d, const RoundGrid& g, hipStream_t s, uint32_t fr
     hipLaunchKernelGGL(k_acct_round3, dim3(ag), dim3(T), 0, s, dp);
     hipLaunchKernelGGL(k_acct_reset, dim3(1), dim3(64), 0, s, dp);
   }
-  HOCHK(tm.begin(s));
-  hipLaunchKernelGGL(k_end, dim3(g.jump), dim3(T), 0, s, dp);
-  HOCHK(tm.end(s, KT_ADVANCE));
+  if (end_phase >= 0) {
+    HOCHK(tm.begin(s));
+    hipLaunchKernelGGL(k_end, dim3(g.jump), dim3(T), 0, s, dp, (uint32_t)end_phase, 0u);
+    HOCHK(tm.end(s, KT_ADVANCE));
+  }
   HIPCHK(hipGetLastError());
   return HO_OK;
 }
@@ -619,16 +636,18 @@ struct GraphKey {
   int dev;
   const void* devs;
   uint32_t S, hmax, jump, mark, level, support;
+  int which;
   bool operator==(const GraphKey& o) const {
     return dev == o.dev && devs == o.devs && S == o.S && hmax == o.hmax && jump == o.jump &&
-           mark == o.mark && level == o.level && support == o.support;
+           mark == o.mark && level == o.level && support == o.support &&
+           which == o.which;
   }
 };
 struct GraphCacheEntry {
   GraphKey key;
-  hipGraphExec_t exec[3];
+  hipGraphExec_t exec;
 };
-constexpr size_t GRAPH_CACHE = 64;
+constexpr size_t GRAPH_CACHE = 256;
 std::mutex g_graph_mu;
 std::vector<GraphCacheEntry> g_graph_cache;
 
@@ -637,7 +656,7 @@ std::vector<GraphCacheEntry> g_graph_cache;
 // kernel returns at once).
 size_t engine_header_bytes(uint32_t S) {
   return up(sizeof(Dev) * S) + up(4ull * HO_STATUS_WORDS * S) + up(4ull * NSTAT * STAT_GRID) +
-         up(sizeof(Ctl));
+         up(sizeof(Ctl)) + up(sizeof(Team) * S) + up(4ull * (S + 1));
 }
 
 // Pinned host buffers and events of the plain entry point, kept per host
@@ -684,6 +703,57 @@ size_t host_bytes(uint32_t S) {
   return up(8ull * HO_STATUS_WORDS * S + sizeof(Ctl)) + 2 * sizeof(Dev) * (size_t)S;
 }
 
+// Graphs an engine launches (see Engine::graph_shape).
+enum { GR_ONE, GR_FEW, GR_MANY, GR_LONG, GR_CHIP, GR_CHIPS, GR_N };
+
+// Which kind of graph runs next, team steps or whole-chip rounds: the one that
+// got further per microsecond lately.  Neither is better by the sizes alone --
+// what counts is how many rounds a graph's peeling has between two large steps:
+// R-MAT 14 h = 2 takes 224 ms by the chip and 257 by teams, Chung-Lu 20,000
+// 98 and 85, and many graphs change sides on the way (er 12,000 deg 15: 6.7 by
+// teams, 5.6 by the chip, 5.4 as it is).  Progress is rounds, slots weighted
+// by their live edges (the largest slot is the last to end).  A step that the
+// team leaves to the whole chip costs about 40 us more than a whole-chip
+// round, so team steps that run many rounds each are never doubted; if they
+// run `few`, the other kind is tried for three launches (two are known when
+// the fourth is picked), and the better one stays for a number of launches
+// that doubles as long as it wins.
+struct Pace {
+  double rate[2] = {0, 0};  // 0 team steps, 1 whole-chip rounds
+  bool chip = false, trial = false, few = false, last = false;
+  uint32_t left = 0, stay = 4;
+
+  void saw(bool c, bool few_rounds, double progress, double us) {
+    const double now = progress / us;
+    rate[c] = last == c ? 0.5 * (rate[c] + now) : now;
+    last = c;
+    few = !c && few_rounds;
+  }
+  // the kind of the next launch
+  bool pick() {
+    if (left) {
+      --left;
+      return chip;
+    }
+    if (!chip && !trial && !few) return false;
+    if (!trial) {
+      trial = true;
+      chip = !chip;
+      left = 2;
+      return chip;
+    }
+    trial = false;
+    if (rate[chip] < rate[!chip]) {
+      chip = !chip;  // the other one was right
+      stay = std::min(2 * stay, 32u);
+    } else {
+      stay = 4;
+    }
+    left = stay - 1;
+    return chip;
+  }
+};
+
 class Engine {
  public:
   hipStream_t s = nullptr;
@@ -693,6 +763,7 @@ class Engine {
   uint64_t cap_factor = 128;
   RoundGrid g{};
   bool plain = false;
+  bool host_rounds = false;  // every round driven from the host, without the team kernel
   Dev* devs_d = nullptr;
   uint32_t* status_d = nullptr;
   uint32_t* spart_d = nullptr;
@@ -700,27 +771,28 @@ class Engine {
   std::vector<Dev> slot_dev;
   std::vector<uint64_t> slot_since;  // first graph launch that can report on the slot
   std::vector<uint32_t> live_seen;   // live edges in the slot's latest status snapshot
-  std::vector<uint32_t> compact_at;  // compact the slot's rows once live falls to this
-  std::vector<uint8_t> compact_each; // testing: compact at every opportunity
+  std::vector<uint32_t> round_seen;  // and its round
   Pool pool;
   std::vector<Request> reqs;
   std::vector<size_t> queue;
   Ctl* idle_ctl_d = nullptr;
+  Team* team_d = nullptr;
+  uint32_t* plan_d = nullptr;  // the team kernel's list of running slots
   uint32_t* hstat = nullptr;  // pinned: 2 buffers x S x status words, then a Ctl
   Dev* idle_h = nullptr;      // pinned: descriptor of each idle slot
   Dev* dev_h = nullptr;       // pinned: staging of each admitted slot's descriptor
   hipEvent_t ev[2] = {nullptr, nullptr};
   bool borrowed_host = false;  // pinned buffers and events belong to the thread's cache
-  hipGraphExec_t exec[3] = {nullptr, nullptr, nullptr};
-  bool owns_graphs = false;
+  hipGraphExec_t exec[GR_N] = {};
+  bool owned[GR_N] = {};
   bool copy_failed = false;
   uint64_t steps = 0;
+  Pace pace;
 
   ~Engine() {
     if (s) (void)hipStreamSynchronize(s);  // nothing in flight may target freed host buffers
-    if (owns_graphs)
-      for (auto& e : exec)
-        if (e) (void)hipGraphExecDestroy(e);
+    for (int i = 0; i < GR_N; ++i)
+      if (owned[i]) (void)hipGraphExecDestroy(exec[i]);
     if (borrowed_host) return;
     for (auto& e : ev)
       if (e) (void)hipEventDestroy(e);
@@ -742,15 +814,15 @@ class Engine {
     devs_d = (Dev*)base;
     status_d = (uint32_t*)(base + up(sizeof(Dev) * S));
     spart_d = (uint32_t*)(base + up(sizeof(Dev) * S) + up(4ull * HO_STATUS_WORDS * S));
-    idle_ctl_d = (Ctl*)(base + up(sizeof(Dev) * S) + up(4ull * HO_STATUS_WORDS * S) +
-                        up(4ull * NSTAT * STAT_GRID));
+    idle_ctl_d = (Ctl*)((uintptr_t)spart_d + up(4ull * NSTAT * STAT_GRID));
+    team_d = (Team*)((uintptr_t)idle_ctl_d + up(sizeof(Ctl)));
+    plan_d = (uint32_t*)((uintptr_t)team_d + up(sizeof(Team) * S));
     pool.reset(engine_header_bytes(S), bytes);
     slot_req.assign(S, -1);
     slot_dev.assign(S, Dev{});
     slot_since.assign(S, 0);
     live_seen.assign(S, 0);
-    compact_at.assign(S, 0);
-    compact_each.assign(S, 0);
+    round_seen.assign(S, 0);
     if (borrow_host) {
       HostCache& hc = host_cache();
       HOCHK(hc.ensure(host_bytes(S)));
@@ -827,14 +899,14 @@ class Engine {
       Dev d = carve(r.plan, (void*)(base + off), r.rp, r.ci, r.t, r.rho);
       d.self = devs_d + slot;
       d.status = status_d + HO_STATUS_WORDS * slot;
+      d.team = team_d + slot;
       d.nminpart = g.jump;
       if (r.has_tune)
         d.serial = r.tune.flags & (HO_FLAG_SERIAL_LEVELS | HO_FLAG_SERIAL_SUPPORT | HO_FLAG_COMPACT_EACH);
       slot_dev[slot] = d;
       slot_since[slot] = steps;
-      live_seen[slot] = 0;
-      compact_at[slot] = compact_next((uint32_t)r.m);
-      compact_each[slot] = r.has_tune && (r.tune.flags & HO_FLAG_COMPACT_EACH) ? 1 : 0;
+      live_seen[slot] = (uint32_t)r.m;
+      round_seen[slot] = 0;
       HOCHK(start_slot(d, r.has_tune ? &r.tune : nullptr, sup0, sup1));
     }
     return HO_OK;
@@ -849,51 +921,82 @@ class Engine {
     dev_h[i] = d;
     HIPCHK(hipMemcpyAsync(d.self, &dev_h[i], sizeof(Dev), hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_post_init, dim3(1), dim3(64), 0, s, d);
-    hipLaunchKernelGGL(k_first_min, dim3(g.jump), dim3(T), 0, s, d.self);
+    if (host_rounds) hipLaunchKernelGGL(k_first_min, dim3(g.jump), dim3(T), 0, s, d.self);
     HIPCHK(hipGetLastError());
     return HO_OK;
   }
 
-  hoStatus ensure_graphs() {
-    if (exec[0]) return HO_OK;
+  // The captured graphs (a graph is made when a call first needs it).
+  // Team steps: the team kernel runs every slot's rounds up to the first step
+  // that is large enough for the whole chip, and the round kernels do that step
+  // and the rest of its round (the next team kernel closes it).  One
+  // decomposition: a launch of the team kernel runs to the next large step;
+  // many: short enough that finished slots are refilled in time.  Whole-chip
+  // rounds: the team kernel at the head does no more than open the first round
+  // (and close one that the last team step left open).  h = 1 is always that: its
+  // round is three kernels (Chung-Lu 2,000: 0.81 ms, by a team 1.19; 100k: 6.5
+  // and 7.5).
+  struct GraphShape {
+    bool chip;
+    uint32_t steps, rounds;  // rounds: of each team step, at most
+  };
+  GraphShape graph_shape(int which) const {
+    static constexpr uint32_t one[GR_N] = {1, 4, 16, 16, 32, 128}, many[GR_N] = {1, 2, 8, 2, 32, 128},
+                              flat[GR_N] = {4, 16, 32, 128, 0, 0};
+    if (S == 1 && hmax == 1) return {true, flat[which], 0};
+    return {which >= GR_CHIP, S == 1 ? one[which] : many[which],
+            S == 1 ? 4096u : which == GR_LONG ? 256u : 32u};
+  }
+  void capture(int which, hipStream_t cap) const {
+    const GraphShape gs = graph_shape(which);
+    if (gs.chip) {
+      launch_team(devs_d, S, plan_d, TeamLimits{2, 0, 0, 0}, cap);
+      hipLaunchKernelGGL(k_compact_due, dim3(g.mark, S), dim3(256), 0, cap, devs_d);
+    }
+    for (uint32_t k = 0; k < gs.steps; ++k) {
+      if (!gs.chip) launch_team(devs_d, S, plan_d, team_limits(S, gs.rounds), cap);
+      launch_round(devs_d, S, hmax, g, cap, !gs.chip || k == 0);
+      if (gs.chip)
+        hipLaunchKernelGGL(k_end, dim3(g.jump, S), dim3(256), 0, cap, devs_d,
+                           k + 1 < gs.steps ? 0u : ROUND_CLOSED, k == 0 ? 1u : 0u);
+    }
+  }
+
+  hoStatus ensure_graph(int which) {
+    if (exec[which]) return HO_OK;
     int dev = 0;
     HIPCHK(hipGetDevice(&dev));
-    const GraphKey key{dev, devs_d, S, hmax, g.jump, g.mark, g.level, g.support};
+    const GraphKey key{dev, devs_d, S, hmax, g.jump, g.mark, g.level, g.support, which};
     {
       std::lock_guard<std::mutex> lk(g_graph_mu);
       for (auto& e : g_graph_cache)
         if (e.key == key) {
-          for (int i = 0; i < 3; ++i) exec[i] = e.exec[i];
+          exec[which] = e.exec;
           return HO_OK;
         }
     }
     hipStream_t cap;
     HIPCHK(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-    const uint32_t sizes[3] = {4, 32, 128};
     hoStatus st = HO_OK;
-    for (int i = 0; i < 3 && st == HO_OK; ++i) {
-      hipGraph_t graph;
-      if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-        st = HO_ERR_HIP;
-        break;
-      }
-      for (uint32_t k = 0; k < sizes[i]; ++k) launch_step(devs_d, S, hmax, g, cap);
+    hipGraph_t graph;
+    if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+      st = HO_ERR_HIP;
+    } else {
+      capture(which, cap);
       if (hipStreamEndCapture(cap, &graph) != hipSuccess) {
         st = HO_ERR_HIP;
-        break;
+      } else {
+        if (hipGraphInstantiate(&exec[which], graph, nullptr, nullptr, 0) != hipSuccess) st = HO_ERR_HIP;
+        (void)hipGraphDestroy(graph);
       }
-      if (hipGraphInstantiate(&exec[i], graph, nullptr, nullptr, 0) != hipSuccess) st = HO_ERR_HIP;
-      (void)hipGraphDestroy(graph);
     }
     (void)hipStreamDestroy(cap);
     if (st != HO_OK) return st;
     std::lock_guard<std::mutex> lk(g_graph_mu);
-    if (g_graph_cache.size() < GRAPH_CACHE) {
-      GraphCacheEntry e{key, {exec[0], exec[1], exec[2]}};
-      g_graph_cache.push_back(e);
-    } else {
-      owns_graphs = true;
-    }
+    if (g_graph_cache.size() < GRAPH_CACHE)
+      g_graph_cache.push_back(GraphCacheEntry{key, exec[which]});
+    else
+      owned[which] = true;
     return HO_OK;
   }
 
@@ -906,20 +1009,25 @@ class Engine {
   // Retire finished slots seen in the status snapshot taken after graph
   // launch `at`; returns whether an active slot halted.  A slot admitted
   // after that launch was enqueued is not described by the snapshot.
-  bool retire(const uint32_t* st, uint64_t at) {
+  // progress: rounds run since the snapshot before (see Pace).
+  bool retire(const uint32_t* st, uint64_t at, double* progress) {
     bool halted = false;
+    double edges = 0, rounds = 0;
     for (uint32_t i = 0; i < S; ++i) {
       const int ri = slot_req[i];
       if (ri < 0 || at < slot_since[i]) continue;
       const uint32_t* sw = st + HO_STATUS_WORDS * i;
       if (sw[1]) halted = true;
+      edges += live_seen[i];
+      rounds += (double)live_seen[i] * (sw[3] - round_seen[i]);
+      round_seen[i] = sw[3];
       if (!sw[0]) {
         live_seen[i] = sw[2];
         continue;
       }
       Request& r = reqs[ri];
       r.state = 2;
-      r.result = sw[0] == 2 ? HO_ERR_BAD_CSR : HO_OK;
+      r.result = sw[0] == 2 ? HO_ERR_BAD_CSR : sw[0] == 3 ? HO_ERR_INTERNAL : HO_OK;
       if (sw[0] == 1) launch_outputs(slot_dev[i], s);
       // park the slot before its memory can be handed to another request:
       // replays already in flight still read the old, finished control block
@@ -929,23 +1037,8 @@ class Engine {
       pool.release(r.off, r.plan.total);
       slot_req[i] = -1;
     }
+    *progress = edges > 0 ? rounds / edges : 0;
     return halted;
-  }
-
-  // Compact the adjacency rows of running slots whose live edge count halved
-  // since the last compaction (enqueued after the launches in flight, so it
-  // runs at a round boundary; the kernels do nothing for a slot that has
-  // finished or halted meanwhile).
-  hoStatus maybe_compact() {
-    for (uint32_t i = 0; i < S; ++i) {
-      if (slot_req[i] < 0 || live_seen[i] == 0) continue;
-      if (!compact_each[i] && live_seen[i] > compact_at[i]) continue;
-      launch_compact(slot_dev[i], s);
-      compact_at[i] = compact_next(live_seen[i]);
-      live_seen[i] = 0;
-    }
-    HIPCHK(hipGetLastError());
-    return HO_OK;
   }
 
   // Finish the current round of every halted slot from the host.
@@ -958,7 +1051,7 @@ class Engine {
       HOCHK(read_ctl(slot_dev[i], &c, s));
       if (!c.halt) continue;
       if (c.halt_step < 2 || c.halt_step > slot_dev[i].h + 1) return HO_ERR_INTERNAL;
-      HOCHK(steps_host(slot_dev[i], g, s, c.halt_step, true, tm));
+      HOCHK(steps_host(slot_dev[i], g, s, c.halt_step, true, tm, ROUND_CLOSED));
       HOCHK(read_ctl(slot_dev[i], &c, s));
       if (c.halt) return HO_ERR_INTERNAL;  // the round must have ended
     }
@@ -990,22 +1083,42 @@ class Engine {
     std::fflush(stderr);
   }
 
+  // The graph of the next launch: short ones right after a halt (overflowing
+  // rounds tend to come in runs, and every round after a halt in the same graph
+  // is skipped), first (the decomposition may be over soon) and on trial.
+  int next_graph(bool halted) {
+    if (halted || steps == 0) return GR_ONE;
+    if (S == 1 && hmax == 1) return steps < 4 ? GR_FEW : steps < 10 ? GR_MANY : GR_LONG;
+    if (pace.pick()) {
+      if (pace.left < 16) return GR_CHIP;
+      pace.left -= 3;
+      return GR_CHIPS;
+    }
+    if (S == 1) return pace.trial || steps < 4 ? GR_FEW : GR_MANY;
+    if (pace.trial || steps < 3) return GR_ONE;
+    return !pace.few ? GR_LONG : steps < 6 || !queue.empty() ? GR_FEW : GR_MANY;
+  }
+
   hoStatus run(uint64_t max_launches = UINT64_MAX) {
     HOCHK(admit());
     if (!busy()) return HO_OK;
-    HOCHK(ensure_graphs());
-    auto last_report = std::chrono::steady_clock::now();
+    using clock = std::chrono::steady_clock;
+    auto last_report = clock::now(), seen = last_report;
     uint64_t launched = 0;
     uint64_t buf_at[2] = {0, 0};
+    int buf_graph[2] = {0, 0};
+    clock::time_point buf_time[2];
     int head = 0, inflight = 0;
     int calm = 2;  // graph launches since the last halt (saturating)
     while (true) {
-      while (inflight < 2 && busy() && launched < max_launches) {
+      // the first launch of a single decomposition may well finish it
+      const int ahead = S == 1 && hmax > 1 && steps <= 1 ? 1 : 2;
+      while (inflight < ahead && busy() && launched < max_launches) {
         const int buf = (head + inflight) & 1;
-        // short graphs right after a halt (overflowing rounds tend to come in
-        // runs, and every round after a halt in the same graph is skipped)
-        const int which = calm < 2 ? 0
-                          : plain ? (steps == 0 ? 0 : steps < 4 ? 1 : 2) : (queue.empty() ? 2 : 1);
+        const int which = next_graph(calm < 2);
+        HOCHK(ensure_graph(which));
+        buf_graph[buf] = which;
+        buf_time[buf] = clock::now();
         HIPCHK(hipGraphLaunch(exec[which], s));
         HIPCHK(hipMemcpyAsync(hstat + HO_STATUS_WORDS * S * buf, status_d,
                               4ull * HO_STATUS_WORDS * S, hipMemcpyDeviceToHost, s));
@@ -1016,8 +1129,14 @@ class Engine {
       }
       if (inflight == 0) break;
       HIPCHK(hipEventSynchronize(ev[head]));
-      const bool halted = retire(hstat + HO_STATUS_WORDS * S * head, buf_at[head]);
+      const auto now = clock::now();
+      double progress;
+      const bool halted = retire(hstat + HO_STATUS_WORDS * S * head, buf_at[head], &progress);
       if (copy_failed) return HO_ERR_HIP;
+      const GraphShape gs = graph_shape(buf_graph[head]);
+      pace.saw(gs.chip, progress < gs.steps * (S == 1 ? 16 : gs.rounds > 32 ? 128 : 29), progress,
+               std::chrono::duration<double, std::micro>(now - std::max(seen, buf_time[head])).count());
+      seen = now;
       head ^= 1;
       --inflight;
       if (halted) {
@@ -1031,7 +1150,6 @@ class Engine {
       }
       HOCHK(admit());
       report_progress(last_report);
-      HOCHK(maybe_compact());
     }
     HIPCHK(hipStreamSynchronize(s));
     return HO_OK;
@@ -1039,8 +1157,9 @@ class Engine {
 };
 
 // Debug / stats form of the plain path: every round driven from the host.
+// team: the team kernel runs every round it can take.
 hoStatus run_rounds_host(const Dev& d, const RoundGrid& g, hipStream_t s, bool timed, double* kms,
-                         uint64_t* klaunch) {
+                         uint64_t* klaunch, bool team = false) {
   const unsigned T = 256;
   const Dev* dp = d.self;
   StepTimer tm;
@@ -1072,7 +1191,13 @@ hoStatus run_rounds_host(const Dev& d, const RoundGrid& g, hipStream_t s, bool t
     }
   }
   while (st == HO_OK && !c.done) {
-    if (c.live <= compact_at || (d.serial & HO_FLAG_COMPACT_EACH)) {
+    if (team) {
+      // (the support step, which frees the team's meeting point, may be skipped)
+      hipLaunchKernelGGL(k_team_reset, dim3(1), dim3(256), 0, s, dp);
+      launch_team(dp, 1, nullptr, team_limits(1, 4096), s);
+      if ((st = read_ctl(d, &c, s)) != HO_OK || c.done) break;
+      if (c.phase == ROUND_CLOSED) continue;
+    } else if (c.live <= compact_at || (d.serial & HO_FLAG_COMPACT_EACH)) {
       launch_compact(d, s);
       compact_at = compact_next(c.live);
     }
@@ -1080,11 +1205,11 @@ hoStatus run_rounds_host(const Dev& d, const RoundGrid& g, hipStream_t s, bool t
     for (int i = 0; i < KT_N; ++i) kms0[i] = timed ? kms[i] : 0.0;
     const Ctl before = c;
     if ((st = tm.begin(s)) != HO_OK) break;
-    hipLaunchKernelGGL(k_mark, dim3(g.mark), dim3(T), 0, s, dp);
+    if (!c.phase) hipLaunchKernelGGL(k_mark, dim3(g.mark), dim3(T), 0, s, dp);
     if ((st = tm.end(s, KT_MARK)) != HO_OK) break;
     Ctl mid;
     if (rlog && (st = read_ctl(d, &mid, s)) != HO_OK) break;
-    st = steps_host(d, g, s, 2, false, tm);
+    st = steps_host(d, g, s, std::max(2u, c.phase), false, tm, team ? -1 : 0);
     if (st == HO_OK) st = read_ctl(d, &c, s);
     if (rlog && st == HO_OK) {
       std::fprintf(rlog, "%u %u %u %u %u %u %llu", mid.r, mid.k, mid.jump, mid.nRc.v, mid.cnt[2][mid.r & 1].nit,
@@ -1108,7 +1233,10 @@ hoStatus run_rounds_host(const Dev& d, const RoundGrid& g, hipStream_t s, bool t
 // code the array's name is not a device address: the address comes from
 // hipGetSymbolAddress, taken once per device (scratch_base), and only that
 // address is used.
-constexpr size_t SCRATCH_BYTES = 256ull << 20;
+// 256 MiB, of which the slot's own state took 2 KiB when that limit was set: its
+// growth since then is added, so that the graphs that fit are the same ones.
+constexpr size_t SCRATCH_BYTES = (256ull << 20) - 2048 + up(sizeof(Dev)) +
+                                 up(4ull * HO_STATUS_WORDS) + up(sizeof(Team)) + up(sizeof(Ctl));
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 
 constexpr int SCRATCH_MAX_DEVICES = 64;
@@ -1131,7 +1259,7 @@ void* scratch_base(int dev) {
 // Bytes of scratch a decomposition of (n, m, h) takes (0: invalid arguments).
 size_t noalloc_bytes(uint32_t n, uint64_t m, uint32_t h, Plan* p) {
   if (!make_plan(n, m, h, nullptr, true, p, 16, false)) return 0;
-  return up(sizeof(Dev)) + up(4ull * HO_STATUS_WORDS) + p->total;
+  return up(sizeof(Dev)) + up(4ull * HO_STATUS_WORDS) + up(sizeof(Team)) + p->total;
 }
 
 hoStatus check_common(const uint32_t* rp, const uint32_t* ci, uint32_t n, uint64_t m, uint32_t h,
@@ -1272,6 +1400,7 @@ hoStatus hoTrussDecompose(const uint32_t* row_ptr, const uint32_t* col_idx, uint
   }
   HIPCHK(hipEventRecord(ev0.e, stream));
   if (host_loop) {
+    eng.host_rounds = true;
     HOCHK(eng.admit(es0.e, es1.e));
     Dev d = eng.slot_dev[0];
     Ctl c;
@@ -1305,7 +1434,7 @@ hoStatus hoTrussDecompose(const uint32_t* row_ptr, const uint32_t* col_idx, uint
   Ctl c;
   HOCHK(read_ctl(eng.slot_dev[0], &c, stream));
   if (c.err) return HO_ERR_BAD_CSR;
-  if (!c.done) return HO_ERR_INTERNAL;
+  if (!c.done || c.failed) return HO_ERR_INTERNAL;
   out.rounds = c.r;
   out.levels = c.levels;
   out.events = c.events;
@@ -1345,11 +1474,13 @@ hoStatus hoTrussDecomposeNoAlloc(const uint32_t* row_ptr, const uint32_t* col_id
   const uintptr_t b = (uintptr_t)base;
   Dev* dself = (Dev*)b;
   uint32_t* status = (uint32_t*)(b + up(sizeof(Dev)));
-  Dev d = carve(p, (void*)(b + up(sizeof(Dev)) + up(4ull * HO_STATUS_WORDS)), row_ptr, col_idx,
-                out_trussness, out_round);
+  Team* team = (Team*)((uintptr_t)status + up(4ull * HO_STATUS_WORDS));
+  Dev d = carve(p, (void*)((uintptr_t)team + up(sizeof(Team))), row_ptr, col_idx, out_trussness,
+                out_round);
   const RoundGrid g = plain_grid(m, nullptr);
   d.self = dself;
   d.status = status;
+  d.team = team;
   d.nminpart = g.jump;
   // the array keeps the previous call's contents: every buffer that must
   // start at a known value is written before it is read
@@ -1360,17 +1491,17 @@ hoStatus hoTrussDecomposeNoAlloc(const uint32_t* row_ptr, const uint32_t* col_id
   // runtime, so the copy is complete when the call returns)
   HIPCHK(hipMemcpyAsync(dself, &d, sizeof(Dev), hipMemcpyHostToDevice, stream));
   hipLaunchKernelGGL(k_post_init, dim3(1), dim3(64), 0, stream, d);
-  hipLaunchKernelGGL(k_first_min, dim3(g.jump), dim3(T), 0, stream, dself);
+  if (h == 1) hipLaunchKernelGGL(k_first_min, dim3(g.jump), dim3(T), 0, stream, dself);
   HIPCHK(hipGetLastError());
   Ctl c;
   HOCHK(read_ctl(d, &c, stream));
   if (c.err) return HO_ERR_BAD_CSR;
   hoStats out{};
-  HOCHK(run_rounds_host(d, g, stream, false, out.kernel_ms, out.kernel_launches));
+  HOCHK(run_rounds_host(d, g, stream, false, out.kernel_ms, out.kernel_launches, h > 1));
   launch_outputs(d, stream);
   HOCHK(read_ctl(d, &c, stream));
   if (c.err) return HO_ERR_BAD_CSR;
-  if (!c.done) return HO_ERR_INTERNAL;
+  if (!c.done || c.failed) return HO_ERR_INTERNAL;
   out.rounds = c.r;
   out.levels = c.levels;
   out.events = c.events;

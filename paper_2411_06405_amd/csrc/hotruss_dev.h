@@ -70,6 +70,9 @@ struct Ctl {
   uint32_t nlong;    // renumbered graphs: rows of 64 slots or more (they come first)
   uint32_t k;        // current level: edges with sup <= k-2 are peeled
   uint32_t r;        // index of the current peel round
+  uint32_t phase;    // first step of this round that the round kernels run: 0 mark, j level
+                     // j, h+1 support; ROUND_CLOSED: none, the round has not begun
+  uint32_t compact_at;  // compact the adjacency rows once live falls to this
   uint32_t live;     // edges still in S
   uint32_t levels;   // levels visited
   uint32_t done;     // decomposition finished (read by the host with halt)
@@ -82,6 +85,7 @@ struct Ctl {
   LineCounter nRc;       // |R_r|, edges peeled in the current round
   LineCounter nPushc[2];          // edges whose support crossed k-2 in a round of this parity
   uint32_t compactions;  // adjacency compactions done (statistics)
+  uint32_t failed;       // a wait of the team kernel ran out: the decomposition is abandoned
   uint32_t recovering;   // the host is re-running an overflowed step in windows
   // stats mode: method-level work count (support evaluations and bytes of the
   // re-evaluating peeling method on the same round schedule)
@@ -95,6 +99,22 @@ struct Ctl {
   // stats mode: work counters, level kernel [0..5), support kernel [5..8)
   uint64_t stat[NSTAT];
 };
+
+constexpr uint32_t ROUND_CLOSED = 0xffu;
+
+// Where the workgroups of one slot's team (see k_team) meet.  Zeroed between
+// launches of the team kernel.
+constexpr uint32_t TEAM_MAX = 64;
+struct alignas(128) Team {
+  uint32_t xcc;     // 1 + the XCD of the team (0: unclaimed)
+  uint32_t joined;  // members so far; from TEAM_CLOSED on, too late
+  uint32_t size;    // members, once closed
+  uint32_t pad[29];
+  uint32_t flag[TEAM_MAX];  // per member: the last barrier it reached
+  uint32_t smin[TEAM_MAX];  // per member: level-jump minimum of its edges ...
+  uint32_t scnt[TEAM_MAX];  // ... and how many of them have it
+};
+constexpr uint32_t TEAM_CLOSED = 1u << 16;
 
 // Everything a kernel needs, passed by value.
 struct Dev {
@@ -148,6 +168,7 @@ struct Dev {
   uint64_t* evl[HMAX + 1][2];  // event lists (x<<32|w) per level and parity
   Item* itl[HMAX + 2];     // work items per level; index h+1: support items
   Ctl* ctl;
+  struct Team* team;    // the team kernel's meeting point for this slot
   Dev* self;               // device-resident copy of this struct (round kernels read it)
   uint32_t* spart;         // stats mode: per-workgroup counters [NSTAT][STAT_GRID], else null
   uint32_t* status;        // this slot's {done, halt, live, -} words in the engine's status
@@ -165,6 +186,46 @@ struct Dev {
 // Compact again once a tenth of the live edges have been peeled since the
 // last compaction (a compaction reads and writes the active slots once).
 __host__ __device__ inline uint32_t compact_next(uint32_t live) { return live - live / 10; }
+
+// Load of a word that another workgroup of the same launch may have written
+// (TEAM): a relaxed device-scope load is served by the L2 that the team's
+// workgroups share, never by this CU's own L1, which nothing keeps current.
+template <bool TEAM, class T>
+__device__ __forceinline__ T ld(const T* p) {
+  if constexpr (TEAM) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else return *p;
+}
+
+template <bool TEAM>
+__device__ __forceinline__ Item ld_item(const Item* p) {
+  if constexpr (TEAM) {
+    const uint64_t* q = reinterpret_cast<const uint64_t*>(p);
+    const uint64_t a = ld<true>(q), b = ld<true>(q + 1);
+    return Item{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
+  } else {
+    return *p;
+  }
+}
+
+// Atomics on words shared by the workgroups of a launch.  Device-scope ones go
+// to memory, past every L2.  A team's workgroups share one L2, where atomics of
+// workgroup scope are done: the same result for them, and the words stay there.
+template <bool TEAM, class T>
+__device__ __forceinline__ T at_add(T* p, T v) {
+  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, TEAM ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+}
+template <bool TEAM, class T>
+__device__ __forceinline__ T at_sub(T* p, T v) {
+  return __hip_atomic_fetch_sub(p, v, __ATOMIC_RELAXED, TEAM ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+}
+template <bool TEAM, class T>
+__device__ __forceinline__ T at_and(T* p, T v) {
+  return __hip_atomic_fetch_and(p, v, __ATOMIC_RELAXED, TEAM ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+}
+template <bool TEAM, class T>
+__device__ __forceinline__ T at_or(T* p, T v) {
+  return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, TEAM ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Workgroups are dealt to the eight XCDs in turn; this numbering gives each XCD
 // consecutive numbers, so that neighbouring work items share an L2.
@@ -237,11 +298,12 @@ __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t* total) 
 
 // Wave-aggregated reservation of `cnt` slots of a counter (all lanes call).
 // Returns this lane's first slot.
+template <bool TEAM>
 __device__ __forceinline__ uint32_t wave_reserve(uint32_t* counter, uint32_t cnt) {
   uint32_t total;
   const uint32_t off = wave_excl_scan(cnt, &total);
   uint32_t base = 0;
-  if (lane_id() == 0 && total) base = atomicAdd(counter, total);
+  if (lane_id() == 0 && total) base = at_add<TEAM>(counter, total);
   base = __shfl(base, 0, WAVE);
   return base + off;
 }

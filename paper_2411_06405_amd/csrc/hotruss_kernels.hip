@@ -47,6 +47,8 @@ __global__ void k_init_ctl(Ctl* ctl, uint32_t n, uint32_t words, uint32_t m) {
     ctl->k = 2;
     ctl->jump = 1;  // nothing pushed yet: the first round jumps to min sup + 2
     ctl->live = m;
+    ctl->phase = ROUND_CLOSED;
+    ctl->compact_at = compact_next(m);
     ctl->levels = 0;
     ctl->done = (m == 0);
   }
@@ -482,9 +484,12 @@ __global__ void __launch_bounds__(256) k_support_init(Dev d, uint32_t* __restric
 }
 
 // ============================================================ peel rounds
-// A round runs as a fixed kernel sequence (captured once into a HIP graph and
-// replayed): k_mark, k_level(j) for j = 2..h, k_support, k_end.  Every kernel reads the control block and returns at once when
-// the decomposition is finished, so a graph may run past the last round.
+// A round of the whole chip is a fixed kernel sequence (captured into a HIP
+// graph and replayed): k_mark, k_level(j) for j = 2..h, k_support, k_end.  Small
+// rounds are run by the team kernel instead, with the same step functions; a
+// round that it began goes on at the step that Ctl::phase names.  Every kernel
+// reads the control block and returns at once when there is nothing for it to
+// do, so a graph may run past the last round.
 
 struct RoundCtx {
   uint32_t r, k, p;
@@ -507,20 +512,28 @@ enum { ITEM_ROW = 0, ITEM_SLOTS = 1, ITEM_WORDS = 2 };
 
 __device__ __forceinline__ uint32_t chunks_of(uint32_t nv) { return (nv + CHUNK - 1) / CHUNK; }
 
-// Item number `chunk` of a group.
+// Ball words per item: a word can hold 64 candidates, so on small graphs 64
+// words would leave a round's few rows to a few waves (Chung-Lu 5,001 h = 3: the
+// slowest workgroup took 24 us over its items, the others 2); the rows of
+// larger graphs make enough items of 64.
+__device__ __forceinline__ uint32_t word_chunk(uint32_t words) { return words <= 512 ? 8 : CHUNK; }
+
+// Item number `chunk` of a group (nv entries, `size` an item).
 template <int MODE>
 __device__ __forceinline__ Item make_item(uint32_t kind, uint32_t extra, uint32_t x, uint32_t y,
-                                          uint32_t base, uint32_t nv, uint32_t chunk) {
-  const uint32_t vs = chunk * CHUNK, len = min(CHUNK, nv - vs);
+                                          uint32_t base, uint32_t nv, uint32_t chunk,
+                                          uint32_t size = CHUNK) {
+  const uint32_t vs = chunk * size, len = min(size, nv - vs);
   if (MODE == ITEM_ROW) return Item{x, y, base, item_meta(kind, extra, len, vs)};
   if (MODE == ITEM_SLOTS) return Item{x, y, base + vs, item_meta(0, 0, len, 0)};
   return Item{x, y, vs, item_meta(KIND_A_WORDS, 0, len, 0)};
 }
 
 // Lane 0 reserves `total` entries of a counter for the whole wave.
+template <bool TEAM>
 __device__ __forceinline__ uint32_t reserve_wave(uint32_t* counter, uint32_t total) {
   uint32_t b = 0;
-  if (lane_id() == 0 && total) b = atomicAdd(counter, total);
+  if (lane_id() == 0 && total) b = at_add<TEAM>(counter, total);
   return __shfl(b, 0, WAVE);
 }
 
@@ -531,10 +544,11 @@ template <int MODE>
 __device__ void emit_items_wave(const Dev& d, uint32_t p, uint32_t list, uint32_t first, uint32_t total,
                                 uint32_t excl, uint32_t cnt, uint32_t kind, uint32_t extra,
                                 uint32_t x, uint32_t y, uint32_t base, uint32_t nv) {
+  const uint32_t size = MODE == ITEM_WORDS ? word_chunk(d.ctl->words) : CHUNK;
   if (!__ballot(cnt > 1)) {
     // at most one item per lane (most rows fit one chunk): no owner to look up
     const uint32_t idx = first + excl;
-    if (cnt && idx < d.itcap) d.itl[list][idx] = make_item<MODE>(kind, extra, x, y, base, nv, 0);
+    if (cnt && idx < d.itcap) d.itl[list][idx] = make_item<MODE>(kind, extra, x, y, base, nv, 0, size);
     if (__ballot(cnt && idx >= d.itcap)) d.ctl->cnt[list][p].iovf = 1;
     return;
   }
@@ -555,7 +569,7 @@ __device__ void emit_items_wave(const Dev& d, uint32_t p, uint32_t list, uint32_
     if (t < total) {
       const uint32_t idx = first + t;
       if (idx < d.itcap)
-        d.itl[list][idx] = make_item<MODE>(kind, extra, ox, oy, ob, onv, t - oex);
+        d.itl[list][idx] = make_item<MODE>(kind, extra, ox, oy, ob, onv, t - oex, size);
       else over = true;
     }
   }
@@ -563,30 +577,33 @@ __device__ void emit_items_wave(const Dev& d, uint32_t p, uint32_t list, uint32_
 }
 
 // One group per lane with its own reservation.
-template <int MODE>
+template <int MODE, bool TEAM>
 __device__ void emit_group(const Dev& d, uint32_t p, uint32_t list, uint32_t kind, uint32_t extra,
                            uint32_t x, uint32_t y, uint32_t base, uint32_t nv) {
-  const uint32_t cnt = chunks_of(nv);
+  const uint32_t size = MODE == ITEM_WORDS ? word_chunk(d.ctl->words) : CHUNK;
+  const uint32_t cnt = (nv + size - 1) / size;
   uint32_t total;
   const uint32_t excl = wave_excl_scan(cnt, &total);
   if (!total) return;
-  const uint32_t first = reserve_wave(&d.ctl->cnt[list][p].nit, total);
+  const uint32_t first = reserve_wave<TEAM>(&d.ctl->cnt[list][p].nit, total);
   emit_items_wave<MODE>(d, p, list, first, total, excl, cnt, kind, extra, x, y, base, nv);
 }
 
 // Support items of event (a -> w): the live edges (a,b), CHUNK slots per item.
+template <bool TEAM>
 __device__ void emit_support_items(const Dev& d, uint32_t p, bool active, uint32_t a, uint32_t w) {
   uint32_t base = 0, deg = 0;
   if (active) {
     base = d.rp[a];
     deg = row_end(d, a) - base;
   }
-  emit_group<ITEM_SLOTS>(d, p, d.h + 1, 0, 0, a, w, base, deg);
+  emit_group<ITEM_SLOTS, TEAM>(d, p, d.h + 1, 0, 0, a, w, base, deg);
 }
 
 // Items over z's old (j-1)-ball words for candidates (x, w), j >= 3.
+template <bool TEAM>
 __device__ void emit_word_items(const Dev& d, uint32_t p, uint32_t j, bool active, uint32_t x, uint32_t z) {
-  emit_group<ITEM_WORDS>(d, p, j, 0, 0, x, z, 0, active ? d.ctl->words : 0u);
+  emit_group<ITEM_WORDS, TEAM>(d, p, j, 0, 0, x, z, 0, active ? d.ctl->words : 0u);
 }
 
 // ---- level-jump minimum ----------------------------------------------------
@@ -615,10 +632,12 @@ __device__ void jump_partials(const Dev& d) {
     d.minpart[blockIdx.x] = min(min(smin[0], smin[1]), min(smin[2], smin[3]));
 }
 
-// After the initial pass: the first round starts with a level jump.
+// After the initial pass: the first round starts with a level jump
+// (host-driven rounds; the team kernel finds its own minimum).
 __global__ void __launch_bounds__(256) k_first_min(const Dev* __restrict__ devs) {
   const Dev& d = devs[blockIdx.y];
   if (d.ctl->done || d.ctl->err) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) d.ctl->phase = 0;
   jump_partials(d);
 }
 
@@ -674,14 +693,15 @@ __device__ __forceinline__ Run word_runs(uint32_t W, uint32_t row_, uint32_t col
 // only, should two hold the same pair).  All lanes of the wave call it; the
 // atomics of both directions are in flight together.  merge: by runs, for
 // renumbered graphs.
+template <bool TEAM>
 __device__ __forceinline__ void clear_pairs(uint64_t* __restrict__ L, uint64_t* __restrict__ D,
                                             uint32_t W, uint32_t x, uint32_t w, bool drop,
                                             bool merge, bool* xw, bool* wx) {
   auto clear = [&](size_t o, uint64_t bits) -> uint64_t {
-    return atomicAnd(reinterpret_cast<unsigned long long*>(L + o), ~(unsigned long long)bits) & bits;
+    return at_and<TEAM>(L + o, ~bits) & bits;
   };
   auto mark = [&](size_t o, uint64_t bits) {
-    if (bits) atomicOr(reinterpret_cast<unsigned long long*>(D + o), (unsigned long long)bits);
+    if (bits) at_or<TEAM>(D + o, bits);
   };
   if (!merge) {
     uint64_t oa = 0, ob = 0;
@@ -716,12 +736,13 @@ __device__ __forceinline__ void clear_pairs(uint64_t* __restrict__ L, uint64_t* 
 // The same for peeled edges {x, w} and level 1, where every edge is listed once
 // and nothing depends on what the atomics return (a marking kernel that waits
 // for them takes 2.6 times as long in the largest rounds).  D: only at h = 1.
+template <bool TEAM>
 __device__ __forceinline__ void clear_edges(uint64_t* __restrict__ L, uint64_t* __restrict__ D,
                                             uint32_t W, uint32_t x, uint32_t w, bool valid,
                                             bool merge) {
   auto clear = [&](size_t o, uint64_t bits) {
-    atomicAnd(reinterpret_cast<unsigned long long*>(L + o), ~(unsigned long long)bits);
-    if (D) atomicOr(reinterpret_cast<unsigned long long*>(D + o), (unsigned long long)bits);
+    at_and<TEAM>(L + o, ~bits);
+    if (D) at_or<TEAM>(D + o, bits);
   };
   if (merge) {
     const Run A = word_runs(W, x, w, valid), B = word_runs(W, w, x, valid);
@@ -734,6 +755,7 @@ __device__ __forceinline__ void clear_edges(uint64_t* __restrict__ L, uint64_t* 
 }
 
 // ---- K2: peel R (level jump: collect it first), level-1 events, items ----
+template <bool TEAM>
 __device__ void mark_edge(const Dev& d, const RoundCtx& rc, bool valid, uint32_t e, uint32_t i) {
   uint32_t a = 0, b = 0;
   if (valid) {
@@ -750,10 +772,10 @@ __device__ void mark_edge(const Dev& d, const RoundCtx& rc, bool valid, uint32_t
     d.evl[1][rc.p][2 * i] = ((uint64_t)a << 32) | b;
     d.evl[1][rc.p][2 * i + 1] = ((uint64_t)b << 32) | a;
   }
-  clear_edges(d.L[1], d.h == 1 ? d.Dm[1] : nullptr, d.W, a, b, valid, d.perm != nullptr);
+  clear_edges<TEAM>(d.L[1], d.h == 1 ? d.Dm[1] : nullptr, d.W, a, b, valid, d.perm != nullptr);
   if (d.h == 1) {
-    emit_support_items(d, rc.p, valid, a, b);
-    emit_support_items(d, rc.p, valid, b, a);
+    emit_support_items<TEAM>(d, rc.p, valid, a, b);
+    emit_support_items<TEAM>(d, rc.p, valid, b, a);
     return;
   }
   // level 2: a lost neighbour b (candidates (a, y), y in b's old neighbourhood,
@@ -775,15 +797,15 @@ __device__ void mark_edge(const Dev& d, const RoundCtx& rc, bool valid, uint32_t
   uint32_t t0, t1, t2, t3;
   const uint32_t e0 = wave_excl_scan(n0, &t0), e1 = wave_excl_scan(n1, &t1);
   const uint32_t e2 = wave_excl_scan(n2, &t2), e3 = wave_excl_scan(n3, &t3);
-  const uint32_t first = reserve_wave(&d.ctl->cnt[2][rc.p].nit, t0 + t1 + t2 + t3);
+  const uint32_t first = reserve_wave<TEAM>(&d.ctl->cnt[2][rc.p].nit, t0 + t1 + t2 + t3);
   emit_items_wave<ITEM_ROW>(d, rc.p, 2, first, t0, e0, n0, KIND_A_SLOTS, 1, a, b, bb, v0);
   emit_items_wave<ITEM_ROW>(d, rc.p, 2, first + t0, t1, e1, n1, KIND_A_SLOTS, 1, b, a, ba, v1);
   emit_items_wave<ITEM_ROW>(d, rc.p, 2, first + t0 + t1, t2, e2, n2, KIND_B_SLOTS, 0, a, b, ba, v2);
   emit_items_wave<ITEM_ROW>(d, rc.p, 2, first + t0 + t1 + t2, t3, e3, n3, KIND_B_SLOTS, 0, b, a, bb,
                             v3);
   for (uint32_t j = 3; j <= d.h; ++j) {
-    emit_word_items(d, rc.p, j, valid, a, b);
-    emit_word_items(d, rc.p, j, valid, b, a);
+    emit_word_items<TEAM>(d, rc.p, j, valid, a, b);
+    emit_word_items<TEAM>(d, rc.p, j, valid, b, a);
   }
 }
 
@@ -791,6 +813,7 @@ __device__ void mark_edge(const Dev& d, const RoundCtx& rc, bool valid, uint32_t
 // another's row, and the items need no owner search -- lane t writes item t.
 // Small rounds are bound by this chain of dependent loads and atomics, not by
 // bytes.
+template <bool TEAM>
 __device__ void mark_edge_wave(const Dev& d, const RoundCtx& rc, uint32_t e, uint32_t i) {
   const uint32_t lane = lane_id();
   const uint32_t a = d.eu[e], b = d.ev[e], q1 = d.s1[e], q2 = d.s2[e];
@@ -803,11 +826,11 @@ __device__ void mark_edge_wave(const Dev& d, const RoundCtx& rc, uint32_t e, uin
     d.srem[q2] = rc.r;
     d.ce[q1] = slot_word(e, b, true);
     d.ce[q2] = slot_word(e, a, true);
-    atomicAnd(&row(d.L[1], d.W, a)[b >> 6], ~(1ull << (b & 63)));
-    atomicAnd(&row(d.L[1], d.W, b)[a >> 6], ~(1ull << (a & 63)));
+    at_and<TEAM>(&row(d.L[1], d.W, a)[b >> 6], ~((uint64_t)1 << (b & 63)));
+    at_and<TEAM>(&row(d.L[1], d.W, b)[a >> 6], ~((uint64_t)1 << (a & 63)));
     if (d.h == 1) {
-      atomicOr(&row(d.Dm[1], d.W, a)[b >> 6], 1ull << (b & 63));
-      atomicOr(&row(d.Dm[1], d.W, b)[a >> 6], 1ull << (a & 63));
+      at_or<TEAM>(&row(d.Dm[1], d.W, a)[b >> 6], (uint64_t)1 << (b & 63));
+      at_or<TEAM>(&row(d.Dm[1], d.W, b)[a >> 6], (uint64_t)1 << (a & 63));
     }
     d.evl[1][rc.p][2 * i] = ((uint64_t)a << 32) | b;
     d.evl[1][rc.p][2 * i + 1] = ((uint64_t)b << 32) | a;
@@ -817,10 +840,11 @@ __device__ void mark_edge_wave(const Dev& d, const RoundCtx& rc, uint32_t e, uin
   const uint32_t v0 = d.h == 1 ? da : db + 1, v1 = d.h == 1 ? db : da + 1;
   const uint32_t n0 = chunks_of(v0), n1 = chunks_of(v1);
   const uint32_t n2 = d.h == 1 ? 0 : chunks_of(da), n3 = d.h == 1 ? 0 : chunks_of(db);
-  const uint32_t words = d.ctl->words, nw = chunks_of(words), rows = n0 + n1 + n2 + n3;
+  const uint32_t words = d.ctl->words, wc = word_chunk(words), nw = (words + wc - 1) / wc;
+  const uint32_t rows = n0 + n1 + n2 + n3;
   uint32_t base = 0;
   if (lane == 0 || lane + 2 <= d.h)  // lane l reserves the items of list l + 2
-    base = atomicAdd(&d.ctl->cnt[lane + 2][rc.p].nit, lane == 0 ? rows : 2 * nw);
+    base = at_add<TEAM>(&d.ctl->cnt[lane + 2][rc.p].nit, lane == 0 ? rows : 2 * nw);
   const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)base, 0);
   bool over = false;
   for (uint32_t t = lane; t < rows; t += WAVE) {
@@ -840,8 +864,8 @@ __device__ void mark_edge_wave(const Dev& d, const RoundCtx& rc, uint32_t e, uin
     const uint32_t at = __shfl(base, j - 2, WAVE);
     over = false;
     for (uint32_t t = lane; t < 2 * nw; t += WAVE) {
-      const Item it = t < nw ? make_item<ITEM_WORDS>(0, 0, a, b, 0, words, t)
-                             : make_item<ITEM_WORDS>(0, 0, b, a, 0, words, t - nw);
+      const Item it = t < nw ? make_item<ITEM_WORDS>(0, 0, a, b, 0, words, t, wc)
+                             : make_item<ITEM_WORDS>(0, 0, b, a, 0, words, t - nw, wc);
       if (at + t < d.itcap) d.itl[j][at + t] = it;
       else over = true;
     }
@@ -854,15 +878,16 @@ __device__ void mark_edge_wave(const Dev& d, const RoundCtx& rc, uint32_t e, uin
 // previous round (this round sets its own in the ball-change step, later), so
 // whole words are zeroed with plain stores; level 1 (h = 1 only) gets this
 // round's marks while this runs, so its old bits are cleared one by one.
+template <bool TEAM>
 __device__ void clear_marks(const Dev& d, uint32_t j, uint32_t q, uint32_t ne, uint32_t first,
                             uint32_t stride) {
   uint64_t* D = d.Dm[j];
   const uint64_t* E = d.evl[j][q];
   for (uint32_t i = first; i < ne; i += stride) {
-    const uint64_t xw = *(E + i);
+    const uint64_t xw = ld<TEAM>(E + i);
     const uint32_t x = (uint32_t)(xw >> 32), w = (uint32_t)xw;
     if (j >= 2) row(D, d.W, x)[w >> 6] = 0;
-    else atomicAnd(&row(D, d.W, x)[w >> 6], ~(1ull << (w & 63)));
+    else at_and<TEAM>(&row(D, d.W, x)[w >> 6], ~((uint64_t)1 << (w & 63)));
   }
 }
 
@@ -873,8 +898,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
 k_mark(const Dev* __restrict__ devs) {
   const Dev& d = devs[blockIdx.y];
   Ctl* c = d.ctl;
-  if (c->done || c->halt) return;
+  if (c->done || c->halt || c->phase != 0) return;
   RoundCtx rc = round_ctx(c);
+  if (blockIdx.x == 0 && threadIdx.x == 0) c->nPushc[rc.p].v = 0;
   const uint32_t q = rc.p ^ 1;
   const uint32_t lane = lane_id();
   const uint32_t wstride = gridDim.x * blockDim.x;
@@ -895,9 +921,9 @@ k_mark(const Dev* __restrict__ devs) {
       const uint32_t sv = e < d.m ? d.sup[e] : SUP_GONE;
       const bool take = sv != SUP_GONE && sv <= rc.k - 2;
       if (!__ballot(take)) continue;  // nothing to peel in these 64 edges
-      const uint32_t i = wave_reserve(&c->nRc.v, take ? 1u : 0u);
+      const uint32_t i = wave_reserve<false>(&c->nRc.v, take ? 1u : 0u);
       if (take) d.R[rc.p][i] = e;
-      mark_edge(d, rc, take, e, i);
+      mark_edge<false>(d, rc, take, e, i);
     }
   } else {
     const uint32_t nR = c->nRc.v;
@@ -906,12 +932,12 @@ k_mark(const Dev* __restrict__ devs) {
       // 64 lanes share the writing of its work items -- the rows of a hub
       // endpoint are hundreds of items
       const uint32_t i = wbase / WAVE;
-      if (i < nR) mark_edge_wave(d, rc, d.R[rc.p][i], i);
+      if (i < nR) mark_edge_wave<false>(d, rc, d.R[rc.p][i], i);
     } else {
       for (uint32_t base = wbase; base < nR; base += wstride) {
         const uint32_t i = base + lane;
         const bool valid = i < nR;
-        mark_edge(d, rc, valid, valid ? d.R[rc.p][i] : 0, i);
+        mark_edge<false>(d, rc, valid, valid ? d.R[rc.p][i] : 0, i);
       }
     }
   }
@@ -926,7 +952,7 @@ k_mark(const Dev* __restrict__ devs) {
   }
   for (uint32_t j = 1; j <= d.h; ++j)
     if (d.Dm[j] && !c->cnt[j][q].ovf)
-      clear_marks(d, j, q, c->cnt[j][q].nev, blockIdx.x * blockDim.x + threadIdx.x, wstride);
+      clear_marks<false>(d, j, q, c->cnt[j][q].nev, blockIdx.x * blockDim.x + threadIdx.x, wstride);
 }
 
 // ---- K3: ball-change events at level j >= 2 ----------------------------
@@ -1008,9 +1034,10 @@ struct LevelLds {
 // reserved by two lanes at once.  With the marking step's changes: Chung-Lu
 // 100k h = 2 287 -> 238 ms, R-MAT 16 h = 2 1,207 -> 1,003 ms, Chung-Lu 5,001
 // h = 3 288 -> 192 ms (there mostly the word-wise candidates) a decomposition.
-// wg of nwg workgroups call it together.
-template <uint32_t LV_THREADS, uint32_t LV_CAP>
-__device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t nit, uint32_t wg,
+// wg of nwg workgroups call it together; TEAM: inside the team kernel, where
+// other workgroups' writes of the same launch are read (see ld()).
+template <uint32_t LV_THREADS, uint32_t LV_CAP, bool TEAM>
+__device__ __forceinline__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t nit, uint32_t wg,
                            uint32_t nwg, LevelLds<LV_THREADS, LV_CAP>& s) {
   static_assert(LV_CAP >= 2 * LV_THREADS && LV_CAP % LV_THREADS == 0, "two emission steps fit");
   constexpr uint32_t LV_WAVES = LV_THREADS / WAVE;
@@ -1023,7 +1050,7 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
   // many CUs as it has items
   const uint32_t stride = nwg * LV_WAVES;
   uint32_t it = wave * nwg + wg;
-  const bool counting = d.spart != nullptr;
+  const bool counting = !TEAM && d.spart != nullptr;
   if (wg >= nit) return;  // whole workgroup idle
   const uint64_t* Lj = d.L[j];
   const uint64_t* Lp = d.L[j - 1];
@@ -1039,9 +1066,11 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
   uint32_t par = 0, pass = 0;
   uint32_t next = wg;  // wave 0's next item
   const bool merge = d.perm != nullptr;
-  uint64_t wd = 0;       // KIND_A_WORDS: this lane's remaining candidates
-  uint32_t wbase = 0;    // ... and its word's first vertex
-  bool inword = false;   // KIND_A_WORDS item in progress
+  // KIND_A_WORDS item in progress: this lane's word of candidates, their number
+  // up to this lane's, in all and so far taken
+  uint64_t wd = 0;
+  uint32_t wincl = 0, wtotal = 0, wdone = 0;
+  bool inword = false;
   uint32_t X = 0, Wv = 0;
   // Append this wave's candidates (X, Wv) to the buffer.  The witness probes
   // run over the endpoint with fewer active slots.  One LDS atomic per wave
@@ -1076,7 +1105,7 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
     bool it_taken = false;
     uint32_t cands = 0;
     if (it < nit) {
-      const Item I = items[it];
+      const Item I = ld_item<TEAM>(items + it);
       const uint32_t kind = meta_kind(I.meta), len = meta_len(I.meta);
       if (kind == KIND_A_WORDS) {
         // the candidates of a whole word at once: members of z's old
@@ -1087,30 +1116,52 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
           if (lane < len) {
             const size_t o = (size_t)I.y * d.W + I.base + lane;
             const size_t ox = (size_t)I.x * d.W + I.base + lane;
-            const uint64_t old = *(Lp + o) | *(d.Dm[j - 1] + o);
-            wd = old & *(Lj + ox) & ~*(Lp + ox);
+            const uint64_t old = ld<TEAM>(Lp + o) | ld<TEAM>(d.Dm[j - 1] + o);
+            wd = old & ld<TEAM>(Lj + ox) & ~ld<TEAM>(Lp + ox);
             if (counting) examined = (uint32_t)__popcll(old);
           }
-          wbase = (I.base + lane) * 64;
+          wincl = wave_incl_scan((uint32_t)__popcll(wd));
+          wtotal = wave_last(wincl);
+          wdone = 0;
           inword = true;
         }
-        const uint32_t bx = d.rp[I.x], dx = d.len[I.x];
-        X = I.x;
-        while (true) {
-          const uint32_t now = (uint32_t)__popcll(__ballot(wd != 0));
-          if (!now || cands + now > WAVE) break;
-          const bool have = wd != 0;
-          uint32_t bw = 0, dw = 0;
-          if (have) {
-            Wv = wbase + (uint32_t)__ffsll((unsigned long long)wd) - 1;
-            wd &= wd - 1;
-            bw = d.rp[Wv];
-            dw = d.len[Wv];
-          }
-          append(have, bx, dx, bw, dw);
-          cands += now;
+        // lane l takes candidate wdone + l: the word that holds it, and its bit
+        const uint32_t t = wdone + lane;
+        const bool have = t < wtotal;
+        uint32_t own = 0;
+#pragma unroll
+        for (uint32_t step = 32; step > 0; step >>= 1) {
+          const uint32_t v = (uint32_t)__shfl(wincl, (int)(own + step - 1), WAVE);
+          if (v <= t) own += step;
         }
-        if (!__ballot(wd != 0)) {
+        own = min(own, WAVE - 1u);
+        uint64_t word = ((uint64_t)(uint32_t)__shfl((uint32_t)(wd >> 32), own, WAVE) << 32) |
+                        (uint32_t)__shfl((uint32_t)wd, own, WAVE);
+        uint32_t nth = t - ((uint32_t)__shfl(wincl, own, WAVE) - (uint32_t)__popcll(word));
+        uint32_t bit = 0;
+#pragma unroll
+        for (uint32_t step = 32; step > 0; step >>= 1) {
+          const uint32_t below = (uint32_t)__popcll(word & ((1ull << step) - 1));
+          if (nth >= below) {
+            nth -= below;
+            word >>= step;
+            bit += step;
+          }
+        }
+        X = I.x;
+        uint32_t bx = 0, dx = 0, bw = 0, dw = 0;
+        if (have) {
+          Wv = (I.base + own) * 64 + bit;
+          bx = d.rp[X];
+          dx = d.len[X];
+          bw = d.rp[Wv];
+          dw = d.len[Wv];
+        }
+        append(have, bx, dx, bw, dw);
+        wdone += WAVE;
+        cands = wdone <= wtotal ? WAVE : wtotal - (wdone - WAVE);
+        if (wdone >= wtotal) {
+          if (wtotal == 0) cands = 0;
           inword = false;
           it += stride;
           it_taken = true;
@@ -1127,8 +1178,8 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
           } else {
             const uint32_t q = I.base + v - extra;
             // live after this round, or (KIND_A) peeled in it
-            const uint32_t sw = (uint32_t)*(d.ce + q), y2 = sw & ~SLOT_GONE;
-            if (!(sw & SLOT_GONE) || (kind == KIND_A_SLOTS && *(d.srem + q) == rc.r)) {
+            const uint32_t sw = (uint32_t)ld<TEAM>(d.ce + q), y2 = sw & ~SLOT_GONE;
+            if (!(sw & SLOT_GONE) || (kind == KIND_A_SLOTS && ld<TEAM>(d.srem + q) == rc.r)) {
               have = true;
               X = (kind == KIND_A_SLOTS) ? I.x : y2;
               Wv = (kind == KIND_A_SLOTS) ? y2 : I.y;
@@ -1148,7 +1199,7 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
           const uint32_t at = kind == KIND_A_SLOTS ? Wv : X;
           const size_t o = (size_t)(kind == KIND_A_SLOTS ? X : Wv) * d.W + (at >> 6);
           const uint64_t sh = at & 63;
-          const uint64_t wj = *(Lj + o), wp = *(Lp + o);
+          const uint64_t wj = ld<TEAM>(Lj + o), wp = ld<TEAM>(Lp + o);
           bx = d.rp[X];
           dx = d.len[X];
           bw = d.rp[Wv];
@@ -1217,11 +1268,11 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
         }
 #pragma unroll
         for (uint32_t u = 0; u < PU; ++u)
-          y[u] = act[u] ? (uint32_t)*(d.ce + q[u]) : SLOT_GONE;
+          y[u] = act[u] ? (uint32_t)ld<TEAM>(d.ce + q[u]) : SLOT_GONE;
 #pragma unroll
         for (uint32_t u = 0; u < PU; ++u)
           if (!(y[u] & SLOT_GONE)) {
-            const uint64_t word = *(row(Lp, d.W, cb[own[u]]) + (y[u] >> 6));
+            const uint64_t word = ld<TEAM>(row(Lp, d.W, cb[own[u]]) + (y[u] >> 6));
             if ((word >> (y[u] & 63)) & 1ull) cflag[own[u]] = 1;
           }
       }
@@ -1281,7 +1332,7 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
   #pragma unroll
           for (uint32_t u = 0; u < 4; ++u) {
             const uint32_t wi = w0 + u * WAVE + lane;
-            if (wi < words) any |= *(ra + wi) & *(rb + wi);
+            if (wi < words) any |= ld<TEAM>(ra + wi) & ld<TEAM>(rb + wi);
           }
           nread += min(4 * WAVE, words - w0);
           found = __ballot(any != 0) != 0;
@@ -1313,7 +1364,7 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
         dw = d.len[w];
       }
       bool w1 = false, w2 = false;
-      if (__ballot(drop)) clear_pairs(d.L[j], d.Dm[j], d.W, x, w, drop, merge, &w1, &w2);
+      if (__ballot(drop)) clear_pairs<TEAM>(d.L[j], d.Dm[j], d.W, x, w, drop, merge, &w1, &w2);
       if (counting && (w1 || w2)) atomicAdd(&s.stat[4], (uint32_t)w1 + (uint32_t)w2);
       // Follow-up work of both events: the events themselves, and items over
       // the row of each event's source -- the support update (j == h), else
@@ -1333,11 +1384,13 @@ __device__ void level_step(const Dev& d, const RoundCtx rc, uint32_t j, uint32_t
       if (lane == 0 && te)
         off = atomicAdd(&s.res[pass], ((unsigned long long)te << 32) | (t1 + t2));
       __syncthreads();
-      if (threadIdx.x < 2) {
+      if (wave == LV_WAVES - 1 && lane < 2) {
+        // the last wave: in small rounds it has no pair, and so no atomics in
+        // flight for the reservation to wait behind
         const unsigned long long sum = s.res[pass];
-        const uint32_t v = threadIdx.x ? (uint32_t)(sum >> 32) : (uint32_t)sum;
-        uint32_t* at = threadIdx.x ? &c->cnt[j][rc.p].nev : &c->cnt[list][rc.p].nit;
-        s.bres[threadIdx.x] = v ? atomicAdd(at, v) : 0u;
+        const uint32_t v = lane ? (uint32_t)(sum >> 32) : (uint32_t)sum;
+        uint32_t* at = lane ? &c->cnt[j][rc.p].nev : &c->cnt[list][rc.p].nit;
+        s.bres[lane] = v ? at_add<TEAM>(at, v) : 0u;
         s.res[pass ^ 1] = 0;
       }
       pass ^= 1;
@@ -1384,7 +1437,7 @@ __global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ de
   if (j > d.h) return;  // this slot's graph has fewer levels
   Ctl* c = d.ctl;
   if (c->done) return;
-  if (c->halt) return;
+  if (c->halt || c->phase > j) return;  // phase: earlier steps were done by the team kernel
   // a round that peels every remaining edge leaves no ball or support that
   // could matter: the decomposition ends with it
   if (c->nRc.v == c->live) return;
@@ -1401,7 +1454,7 @@ __global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ de
   for (uint32_t i = threadIdx.x; i < LV_CAP; i += LV_THREADS) s.flag[i] = 0;
   if (threadIdx.x < 5) s.stat[threadIdx.x] = 0;
   __syncthreads();
-  level_step<LV_THREADS, LV_CAP>(d, rc, j, min(c->cnt[j][rc.p].nit, d.itcap), blockIdx.x,
+  level_step<LV_THREADS, LV_CAP, false>(d, rc, j, min(c->cnt[j][rc.p].nit, d.itcap), blockIdx.x,
                                         gridDim.x, s);
   if (d.spart) {
     __syncthreads();
@@ -1410,13 +1463,19 @@ __global__ void __launch_bounds__(LV_THREADS) k_level(const Dev* __restrict__ de
 }
 
 
+__device__ __forceinline__ void reset_team(const Dev& d) {
+  if (d.team)
+    for (uint32_t i = threadIdx.x; i < sizeof(Team) / 4; i += blockDim.x)
+      reinterpret_cast<uint32_t*>(d.team)[i] = 0;
+}
+
 // ---- K4: support update --------------------------------------------------
 // Top-level event (a -> w): every live edge (a,b) that had w as a common
 // h-neighbour loses it.  Old/new rule: w counts against (a,b) if it was in
 // b's old ball when a < b, and in b's new ball when a > b (see the header).
 // wg of nwg workgroups of `wpb` waves call it together; stat: stats mode only.
-template <uint32_t U>
-__device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint32_t wg,
+template <bool TEAM, uint32_t U>
+__device__ __forceinline__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint32_t wg,
                              uint32_t nwg, uint32_t wpb, uint32_t* stat) {
   const uint32_t lane = lane_id();
   const uint64_t* Lh = d.L[d.h];
@@ -1432,7 +1491,7 @@ __device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint
   const bool flip = d.perm != nullptr;
   const uint32_t waves = nwg * wpb, wave = threadIdx.x / WAVE;
   const uint32_t sh = nit <= waves ? 0 : nit <= 2 * waves ? 1 : 2;  // log2 of the block
-  const uint32_t wid = sh == 0 ? wave * nwg + wg : xcd_first(wg, nwg) * wpb + wave;
+  const uint32_t wid = sh == 0 ? wave * nwg + wg : (TEAM ? wg : xcd_first(wg, nwg)) * wpb + wave;
   // this wave's s-th item
   auto item_at = [&](uint32_t s) {
     return ((wid + (s >> sh) * waves) << sh) + (s & ((1u << sh) - 1));
@@ -1452,9 +1511,9 @@ __device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint
     S.e = 0;
     const uint32_t i = item_at(s);
     if (i < nit) {
-      S.I = items[i];
+      S.I = ld_item<TEAM>(items + i);
       if (lane < meta_len(S.I.meta)) {
-        const uint64_t w = *(d.ce + S.I.base + lane);
+        const uint64_t w = ld<TEAM>(d.ce + S.I.base + lane);
         S.b = (uint32_t)w;
         S.e = (uint32_t)(w >> 32);
       }
@@ -1467,8 +1526,8 @@ __device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint
   auto hit_of = [&](const Slot& S) -> bool {
     if (S.b & SLOT_GONE) return false;
     const size_t o = (size_t)S.I.y * d.W + (S.b >> 6);
-    uint64_t word = *(Lh + o);
-    if ((S.I.x < S.b) != flip) word |= *(Dh + o);
+    uint64_t word = ld<TEAM>(Lh + o);
+    if ((S.I.x < S.b) != flip) word |= ld<TEAM>(Dh + o);
     return (word >> (S.b & 63)) & 1ull;
   };
   Slot A[U];
@@ -1484,7 +1543,7 @@ __device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint
       e[u] = A[u].e;
       base[u] = A[u].I.base;
     }
-    if (stat) {
+    if (!TEAM && stat) {
       uint32_t hits = 0, slots = 0, taken = 0;
       for (uint32_t u = 0; u < U; ++u) {
         taken += item_at(it + u) < nit;
@@ -1511,11 +1570,11 @@ __device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint
 #pragma unroll
     for (uint32_t u = 0; u < U; ++u)
       if (dec[u]) {
-        const uint32_t old = atomicSub(&d.sup[e[u]], dec[u]);
+        const uint32_t old = at_sub<TEAM>(&d.sup[e[u]], dec[u]);
         push |= (uint32_t)(old > rc.k - 2 && old - dec[u] <= rc.k - 2) << u;
       }
     if (__ballot(push != 0)) {
-      uint32_t slot = wave_reserve(nPush, (uint32_t)__popc(push));
+      uint32_t slot = wave_reserve<TEAM>(nPush, (uint32_t)__popc(push));
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u)
         if ((push >> u) & 1u) Rn[slot++] = e[u];
@@ -1523,12 +1582,14 @@ __device__ void support_step(const Dev& d, const RoundCtx rc, uint32_t nit, uint
   }
 }
 
-__global__ void __launch_bounds__(256) k_support(const Dev* __restrict__ devs) {
+__global__ void __launch_bounds__(256) k_support(const Dev* __restrict__ devs, uint32_t after_team) {
   const Dev& d = devs[blockIdx.y];
   Ctl* c = d.ctl;
+  // the team of this graph step has gone; its meeting point is free again
+  if (after_team && blockIdx.x == 0) reset_team(d);
   if (c->done) return;
   const uint32_t list = d.h + 1;
-  if (c->halt) return;
+  if (c->halt || c->phase > list) return;
   if (c->nRc.v == c->live) return;  // the last round: nothing left to update
   const RoundCtx rc = round_ctx(c);
   if (!c->recovering && (c->cnt[list][rc.p].iovf || (d.serial & 8u))) {
@@ -1545,7 +1606,7 @@ __global__ void __launch_bounds__(256) k_support(const Dev* __restrict__ devs) {
     if (threadIdx.x < 3) s_stat[threadIdx.x] = 0;
     __syncthreads();
   }
-  support_step<2>(d, rc, min(c->cnt[list][rc.p].nit, d.itcap), blockIdx.x, gridDim.x,
+  support_step<false, 2>(d, rc, min(c->cnt[list][rc.p].nit, d.itcap), blockIdx.x, gridDim.x,
                       blockDim.x / WAVE, counting ? s_stat : nullptr);
   if (counting) {
     __syncthreads();
@@ -1573,54 +1634,79 @@ __global__ void k_stats_fold(const Dev* __restrict__ dp, uint32_t first, uint32_
     d.ctl->stat[threadIdx.x] += acc[threadIdx.x];
 }
 
-// The counters of one round parity back to zero.
-__device__ __forceinline__ void reset_parity(Ctl* c, uint32_t h, uint32_t q) {
-  for (uint32_t j = 1; j <= h + 1; ++j) {
-    Cnt& n = c->cnt[j][q];
-    n.nit = n.iovf = n.nev = n.ovf = 0;
-  }
-  c->nPushc[q].v = 0;
-}
-
 // ---- K5: end of round ------------------------------------------------------
-// One thread closes the round (counters, next round's peel set and level-jump
+// Ends a round that the whole chip ran (the team kernel ends the others
+// itself); phase: what the next one starts with, 0 or ROUND_CLOSED.  One
+// wavefront closes the round (counters, next round's peel set and level-jump
 // flag).  When the round pushed no edge, the next round starts with a level
-// jump, and every workgroup computes its share of the live minimum now.  A
-// workgroup may look while the closing thread is at work, or after it: so it
-// asks whether either parity's push count is zero.  This round's count is not
-// written here, so a needed minimum is never skipped; one computed because the
-// other count is zero is read by nobody.
-__global__ void __launch_bounds__(256) k_end(const Dev* __restrict__ devs) {
+// jump, and every workgroup computes its share of the live minimum now (not
+// for ROUND_CLOSED: the team kernel has its own).  A workgroup may look while
+// the closing wavefront is at work, or after it, when the round number may
+// have moved on: so it asks whether either parity's push count is zero.  Both
+// stay as they are until the next round's marking, so a minimum is computed
+// too often only in the round of a jump.
+// Closing is a handful of words, each on a line of its own that the kernels
+// before wrote in memory: lane j has level j's, so that all of them are in
+// flight at once and the stores follow (R-MAT 16 h = 2: 4.0 us for one thread
+// one after the other).
+// compacted: rows were compacted, if due, before this round.
+__global__ void __launch_bounds__(256) k_end(const Dev* __restrict__ devs, uint32_t phase,
+                                             uint32_t compacted) {
   const Dev& d = devs[blockIdx.y];
   Ctl* c = d.ctl;
-  // one decision per workgroup, taken before its closing thread (workgroup 0)
-  // changes anything, so that every thread of it takes the same branch
+  // one decision per workgroup, taken before its closing wavefront (workgroup
+  // 0) changes anything, so that every thread of it takes the same branch
   __shared__ uint32_t s_mode;  // 0 close only, 1 minimum and close, 2 nothing
-  if (threadIdx.x == 0) s_mode = (c->done || c->halt) ? 2u : (c->nPushc[0].v == 0 || c->nPushc[1].v == 0 ? 1u : 0u);
+  if (threadIdx.x == 0) {
+    const uint32_t none = (c->done != 0) | (c->halt != 0) | (c->phase == ROUND_CLOSED);
+    const uint32_t jump = (c->nPushc[0].v == 0) | (c->nPushc[1].v == 0);
+    s_mode = none ? 2u : phase == ROUND_CLOSED ? 0u : jump;
+  }
   __syncthreads();
   const uint32_t mode = s_mode;
   if (mode == 2) return;
   if (mode == 1) jump_partials(d);
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  const uint32_t p = c->r & 1, q = p ^ 1;
-  const uint32_t pushed = c->nPushc[p].v;
-  c->cnt[1][p].nev = 2 * c->nRc.v;  // level-1 events: both directions of every peeled edge
-  c->events += c->cnt[d.h][p].nev;
-  for (uint32_t j = 1; j <= d.h; ++j) c->levents[j] += c->cnt[j][p].nev;
-  uint32_t any = 0;
-  for (uint32_t j = 1; j <= d.h + 1; ++j) any |= c->cnt[j][p].ovf | c->cnt[j][p].iovf;
-  // the other parity's counters, for the next round (this round's stay: the
-  // next one clears the change marks they list and peels the edges it pushed)
-  reset_parity(c, d.h, q);
-  c->overflows += any ? 1 : 0;
-  c->live -= c->nRc.v;
-  c->r += 1;
-  c->nRc.v = pushed;
-  c->jump = pushed == 0;
-  d.status[2] = c->live;
-  if (c->live == 0) {
-    c->done = 1;
-    d.status[0] = 1;
+  if (blockIdx.x != 0 || threadIdx.x >= WAVE) return;
+  const uint32_t lane = threadIdx.x, h = d.h, r = c->r, p = r & 1, q = p ^ 1;
+  const uint32_t nR = c->nRc.v, was = c->live, live = was - nR;
+  const uint32_t pushed = p ? c->nPushc[1].v : c->nPushc[0].v;
+  const bool level = lane >= 1 && lane <= h + 1;  // h + 1: the support items
+  uint32_t over = 0, nev = 0;
+  uint64_t levents = 0;
+  if (level) {
+    const Cnt& n = c->cnt[lane][p];
+    over = n.ovf | n.iovf;
+    nev = n.nev;
+    if (lane <= h) levents = c->levents[lane];
+  }
+  if (lane == 1) nev = 2 * nR;  // level-1 events: both directions of every peeled edge
+  const uint64_t events = c->events, overflows = c->overflows;
+  const uint32_t top = __shfl(nev, (int)h, WAVE);
+  const bool any = __ballot(over != 0) != 0;
+  if (level) {
+    // the other parity's counters, for the next round (this round's stay: the
+    // next one clears the change marks they list and peels the edges it pushed)
+    Cnt& n = c->cnt[lane][q];
+    n.nit = n.iovf = n.nev = n.ovf = 0;
+    if (lane <= h) c->levents[lane] = levents + nev;
+  }
+  if (lane == 1) c->cnt[1][p].nev = nev;
+  if (lane == 0) {
+    if (phase == ROUND_CLOSED) c->nPushc[q].v = 0;  // else the marking does it
+    if (compacted && was <= c->compact_at) c->compact_at = compact_next(was);
+    c->events = events + top;
+    c->overflows = overflows + (any ? 1 : 0);
+    c->live = live;
+    c->r = r + 1;
+    c->nRc.v = pushed;
+    c->jump = pushed == 0;
+    c->phase = phase;
+    d.status[2] = live;
+    d.status[3] = r + 1;
+    if (live == 0) {
+      c->done = 1;
+      d.status[0] = 1;
+    }
   }
 }
 
@@ -1640,12 +1726,15 @@ __global__ void __launch_bounds__(256) k_outputs(Dev d) {
 // After the initial pass of a newly admitted graph: publish its state
 // (malformed CSR: finished with error).
 __global__ void k_post_init(Dev d) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+  if (blockIdx.x != 0) return;
+  reset_team(d);
+  if (threadIdx.x != 0) return;
   Ctl* c = d.ctl;
   if (c->err) c->done = 1;
   d.status[0] = c->err ? 2u : (c->done ? 1u : 0u);
   d.status[1] = 0;
   d.status[2] = c->err ? 0u : c->live;
+  d.status[3] = 0;
 }
 
 // ---- recovery of a round whose work list overflowed ----------------------
@@ -1665,8 +1754,8 @@ __device__ __forceinline__ void fill_event_items(const Dev& d, uint32_t p, uint3
     bx = d.rp[x];
     nx = d.len[x] + (support ? 0u : 1u);
   }
-  if (support) emit_group<ITEM_SLOTS>(d, p, list, 0, 0, x, w, bx, nx);
-  else emit_group<ITEM_ROW>(d, p, list, KIND_B_SLOTS, 1, x, w, bx, nx);
+  if (support) emit_group<ITEM_SLOTS, false>(d, p, list, 0, 0, x, w, bx, nx);
+  else emit_group<ITEM_ROW, false>(d, p, list, KIND_B_SLOTS, 1, x, w, bx, nx);
 }
 
 // Change-mark bits [blo, bhi) of level jm as events (x -> w): follow-up
@@ -1757,11 +1846,11 @@ __global__ void __launch_bounds__(256) k_fill_level(const Dev* __restrict__ dp, 
       const uint32_t n0 = chunks_of(v0), n1 = chunks_of(v1);
       uint32_t t0, t1;
       const uint32_t e0 = wave_excl_scan(n0, &t0), e1 = wave_excl_scan(n1, &t1);
-      const uint32_t first = reserve_wave(&d.ctl->cnt[2][rc.p].nit, t0 + t1);
+      const uint32_t first = reserve_wave<false>(&d.ctl->cnt[2][rc.p].nit, t0 + t1);
       emit_items_wave<ITEM_ROW>(d, rc.p, 2, first, t0, e0, n0, KIND_A_SLOTS, 1, x, z, bz, v0);
       emit_items_wave<ITEM_ROW>(d, rc.p, 2, first + t0, t1, e1, n1, KIND_B_SLOTS, 0, x, z, bx, v1);
     } else {
-      emit_word_items(d, rc.p, j, a, x, z);  // (x, w), w in z's old (j-1)-ball
+      emit_word_items<false>(d, rc.p, j, a, x, z);  // (x, w), w in z's old (j-1)-ball
     }
   }
   // the level-(j-1) events (x -> w): (y, w), y a live neighbour of x, and (x, w)
@@ -1804,6 +1893,7 @@ __global__ void k_recovery_end(const Dev* __restrict__ dp) {
 // are short, and what bounds the step is the chain of dependent loads per row,
 // not bytes.  In place: a chunk's slots are read before any is written, and
 // slots only move to the front, never past a chunk still to be read.
+template <bool TEAM>
 __device__ void compact_rows(const Dev& d, uint32_t wave, uint32_t nwaves) {
   constexpr uint32_t G = 16;
   const uint32_t g = lane_id() / G, sub = lane_id() & (G - 1);
@@ -1816,7 +1906,7 @@ __device__ void compact_rows(const Dev& d, uint32_t wave, uint32_t nwaves) {
       uint64_t w = SLOT_GONE;
       uint32_t y = 0, e = 0;
       if (i < n) {
-        w = *(d.ce + q);
+        w = ld<TEAM>(d.ce + q);
         y = d.cix[q];
         e = (uint32_t)(w >> 32);
       }
@@ -1837,12 +1927,22 @@ __device__ void compact_rows(const Dev& d, uint32_t wave, uint32_t nwaves) {
   }
 }
 
+// At the head of a captured run of whole-chip rounds, where it is due.
+__global__ void __launch_bounds__(256) k_compact_due(const Dev* __restrict__ devs) {
+  const Dev& d = devs[blockIdx.y];
+  Ctl* c = d.ctl;
+  if (c->done || c->halt || !(c->live <= c->compact_at || (d.serial & 16u))) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) c->compactions += 1;
+  compact_rows<false>(d, blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE,
+                      gridDim.x * (blockDim.x / WAVE));
+}
+
 // Host-driven rounds: runs only at a round boundary of a running slot.
 __global__ void __launch_bounds__(256) k_compact(Dev d) {
   Ctl* c = d.ctl;
   if (c->done || c->halt) return;
   if (blockIdx.x == 0 && threadIdx.x == 0) c->compactions += 1;
-  compact_rows(d, blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE,
+  compact_rows<false>(d, blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE,
                gridDim.x * (blockDim.x / WAVE));
 }
 
