@@ -79,15 +79,15 @@ typedef enum {
  * in the Python package picks them per graph shape by measurement. */
 typedef struct {
     uint32_t word_bits;       /* initial h-support: bitset load width per lane, 64 or 128
-                                 (0 = 64)                                                 */
-    uint32_t dense_threshold; /* level-2 ball build: a row is built bottom-up (OR of the
-                                 neighbours' level-1 rows, dense frontier) instead of
-                                 top-down (scatter of their adjacency lists, sparse
-                                 frontier) when those lists hold more than
-                                 dense_threshold/16 entries per bitset word the bottom-up
-                                 build reads, i.e. (deg(x)+1)*W words; 0 = 32            */
+                                 (0 = 64; 128 where the graph is renumbered)              */
+    uint32_t dense_threshold; /* level-2 ball build: a vertex of the frontier is taken
+                                 bottom-up (OR of its level-1 row) instead of top-down
+                                 (scatter of its adjacency list) when its list holds more
+                                 than dense_threshold/16 entries per bitset word; 0 = 8,
+                                 and more than 128 entries                               */
     uint32_t edges_per_wave;  /* initial h-support: edges sharing one wavefront, 1..16
-                                 (0 = by row width)                                      */
+                                 (0 = by row width; renumbered graphs: 0 and 1 by slices
+                                 of the words)                                           */
     uint32_t flags;           /* HO_FLAG_*                                               */
     uint32_t event_capacity;  /* per-level ball-change event list entries; a round that
                                  overflows it re-creates the next step's work from the

@@ -3,9 +3,8 @@
 The initial pass of a decomposition (edge ids, level-1..h ball build,
 h-support of every edge) has three knobs that change speed, never results:
 
-* ``dense_threshold`` -- level-2 ball build: bottom-up (OR of neighbour rows,
-  a dense-bitset frontier) versus top-down (scatter of adjacency lists, a
-  sparse-list frontier) per row;
+* ``dense_threshold`` -- level-2 ball build: bottom-up (OR of a neighbour's
+  bitset row) versus top-down (scatter of its adjacency list) per neighbour;
 * ``word_bits`` -- bitset load width per lane in the h-support pass (64/128);
 * ``edges_per_wave`` -- edges sharing one wavefront in that pass (1..16).
 

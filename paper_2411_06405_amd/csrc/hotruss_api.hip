@@ -326,8 +326,9 @@ hoStatus run_init(const Dev& d, uint32_t* out_sup, const hoTuning* tune, hipStre
   const size_t lds = (size_t)d.W * 8;
   const unsigned rows_grid = grid_for(d.n, 1, 64);
   hipLaunchKernelGGL(k_build_L1, dim3(rows_grid), dim3(T), lds, s, d);
-  const uint32_t dthr = tune && tune->dense_threshold ? tune->dense_threshold : 32;
-  if (d.h >= 2) hipLaunchKernelGGL(k_build_L2, dim3(rows_grid), dim3(T), lds, s, d, dthr);
+  const bool dset = tune && tune->dense_threshold;
+  const uint32_t dthr = dset ? tune->dense_threshold : 8, dmin = dset ? 0 : BALL_SHORT;
+  if (d.h >= 2) hipLaunchKernelGGL(k_build_L2, dim3(rows_grid), dim3(T), lds, s, d, dthr, dmin);
   for (uint32_t j = 3; j <= d.h; ++j)
     hipLaunchKernelGGL(k_build_Lj, dim3(rows_grid), dim3(T), 0, s, d, j);
   uint32_t epw = tune && tune->edges_per_wave ? tune->edges_per_wave : 0;
@@ -344,7 +345,16 @@ hoStatus run_init(const Dev& d, uint32_t* out_sup, const hoTuning* tune, hipStre
       hipLaunchKernelGGL((k_support_init<G, 1>), dim3(grid_for(d.m, T / G)), dim3(T), 0, s, \
                          d, out_sup, by_caller);                                            \
   } while (0)
-  if (epw >= 16) HO_SUPINIT(4);
+  if (d.perm && epw == 1) {  // rows of 4 KiB and more: see k_support_slices
+    const unsigned blocks = std::max(8u, grid_for(d.m, T / 16 * SLICE_EDGES) / 8 * 8);
+    hipLaunchKernelGGL(k_fill32, dim3(grid_for(d.m, T)), dim3(T), 0, s, d.sup, (size_t)d.m, 0u - 2u);
+    if (tune && tune->word_bits == 64)
+      hipLaunchKernelGGL(k_support_slices<1>, dim3(blocks), dim3(T), 0, s, d, d.sup);
+    else
+      hipLaunchKernelGGL(k_support_slices<2>, dim3(blocks), dim3(T), 0, s, d, d.sup);
+    if (by_caller)
+      hipLaunchKernelGGL(k_support_out, dim3(grid_for(d.m, T)), dim3(T), 0, s, d, d.sup, out_sup);
+  } else if (epw >= 16) HO_SUPINIT(4);
   else if (epw >= 8) HO_SUPINIT(8);
   else if (epw >= 4) HO_SUPINIT(16);
   else if (epw >= 2) HO_SUPINIT(32);

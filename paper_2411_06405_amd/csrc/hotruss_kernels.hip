@@ -378,51 +378,72 @@ __global__ void __launch_bounds__(256) k_build_L1(Dev d) {
   }
 }
 
-// Level 2.  Each row is built in LDS, by whichever of two frontier
-// expansions reads less: top-down (sparse) scatters the adjacency of every
-// z in N[x]; bottom-up (dense) ORs the level-1 rows of every z in N[x]
-// (B(x,2) = union of N[z] over z in N[x]).  The dense form is taken when the
-// frontier's adjacency entries exceed dthr/16 times the bitset words it
-// would read, (deg(x)+1)·W.
-__global__ void __launch_bounds__(256) k_build_L2(Dev d, uint32_t dthr) {
+// Level 2: B(x,2) is the union of N[z] over z in N[x].  The row is built in
+// LDS, each z in the way that reads less: the adjacency of a short one is
+// scattered into it, by 16 lanes (the chains of 16 rows run side by side) or
+// by a wavefront, and the level-1 row of a long one is ORed, each thread owning
+// words (long: more than dthr/16 entries a bitset word, and more than dmin).
+// Hubs and short rows meet in most frontiers of a power-law graph; with one way
+// for the whole frontier R-MAT 17 takes 5.28 ms, so 2.75 (a way for each, the
+// line at 2 entries a word: 3.59; at a half: 2.75; at a quarter or an eighth
+// 0.1 and 0.5 more).
+constexpr uint32_t BALL_BATCH = 1024;  // frontier vertices per pass
+constexpr uint32_t BALL_SHORT = 128;   // entries that 16 lanes scatter
+__global__ void __launch_bounds__(256) k_build_L2(Dev d, uint32_t dthr, uint32_t dmin) {
   extern __shared__ uint64_t srow[];
-  __shared__ uint32_t s_fsum;
+  __shared__ uint32_t s_z[BALL_BATCH], s_mid, s_long;
   if (d.ctl->err) return;
   const uint32_t nact = d.ctl->nact, words = d.ctl->words;
   const uint32_t lane = lane_id(), wv = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
+  const uint32_t grp = threadIdx.x / 16, sub = threadIdx.x & 15, ngrp = blockDim.x / 16;
   const uint64_t* L1 = d.L[1];
   for (uint32_t x = blockIdx.x; x < nact; x += gridDim.x) {
     const uint32_t beg = d.rp[x], end = d.rp[x + 1];
-    if (threadIdx.x == 0) s_fsum = 0;
     for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) srow[i] = 0;
-    __syncthreads();
-    uint32_t fs = 0;
-    for (uint32_t q = beg + threadIdx.x; q < end; q += blockDim.x) {
-      const uint32_t z = d.ci[q];
-      fs += d.rp[z + 1] - d.rp[z];
-    }
-    fs = wave_sum(fs);
-    if (lane == 0 && fs) atomicAdd(&s_fsum, fs);
-    __syncthreads();
-    const bool dense = (uint64_t)s_fsum * 16 > (uint64_t)dthr * (end - beg + 1) * words;
-    if (dense) {
-      for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) {
-        uint64_t acc = L1[(size_t)x * d.W + i];
-        for (uint32_t q = beg; q < end; ++q) acc |= L1[(size_t)d.ci[q] * d.W + i];
-        srow[i] = acc;
-      }
-    } else {
-      // z = x (index end) and every neighbour z = ci[q]
-      for (uint32_t q = beg + wv; q < end + 1; q += nw) {
+    // z = x (index end) and every neighbour z = ci[q]
+    for (uint32_t q0 = beg; q0 <= end; q0 += BALL_BATCH) {
+      const uint32_t q1 = min(q0 + BALL_BATCH, end + 1);
+      if (threadIdx.x == 0) s_mid = s_long = 0;
+      __syncthreads();
+      for (uint32_t q = q0 + grp; q < q1; q += ngrp) {
         const uint32_t z = (q == end) ? x : d.ci[q];
-        if (lane == 0) atomicOr(&srow[z >> 6], 1ull << (z & 63));
-        for (uint32_t k = d.rp[z] + lane; k < d.rp[z + 1]; k += WAVE) {
+        const uint32_t zb = d.rp[z], ze = d.rp[z + 1];
+        const bool dense = ze - zb > dmin && (uint64_t)(ze - zb) * 16 > (uint64_t)dthr * words;
+        if (dense || ze - zb > BALL_SHORT) {
+          // mid-sized rows from the front of the list, long ones from its end
+          if (sub == 0) {
+            if (dense) s_z[BALL_BATCH - 1 - atomicAdd(&s_long, 1u)] = z;
+            else s_z[atomicAdd(&s_mid, 1u)] = z;
+          }
+          continue;
+        }
+        if (sub == 0) atomicOr(&srow[z >> 6], 1ull << (z & 63));
+        for (uint32_t k = zb + sub; k < ze; k += 16) {
           const uint32_t y = d.ci[k];
           atomicOr(&srow[y >> 6], 1ull << (y & 63));
         }
       }
+      __syncthreads();
+      const uint32_t nmid = s_mid, nlong = s_long;
+      for (uint32_t l = wv; l < nmid; l += nw) {
+        const uint32_t z = s_z[l], ze = d.rp[z + 1];
+        if (lane == 0) atomicOr(&srow[z >> 6], 1ull << (z & 63));
+        for (uint32_t k = d.rp[z] + lane; k < ze; k += WAVE) {
+          const uint32_t y = d.ci[k];
+          atomicOr(&srow[y >> 6], 1ull << (y & 63));
+        }
+      }
+      if (nlong) {
+        if (nmid) __syncthreads();
+        for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) {
+          uint64_t acc = srow[i];
+#pragma unroll 8
+          for (uint32_t l = 0; l < nlong; ++l) acc |= L1[(size_t)s_z[BALL_BATCH - 1 - l] * d.W + i];
+          srow[i] = acc;
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
     uint64_t* out = row(d.L[2], d.W, x);
     for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) out[i] = srow[i];
     __syncthreads();
@@ -440,6 +461,7 @@ __global__ void __launch_bounds__(256) k_build_Lj(Dev d, uint32_t j) {
     const uint32_t beg = d.rp[x], end = d.rp[x + 1];
     for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) {
       uint64_t acc = P[(size_t)x * d.W + i];
+#pragma unroll 8
       for (uint32_t q = beg; q < end; ++q) acc |= P[(size_t)d.ci[q] * d.W + i];
       O[(size_t)x * d.W + i] = acc;
     }
@@ -481,6 +503,73 @@ __global__ void __launch_bounds__(256) k_support_init(Dev d, uint32_t* __restric
     for (int o = G / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, WAVE);
     if (sub == 0) out[by_caller && d.oe ? d.oe[e] : e] = c - 2;
   }
+}
+
+// The same for renumbered graphs, by slices of the words: blocks b with the
+// same b mod 8 share an XCD, and take every edge's words of one eighth.  One
+// wavefront an edge reads both rows whole, and is bound by the rows of the
+// hubs, which most edges end at and no L2 holds (R-MAT 17 h = 2: 8.8 KB a row,
+// 5.5 TB/s); an eighth of them, for the few thousand hubs that matter, stays in
+// the XCD's L2 (2.70 ms before, 1.66 now; with 64-bit loads 2.44).  Uniform random
+// 60,000 h = 2, all rows alike: 0.94 and 0.92 ms a call.  16 lanes take SLICE_EDGES consecutive edges, which share their
+// upper endpoint in most cases, and add the eighth to each edge's support
+// (sup: -2 before; own edge numbers, so that neighbouring edges' sums go to
+// memory in one request).
+constexpr int SLICE_EDGES = 4;
+template <int V>
+__global__ void __launch_bounds__(256) k_support_slices(Dev d, uint32_t* __restrict__ sup) {
+  if (d.ctl->err) return;
+  using Word = std::conditional_t<V == 2, ulonglong2, unsigned long long>;
+  const Word* Lh = reinterpret_cast<const Word*>(d.L[d.h]);
+  const uint32_t words = d.ctl->words, per = ((words + 7) / 8 + 7) & ~7u;
+  const uint32_t lo = min(words, (blockIdx.x & 7) * per) / V, hi = min(words, lo * V + per) / V;
+  if (lo >= hi) return;
+  constexpr uint32_t G = 16, K = SLICE_EDGES;
+  const uint32_t sub = threadIdx.x & (G - 1), gpb = blockDim.x / G;
+  const uint32_t stride = (gridDim.x >> 3) * gpb * K;
+  const size_t W = d.W / V;
+  auto both = [](const Word& x, const Word& y) -> uint32_t {
+    if constexpr (V == 2) return __popcll(x.x & y.x) + __popcll(x.y & y.y);
+    else return __popcll(x & y);
+  };
+  for (uint32_t e0 = ((blockIdx.x >> 3) * gpb + threadIdx.x / G) * K; e0 < d.m; e0 += stride) {
+    const Word *a[K], *b[K];
+    uint32_t c[K] = {};
+    bool one = true;
+#pragma unroll
+    for (uint32_t k = 0; k < K; ++k) {
+      const uint32_t e = min(e0 + k, d.m - 1);
+      a[k] = Lh + d.ev[e] * W;
+      b[k] = Lh + d.eu[e] * W;
+      one = one && a[k] == a[0];
+    }
+    if (one) {
+#pragma unroll 2
+      for (uint32_t i = lo + sub; i < hi; i += G) {
+        const Word x = a[0][i];
+#pragma unroll
+        for (uint32_t k = 0; k < K; ++k) c[k] += both(x, b[k][i]);
+      }
+    } else {
+      for (uint32_t i = lo + sub; i < hi; i += G)
+#pragma unroll
+        for (uint32_t k = 0; k < K; ++k) c[k] += both(a[k][i], b[k][i]);
+    }
+    uint32_t mine = 0;  // lane k of the group: edge e0 + k
+#pragma unroll
+    for (uint32_t k = 0; k < K; ++k) {
+      for (int o = G / 2; o > 0; o >>= 1) c[k] += __shfl_xor(c[k], o, WAVE);
+      if (sub == k) mine = c[k];
+    }
+    if (mine && e0 + sub < d.m) atomicAdd(&sup[e0 + sub], mine);
+  }
+}
+
+// Supports by own edge number to the caller's.
+__global__ void __launch_bounds__(256) k_support_out(Dev d, const uint32_t* __restrict__ sup,
+                                                     uint32_t* __restrict__ out) {
+  for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < d.m; e += gridDim.x * blockDim.x)
+    out[e] = sup[d.ne[e]];
 }
 
 // ============================================================ peel rounds
