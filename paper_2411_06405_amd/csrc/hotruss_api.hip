@@ -54,6 +54,12 @@ uint32_t clamp_cap(uint64_t want, uint64_t lo, uint64_t hi) {
 // work items (h >= 2): R-MAT 18 h = 2 5.46 -> 4.96 s, the h-support of R-MAT 17
 // 11.1 -> 8.8 ms.  BA 12,345 (1.5 KiB a row) lost 5%, Chung-Lu 100k at h = 1 4%.
 constexpr uint32_t RENUMBER_MIN_N = 32768;
+// A support query alone has no rounds to win the renumbering's 0.1 ms back, so
+// there the edges' rows must hold this many words in all.  Without and with, ms:
+// uniform random 53,443 (176 Mi words) 0.52, 0.61; 100,000 deg 6 (411 Mi) 1.31,
+// 1.45; Chung-Lu 84,075 (436 Mi) 1.44, 1.46; 100,000 (686 Mi) 2.13, 2.02; R-MAT
+// 16 (819 Mi) 3.31, 2.05; uniform random 100,000 deg 15 (1,029 Mi) 2.30, 2.37.
+constexpr uint64_t RENUMBER_MIN_WORDS = 600ull << 20;
 
 // may_renumber false: the smaller layout, for a graph that the memory at hand
 // does not hold otherwise (and for the H-index method, which reads the caller's).
@@ -65,8 +71,9 @@ bool make_plan(uint32_t n, uint64_t m, uint32_t h, const hoTuning* tune, bool fu
   if (h > HMAX) return false;
   Plan p;
   p.n = n; p.m = m; p.h = h; p.full = full;
-  p.renumber = may_renumber && h >= 2 && n >= RENUMBER_MIN_N;
   p.W = words_per_row(n);
+  p.renumber = may_renumber && h >= 2 && n >= RENUMBER_MIN_N &&
+               (full || m * p.W >= RENUMBER_MIN_WORDS);
   // Lists are sized so that a round rarely overflows them (a round that does
   // re-runs the overflowed step from the host in windows that fit).
   p.evcap = tune && tune->event_capacity ? tune->event_capacity
