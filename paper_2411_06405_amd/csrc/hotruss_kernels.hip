@@ -565,9 +565,10 @@ __global__ void __launch_bounds__(256) k_support_slices(Dev d, uint32_t* __restr
   }
 }
 
-// Supports by own edge number to the caller's.
+// Supports by own edge number to the caller's (a malformed graph has no numbers).
 __global__ void __launch_bounds__(256) k_support_out(Dev d, const uint32_t* __restrict__ sup,
                                                      uint32_t* __restrict__ out) {
+  if (d.ctl->err) return;
   for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < d.m; e += gridDim.x * blockDim.x)
     out[e] = sup[d.ne[e]];
 }
@@ -1805,6 +1806,7 @@ __global__ void __launch_bounds__(256) k_end(const Dev* __restrict__ devs, uint3
 // are writing too cost more than this pass (Chung-Lu 100k h = 1: the marking
 // of the largest round 740 us with them, 274 us without).
 __global__ void __launch_bounds__(256) k_outputs(Dev d) {
+  if (d.ctl->err) return;
   for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < d.m; e += gridDim.x * blockDim.x) {
     const uint32_t own = d.ne[e];
     d.out_t[e] = d.t[own];
