@@ -116,6 +116,14 @@ struct alignas(128) Team {
 };
 constexpr uint32_t TEAM_CLOSED = 1u << 16;
 
+// Arrivals at a team are numbered from 0.  The launch and the dealing of its
+// workgroups keep them at about 32; a team has room for TEAM_MAX whoever
+// comes, so the bound does not rest on them.
+constexpr __host__ __device__ bool team_admits(uint32_t arrival) { return arrival < TEAM_MAX; }
+constexpr __host__ __device__ uint32_t team_size(uint32_t arrivals) {
+  return arrivals < TEAM_MAX ? arrivals : TEAM_MAX;
+}
+
 // Everything a kernel needs, passed by value.
 struct Dev {
   const uint32_t* orp;  // the caller's row_ptr [n+1]

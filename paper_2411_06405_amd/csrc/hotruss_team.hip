@@ -25,7 +25,8 @@
 //
 // What makes it safe:
 //  * A team is whoever arrived: its workgroups join by a counter, the first
-//    one closes it after a bounded wait, and late ones return.  Every member
+//    one closes it after a bounded wait, and late ones return, as do those
+//    that come to a full team (TEAM_MAX).  Every member
 //    is running when the team starts, so a barrier never waits for a
 //    workgroup that has yet to be scheduled, whatever else shares the GPU.
 //  * Members check that they are on the same XCD (XCC_ID register).
@@ -106,9 +107,9 @@ __device__ bool team_join(Team* t, uint32_t expected, TeamLds& s) {
       me = atomicAdd(&t->joined, 1u);
       if (me == 0) {
         for (uint32_t i = 0; i < TEAM_JOIN_POLLS && ld<true>(&t->joined) < expected; ++i) {}
-        n = atomicExch(&t->joined, TEAM_CLOSED);
+        n = team_size(atomicExch(&t->joined, TEAM_CLOSED));
         __hip_atomic_store(&t->size, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      } else if (me < TEAM_CLOSED) {
+      } else if (team_admits(me)) {  // not after TEAM_CLOSED, nor once the team is full
         for (uint32_t i = 0; i < TEAM_SPIN && !n; ++i) n = ld<true>(&t->size);
       }
     }
@@ -379,10 +380,11 @@ __device__ void team_run(const Dev& d, uint32_t me, uint32_t n, const TeamLimits
   }
 }
 
-// One workgroup per CU (registers and LDS allow no second).  Workgroups are
-// dealt to the XCDs in turn, so block b is taken to be on XCD b mod 8; the
-// slots of an XCD share its workgroups evenly (fewer than eight slots: the
-// first XCD with a free CU takes a slot, and the others' workgroups return).
+// One workgroup per CU (its registers leave room for no second one; nothing but
+// speed depends on it).  Workgroups are dealt to the XCDs in turn, so block b is
+// taken to be on XCD b mod 8; the slots of an XCD share its workgroups evenly
+// (fewer than eight slots: the first XCD with a free CU takes a slot, and the
+// others' workgroups return).
 __global__ void __launch_bounds__(TEAM_THREADS) k_team(const Dev* __restrict__ devs,
                                                        const uint32_t* __restrict__ plan,
                                                        TeamLimits lim) {
