@@ -4,6 +4,15 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+// The team kernel (hotruss_team.hip) hands data from workgroup to workgroup of
+// one XCD by what this chip does and HIP's memory model does not promise: loads
+// of device scope are served by the XCD's L2, stores and atomics of workgroup
+// scope are complete there after s_waitcnt vmcnt(0), and XCC_ID names the XCD.
+// On another chip each of these has to be looked at first.
+#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
+#error "hotruss is written for gfx950: see the team kernel's use of the L2"
+#endif
+
 namespace hotruss {
 
 constexpr uint32_t HMAX = 16;            // largest hop threshold with its own ball level

@@ -29,3 +29,10 @@ static_assert(team_size(1) == 1 && team_size(TEAM_MAX) == TEAM_MAX && team_size(
 static_assert(team_size(TEAM_CLOSED - 1) == TEAM_MAX, "");
 """, tmp_path)
     assert r.returncode == 0, r.stderr[-2000:]
+
+
+def test_device_code_is_tied_to_its_chip(tmp_path):
+    src = '#include "hotruss_dev.h"\n'
+    assert _compile(src, tmp_path, device=True).returncode == 0
+    r = _compile(src, tmp_path, arch="gfx942", device=True)
+    assert r.returncode != 0 and "gfx950" in r.stderr
