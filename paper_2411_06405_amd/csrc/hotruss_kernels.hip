@@ -261,9 +261,9 @@ __global__ void __launch_bounds__(256) k_rows_lower(Dev d) {
   if (d.ctl->err) return;
   const uint32_t lane = lane_id(), wpb = blockDim.x / WAVE, nact = d.ctl->nact;
   for (uint32_t x = blockIdx.x * wpb + threadIdx.x / WAVE; x < nact; x += gridDim.x * wpb) {
-    const uint32_t o = d.inv[x], beg = d.orp[o], end = d.orp[o + 1];
+    const uint32_t o = d.inv[x], beg = d.orp[o], deg = d.orp[o + 1] - beg;
     uint32_t c = 0;
-    for (uint32_t q = beg + lane; q < end; q += WAVE) c += d.perm[d.oci[q]] < x;
+    for (uint32_t i = lane; i < deg; i += WAVE) c += d.perm[d.oci[beg + i]] < x;
     c = wave_sum(c);
     if (lane == 0) d.up_cnt[x] = c;
   }
@@ -320,12 +320,12 @@ __global__ void __launch_bounds__(1024) k_rows_long(Dev d) {
   while ((d.n - 1) >> shift >= 1024) ++shift;
   const uint32_t nlong = d.ctl->nlong, wave = threadIdx.x / WAVE;
   for (uint32_t x = blockIdx.x; x < nlong; x += gridDim.x) {
-    const uint32_t o = d.inv[x], beg = d.orp[o], end = d.orp[o + 1];
+    const uint32_t o = d.inv[x], beg = d.orp[o], deg = d.orp[o + 1] - beg;
     const uint32_t low = d.up_cnt[x];
     h[threadIdx.x] = 0;
     __syncthreads();
-    for (uint32_t q = beg + threadIdx.x; q < end; q += 1024)
-      atomicAdd(&h[d.perm[d.oci[q]] >> shift], 1u);
+    for (uint32_t i = threadIdx.x; i < deg; i += 1024)
+      atomicAdd(&h[d.perm[d.oci[beg + i]] >> shift], 1u);
     __syncthreads();
     const uint32_t v = h[threadIdx.x], incl = wave_incl_scan(v);
     if (lane_id() == WAVE - 1) ws[wave] = incl;
@@ -335,23 +335,25 @@ __global__ void __launch_bounds__(1024) k_rows_long(Dev d) {
     h[threadIdx.x] = start;
     if (threadIdx.x == 0) mid = low;  // slots above x of x's own range start here
     __syncthreads();
-    for (uint32_t q = beg + threadIdx.x; q < end; q += 1024) {
-      const uint32_t y = d.perm[d.oci[q]], r = y >> shift;
+    for (uint32_t i = threadIdx.x; i < deg; i += 1024) {
+      const uint32_t y = d.perm[d.oci[beg + i]], r = y >> shift;
       const uint32_t at = atomicAdd(r == x >> shift && y > x ? &mid : &h[r], 1u);
-      place_slot(d, x, at, y, d.eid[q]);
+      place_slot(d, x, at, y, d.eid[beg + i]);
     }
     __syncthreads();
   }
 }
 
-// Own edge numbers in place of the caller's; the lower endpoints' slots.
+// Own edge numbers in place of the caller's; the lower endpoints' slots.  (Up to
+// 2^32 - 2 slots: a 32-bit index would step past the last one and start again.)
 __global__ void __launch_bounds__(256) k_rows_edges(Dev d) {
   if (d.ctl->err) return;
-  for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < d.nnz; q += gridDim.x * blockDim.x) {
+  for (size_t q = blockIdx.x * (size_t)blockDim.x + threadIdx.x; q < d.nnz;
+       q += (size_t)gridDim.x * blockDim.x) {
     const uint64_t w = d.ce[q];
     const uint32_t y = (uint32_t)w, own = d.ne[(uint32_t)(w >> 32)];
     d.ce[q] = slot_word(own, y, false);
-    if (d.ev[own] == y) d.s1[own] = q;
+    if (d.ev[own] == y) d.s1[own] = (uint32_t)q;
   }
 }
 
@@ -398,18 +400,18 @@ __global__ void __launch_bounds__(256) k_build_L2(Dev d, uint32_t dthr, uint32_t
   const uint32_t grp = threadIdx.x / 16, sub = threadIdx.x & 15, ngrp = blockDim.x / 16;
   const uint64_t* L1 = d.L[1];
   for (uint32_t x = blockIdx.x; x < nact; x += gridDim.x) {
-    const uint32_t beg = d.rp[x], end = d.rp[x + 1];
+    const uint32_t beg = d.rp[x], deg = d.rp[x + 1] - beg;
     for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) srow[i] = 0;
-    // z = x (index end) and every neighbour z = ci[q]
-    for (uint32_t q0 = beg; q0 <= end; q0 += BALL_BATCH) {
-      const uint32_t q1 = min(q0 + BALL_BATCH, end + 1);
+    // z = x (index deg) and every neighbour z = ci[beg + q]
+    for (uint32_t q0 = 0; q0 <= deg; q0 += BALL_BATCH) {
+      const uint32_t q1 = min(q0 + BALL_BATCH, deg + 1);
       if (threadIdx.x == 0) s_mid = s_long = 0;
       __syncthreads();
       for (uint32_t q = q0 + grp; q < q1; q += ngrp) {
-        const uint32_t z = (q == end) ? x : d.ci[q];
-        const uint32_t zb = d.rp[z], ze = d.rp[z + 1];
-        const bool dense = ze - zb > dmin && (uint64_t)(ze - zb) * 16 > (uint64_t)dthr * words;
-        if (dense || ze - zb > BALL_SHORT) {
+        const uint32_t z = (q == deg) ? x : d.ci[beg + q];
+        const uint32_t zb = d.rp[z], zd = d.rp[z + 1] - zb;
+        const bool dense = zd > dmin && (uint64_t)zd * 16 > (uint64_t)dthr * words;
+        if (dense || zd > BALL_SHORT) {
           // mid-sized rows from the front of the list, long ones from its end
           if (sub == 0) {
             if (dense) s_z[BALL_BATCH - 1 - atomicAdd(&s_long, 1u)] = z;
@@ -418,18 +420,18 @@ __global__ void __launch_bounds__(256) k_build_L2(Dev d, uint32_t dthr, uint32_t
           continue;
         }
         if (sub == 0) atomicOr(&srow[z >> 6], 1ull << (z & 63));
-        for (uint32_t k = zb + sub; k < ze; k += 16) {
-          const uint32_t y = d.ci[k];
+        for (uint32_t k = sub; k < zd; k += 16) {
+          const uint32_t y = d.ci[zb + k];
           atomicOr(&srow[y >> 6], 1ull << (y & 63));
         }
       }
       __syncthreads();
       const uint32_t nmid = s_mid, nlong = s_long;
       for (uint32_t l = wv; l < nmid; l += nw) {
-        const uint32_t z = s_z[l], ze = d.rp[z + 1];
+        const uint32_t z = s_z[l], zb = d.rp[z], zd = d.rp[z + 1] - zb;
         if (lane == 0) atomicOr(&srow[z >> 6], 1ull << (z & 63));
-        for (uint32_t k = d.rp[z] + lane; k < ze; k += WAVE) {
-          const uint32_t y = d.ci[k];
+        for (uint32_t k = lane; k < zd; k += WAVE) {
+          const uint32_t y = d.ci[zb + k];
           atomicOr(&srow[y >> 6], 1ull << (y & 63));
         }
       }
