@@ -87,7 +87,7 @@ bool make_plan(uint32_t n, uint64_t m, uint32_t h, const hoTuning* tune, bool fu
   if (rowbytes > MAX_LDS_ROW) return false;  // rows are built in LDS
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o += up(bytes); return r; };
-  p.off_ctl = take(sizeof(Ctl));
+  p.off_ctl = take(ctl_bytes(full, p.renumber));
   p.off_eid = take(8 * m + 4);
   p.off_eu = take(4 * m + 4);
   p.off_ev = take(4 * m + 4);
@@ -133,6 +133,13 @@ bool make_plan(uint32_t n, uint64_t m, uint32_t h, const hoTuning* tune, bool fu
   return true;
 }
 
+// The plan that fits `room` bytes: the renumbered layout, else the smaller one.
+bool make_plan_in(size_t room, uint32_t n, uint64_t m, uint32_t h, const hoTuning* tune, bool full,
+                  Plan* P, uint64_t cap_factor = 128) {
+  return make_plan(n, m, h, tune, full, P, cap_factor) &&
+         (P->total <= room || make_plan(n, m, h, tune, full, P, cap_factor, false));
+}
+
 // Workspace of the truss extraction: validation state, edge ids, and the
 // union-find arrays (parent, touched) plus a counter, after the plan.
 bool make_topo_plan(uint32_t n, uint64_t m, Plan* P, size_t* off_cc) {
@@ -142,7 +149,7 @@ bool make_topo_plan(uint32_t n, uint64_t m, Plan* P, size_t* off_cc) {
   p.W = words_per_row(n);
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o += up(bytes); return r; };
-  p.off_ctl = take(sizeof(Ctl));
+  p.off_ctl = take(ctl_bytes(false, false));
   p.off_eid = take(8 * m + 4);
   p.off_eu = take(4 * m + 4);
   p.off_ev = take(4 * m + 4);
@@ -298,7 +305,8 @@ void run_scan(const Dev& d, uint32_t* out, hipStream_t s) {
 // CSR validation and canonical edge ids (slot <-> edge maps).
 void run_topology(const Dev& d, hipStream_t s) {
   const unsigned T = 256;
-  hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(256), 0, s, d.ctl, d.n, d.W, d.m);
+  hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(256), 0, s, d.ctl,
+                     (uint32_t)ctl_bytes(d.len != nullptr, d.perm != nullptr), d.n, d.W, d.m);
   hipLaunchKernelGGL(k_check_rowptr, dim3(grid_for(d.n + 1, T)), dim3(T), 0, s, d);
   hipLaunchKernelGGL(k_row_upper, dim3(grid_for(d.n, T / WAVE)), dim3(T), 0, s, d);
   run_scan(d, d.up_off, s);
@@ -452,6 +460,14 @@ hoStatus read_ctl(const Dev& d, Ctl* host, hipStream_t s) {
   HIPCHK(hipMemcpyAsync(host, d.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   return HO_OK;
+}
+
+// The verdict on the CSR, after an initial pass of its own.
+hoStatus check_csr(const Dev& d, hipStream_t s) {
+  uint32_t err;
+  HIPCHK(hipMemcpyAsync(&err, &d.ctl->err, sizeof err, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  return err ? HO_ERR_BAD_CSR : HO_OK;
 }
 
 // Timing of host-driven round steps (stats mode).
@@ -668,12 +684,18 @@ constexpr size_t GRAPH_CACHE = 256;
 std::mutex g_graph_mu;
 std::vector<GraphCacheEntry> g_graph_cache;
 
-// Engine header: S slot descriptors, S {done, halt} status pairs, the stats
-// counters and the control block of an idle slot (finished, so every round
-// kernel returns at once).
+// The stats counters of one decomposition, in the same place as the teams'
+// meeting points and the list of running slots: stats mode drives the rounds
+// from the host and has no teams.
+size_t shared_bytes(uint32_t S) {
+  return std::max(up(4ull * NSTAT * STAT_GRID), up(sizeof(Team) * S) + up(4ull * (S + 1)));
+}
+
+// Engine header: S slot descriptors, S {done, halt} status pairs, the shared
+// part and the control block of an idle slot (finished, so every round kernel
+// returns at once).
 size_t engine_header_bytes(uint32_t S) {
-  return up(sizeof(Dev) * S) + up(4ull * HO_STATUS_WORDS * S) + up(4ull * NSTAT * STAT_GRID) +
-         up(sizeof(Ctl)) + up(sizeof(Team) * S) + up(4ull * (S + 1));
+  return up(sizeof(Dev) * S) + up(4ull * HO_STATUS_WORDS * S) + shared_bytes(S) + up(sizeof(Ctl));
 }
 
 // Pinned host buffers and events of the plain entry point, kept per host
@@ -831,8 +853,8 @@ class Engine {
     devs_d = (Dev*)base;
     status_d = (uint32_t*)(base + up(sizeof(Dev) * S));
     spart_d = (uint32_t*)(base + up(sizeof(Dev) * S) + up(4ull * HO_STATUS_WORDS * S));
-    idle_ctl_d = (Ctl*)((uintptr_t)spart_d + up(4ull * NSTAT * STAT_GRID));
-    team_d = (Team*)((uintptr_t)idle_ctl_d + up(sizeof(Ctl)));
+    idle_ctl_d = (Ctl*)((uintptr_t)spart_d + shared_bytes(S));
+    team_d = (Team*)spart_d;
     plan_d = (uint32_t*)((uintptr_t)team_d + up(sizeof(Team) * S));
     pool.reset(engine_header_bytes(S), bytes);
     slot_req.assign(S, -1);
@@ -877,10 +899,7 @@ class Engine {
   }
 
   size_t need_bytes(uint32_t n, uint64_t m, uint32_t h, const hoTuning* tune, Plan* p) const {
-    if (!make_plan(n, m, h, tune, true, p, cap_factor)) return 0;
-    if (p->total > bytes - engine_header_bytes(S) &&
-        !make_plan(n, m, h, tune, true, p, cap_factor, false))
-      return 0;
+    if (!make_plan_in(bytes - engine_header_bytes(S), n, m, h, tune, true, p, cap_factor)) return 0;
     return p->total;
   }
 
@@ -1251,7 +1270,7 @@ hoStatus run_rounds_host(const Dev& d, const RoundGrid& g, hipStream_t s, bool t
 // hipGetSymbolAddress, taken once per device (scratch_base), and only that
 // address is used.
 // 256 MiB, of which the slot's own state took 2 KiB when that limit was set: its
-// growth since then is added, so that the graphs that fit are the same ones.
+// growth since then is added, so that every graph that fitted still does.
 constexpr size_t SCRATCH_BYTES = (256ull << 20) - 2048 + up(sizeof(Dev)) +
                                  up(4ull * HO_STATUS_WORDS) + up(sizeof(Team)) + up(sizeof(Ctl));
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
@@ -1371,15 +1390,12 @@ hoStatus hoTrussHSupport(const uint32_t* row_ptr, const uint32_t* col_idx, uint3
   hoStatus st = check_common(row_ptr, col_idx, n, m, h, out_support, workspace);
   if (st != HO_OK || m == 0) return st;
   Plan p;
-  if (!make_plan(n, m, h, tune, false, &p)) return HO_ERR_INVALID_ARG;
+  if (!make_plan_in(workspace_bytes, n, m, h, tune, false, &p)) return HO_ERR_INVALID_ARG;
   if (workspace_bytes < p.total) return HO_ERR_WORKSPACE;
   Dev d = carve(p, workspace, row_ptr, col_idx, nullptr, nullptr);
   st = run_init(d, out_support, tune, stream);
   if (st != HO_OK) return st;
-  Ctl c;
-  st = read_ctl(d, &c, stream);
-  if (st != HO_OK) return st;
-  return c.err ? HO_ERR_BAD_CSR : HO_OK;
+  return check_csr(d, stream);
 }
 
 hoStatus hoTrussDecompose(const uint32_t* row_ptr, const uint32_t* col_idx, uint32_t n,
@@ -1393,7 +1409,8 @@ hoStatus hoTrussDecompose(const uint32_t* row_ptr, const uint32_t* col_idx, uint
     return HO_OK;
   }
   Plan p;
-  if (!make_plan(n, m, h, tune, true, &p)) return HO_ERR_INVALID_ARG;
+  // (the engine looks again at what is left after its header)
+  if (!make_plan(n, m, h, tune, true, &p, 128, false)) return HO_ERR_INVALID_ARG;
   if (workspace_bytes < p.total + engine_header_bytes(1) + ALIGN) return HO_ERR_WORKSPACE;
   const bool stats = tune && (tune->flags & HO_FLAG_STATS);
   const bool host_loop = stats || (tune && (tune->flags & HO_FLAG_HOST_LOOP));
@@ -1591,6 +1608,7 @@ hoStatus hoTrussDecomposeBatched(const uint32_t* row_ptr_cat, const uint32_t* co
     const uint32_t n = (uint32_t)(vtx_off[g + 1] - vtx_off[g]);
     if (!make_plan(n, m, h[g], tune, true, &p, 16)) return HO_ERR_INVALID_ARG;
     order.push_back({p.total, g});
+    if (!make_plan(n, m, h[g], tune, true, &p, 16, false)) return HO_ERR_INVALID_ARG;
     largest = std::max(largest, up(p.total));
   }
   if (order.empty()) return HO_OK;
@@ -1754,9 +1772,7 @@ hoStatus hoTrussComponents(const uint32_t* row_ptr, const uint32_t* col_idx, uin
   hipLaunchKernelGGL(k_cc_label, dim3(grid_for(std::max<uint64_t>(m, n), T)), dim3(T), 0, stream, d,
                      trussness, k, parent, touched, out_component, counter);
   HIPCHK(hipGetLastError());
-  Ctl c;
-  HOCHK(read_ctl(d, &c, stream));
-  if (c.err) return HO_ERR_BAD_CSR;
+  HOCHK(check_csr(d, stream));
   uint32_t cnt = 0;
   HIPCHK(hipMemcpyAsync(&cnt, counter, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
   HIPCHK(hipStreamSynchronize(stream));
@@ -1824,9 +1840,7 @@ hoStatus hoTrussHIndex(const uint32_t* row_ptr, const uint32_t* col_idx, uint32_
   hoStatus init_st = HO_OK;
   HOCHK(timed(0, [&] { init_st = run_init(d, d.sup, nullptr, stream); }));
   HOCHK(init_st);
-  Ctl c;
-  HOCHK(read_ctl(d, &c, stream));
-  if (c.err) return HO_ERR_BAD_CSR;
+  HOCHK(check_csr(d, stream));
   Hx x;
   memset(&x, 0, sizeof x);
   x.rp = d.rp; x.ci = d.ci; x.eid = d.eid; x.eu = d.eu; x.ev = d.ev;

@@ -2,6 +2,7 @@
 // kernels (gfx950, wave64).  Internal header of the GPU library.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 // The team kernel (hotruss_team.hip) hands data from workgroup to workgroup of
@@ -24,7 +25,7 @@ constexpr uint32_t CHUNK = 64;           // slots (or bitset words) per work ite
 constexpr uint32_t MIN_PART = 1024;      // partial-minimum slots of the level-jump reduction
 constexpr uint32_t DEG_BUCKETS = 256;    // degree classes of the renumbering
 constexpr uint32_t NSTAT = 8;            // work counters kept in stats mode
-constexpr uint32_t STAT_GRID = 8192;     // most workgroups a counted kernel may use
+constexpr uint32_t STAT_GRID = 6144;     // most workgroups a counted kernel may use
 
 // error bits in Ctl::err (set by the validation kernels)
 constexpr uint32_t ERR_ROWPTR = 1u, ERR_COL = 2u, ERR_ORDER = 4u, ERR_LOOP = 8u,
@@ -88,6 +89,9 @@ struct Ctl {
   uint32_t halt;     // a work list overflowed: the host re-runs the step in windows
   uint32_t halt_step;  // step that halted: level j (2..h), or h+1 for the support update
   uint32_t jump;     // this round starts with a level jump
+  // A support query keeps the words up to here, and on a renumbered graph the
+  // buckets; the rest is the rounds' (see ctl_bytes).
+  uint32_t bucket[DEG_BUCKETS];  // vertices per degree bucket, then where each starts
   uint64_t events;   // top-level ball-change events (statistics)
   uint64_t overflows;
   Cnt cnt[HMAX + 2][2];  // per level (h+1: support items) and round parity
@@ -101,13 +105,17 @@ struct Ctl {
   uint32_t acct_nch;     // vertices whose h-ball changed this round (listed)
   uint32_t acct_nv;      // ball builds of this round (listed)
   uint32_t acct_incomplete;  // an event list overflowed: the count is a lower bound
-  uint32_t bucket[DEG_BUCKETS];  // vertices per degree bucket, then where each starts
   uint64_t acct_evals;
   uint64_t acct_bytes;
   uint64_t levents[HMAX + 1];  // ball-change events per level, all rounds
   // stats mode: work counters, level kernel [0..5), support kernel [5..8)
   uint64_t stat[NSTAT];
 };
+
+// Bytes of a control block: of a decomposition (full), or of the initial pass.
+constexpr __host__ __device__ size_t ctl_bytes(bool full, bool renumber) {
+  return full ? sizeof(Ctl) : renumber ? offsetof(Ctl, events) : offsetof(Ctl, bucket);
+}
 
 constexpr uint32_t ROUND_CLOSED = 0xffu;
 

@@ -37,9 +37,9 @@ __global__ void k_fill32(uint32_t* __restrict__ p, size_t cnt, uint32_t v) {
     p[i] = v;
 }
 
-__global__ void k_init_ctl(Ctl* ctl, uint32_t n, uint32_t words, uint32_t m) {
+__global__ void k_init_ctl(Ctl* ctl, uint32_t bytes, uint32_t n, uint32_t words, uint32_t m) {
   uint32_t* w = reinterpret_cast<uint32_t*>(ctl);
-  for (uint32_t i = threadIdx.x; i < sizeof(Ctl) / 4; i += blockDim.x) w[i] = 0;
+  for (uint32_t i = threadIdx.x; i < bytes / 4; i += blockDim.x) w[i] = 0;
   __syncthreads();
   if (threadIdx.x == 0) {
     ctl->nact = n;
