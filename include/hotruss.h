@@ -244,11 +244,13 @@ hoStatus hoTrussDecomposeBatched(const uint32_t *row_ptr_cat, const uint32_t *co
  *   hoSessionProgress admits queued requests first-come first-served while a
  *                     slot and pool memory are free (a request too large for
  *                     the memory free now waits, and later smaller ones may
- *                     pass it), then replays the step graph up to
+ *                     pass it), then replays step graphs up to
  *                     max_graph_launches times (0: until nothing is queued or
- *                     running), retiring finished requests.  Blocks on
- *                     `stream`.  Reports active and queued counts (host, may
- *                     be NULL).
+ *                     running), retiring finished requests.  A counted launch
+ *                     is at most 128 peel rounds of each running request (it
+ *                     may also end one that the launch before it began).
+ *                     Blocks on `stream`.  Reports active and queued counts
+ *                     (host, may be NULL).
  *   hoPoll            *done (host) = 1 once the ticket's outputs are final;
  *                     returns that request's status (HO_ERR_BAD_CSR for a
  *                     malformed graph, HO_ERR_CANCELLED if cancelled).

@@ -743,7 +743,7 @@ size_t host_bytes(uint32_t S) {
 }
 
 // Graphs an engine launches (see Engine::graph_shape).
-enum { GR_ONE, GR_FEW, GR_MANY, GR_LONG, GR_CHIP, GR_CHIPS, GR_N };
+enum { GR_ONE, GR_FEW, GR_MANY, GR_LONG, GR_SHORT, GR_CHIP, GR_CHIPS, GR_N };
 
 // Which kind of graph runs next, team steps or whole-chip rounds: the one that
 // got further per microsecond lately.  Neither is better by the sizes alone --
@@ -977,11 +977,11 @@ class Engine {
     uint32_t steps, rounds;  // rounds: of each team step, at most
   };
   GraphShape graph_shape(int which) const {
-    static constexpr uint32_t one[GR_N] = {1, 4, 16, 16, 32, 128}, many[GR_N] = {1, 2, 8, 2, 32, 128},
-                              flat[GR_N] = {4, 16, 32, 128, 0, 0};
+    static constexpr uint32_t one[GR_N] = {1, 4, 16, 16, 4, 32, 128}, many[GR_N] = {1, 2, 8, 2, 4, 32, 128},
+                              flat[GR_N] = {4, 16, 32, 128, 32, 0, 0};
     if (S == 1 && hmax == 1) return {true, flat[which], 0};
     return {which >= GR_CHIP, S == 1 ? one[which] : many[which],
-            S == 1 ? 4096u : which == GR_LONG ? 256u : 32u};
+            which == GR_SHORT ? 32u : S == 1 ? 4096u : which == GR_LONG ? 256u : 32u};
   }
   void capture(int which, hipStream_t cap) const {
     const GraphShape gs = graph_shape(which);
@@ -1119,10 +1119,18 @@ class Engine {
     std::fflush(stderr);
   }
 
-  // The graph of the next launch: short ones right after a halt (overflowing
-  // rounds tend to come in runs, and every round after a halt in the same graph
-  // is skipped), first (the decomposition may be over soon) and on trial.
-  int next_graph(bool halted) {
+  // The graph of the next launch.  A caller that counts launches gets them no
+  // longer than 128 rounds of a slot, whatever their kind.
+  int next_graph(bool halted, bool counted) {
+    const int which = pick_graph(halted);
+    if (!counted || which >= GR_CHIP || (S == 1 && hmax == 1)) return which;
+    return S == 1 || which == GR_MANY || which == GR_LONG ? (int)GR_SHORT : which;
+  }
+
+  // Short ones right after a halt (overflowing rounds tend to come in runs, and
+  // every round after a halt in the same graph is skipped), first (the
+  // decomposition may be over soon) and on trial.
+  int pick_graph(bool halted) {
     if (halted || steps == 0) return GR_ONE;
     if (S == 1 && hmax == 1) return steps < 4 ? GR_FEW : steps < 10 ? GR_MANY : GR_LONG;
     if (pace.pick()) {
@@ -1151,7 +1159,7 @@ class Engine {
       const int ahead = S == 1 && hmax > 1 && steps <= 1 ? 1 : 2;
       while (inflight < ahead && busy() && launched < max_launches) {
         const int buf = (head + inflight) & 1;
-        const int which = next_graph(calm < 2);
+        const int which = next_graph(calm < 2, max_launches != UINT64_MAX);
         HOCHK(ensure_graph(which));
         buf_graph[buf] = which;
         buf_time[buf] = clock::now();
