@@ -585,9 +585,10 @@ __global__ void __launch_bounds__(256) k_support_out(Dev d, const uint32_t* __re
 
 struct RoundCtx {
   uint32_t r, k, p;
+  uint32_t edges;  // peeled in the round, where the marking goes by it (see word_chunk)
 };
 
-__device__ __forceinline__ RoundCtx round_ctx(const Ctl* c) { return RoundCtx{c->r, c->k, c->r & 1}; }
+__device__ __forceinline__ RoundCtx round_ctx(const Ctl* c) { return RoundCtx{c->r, c->k, c->r & 1, 0}; }
 
 // ---- work item emission (all 64 lanes call; per-lane counts may be 0) ----
 // A lane's group of items covers one CSR row (or one ball row's words), CHUNK
@@ -604,11 +605,26 @@ enum { ITEM_ROW = 0, ITEM_SLOTS = 1, ITEM_WORDS = 2 };
 
 __device__ __forceinline__ uint32_t chunks_of(uint32_t nv) { return (nv + CHUNK - 1) / CHUNK; }
 
-// Ball words per item: a word can hold 64 candidates, so on small graphs 64
-// words would leave a round's few rows to a few waves (Chung-Lu 5,001 h = 3: the
-// slowest workgroup took 24 us over its items, the others 2); the rows of
-// larger graphs make enough items of 64.
-__device__ __forceinline__ uint32_t word_chunk(uint32_t words) { return words <= 512 ? 8 : CHUNK; }
+// Ball words per item.  A word can hold 64 candidates, so on small graphs 64
+// words would leave the few rows of a small round to a few waves (Chung-Lu 5,001
+// h = 3: the slowest workgroup took 24 us over its items, the others 2), and 8
+// are taken.  A round with enough items of 64 words takes those: eight times
+// the items are that many more steps of mostly idle lanes, and more list space.
+// `edges`: peeled in the round.  12 uniform graphs of 8,000 to 11,300 h = 3 in one
+// batch: 8 words always 59.3 ms, 64 always 45.3, by this rule 52.6; 6 Chung-Lu
+// of 12,000 to 16,500 h = 3: 984, 1,253, 988 ms; uniform 32,000 of degree 5 alone:
+// 20.2 by 8 always, 14.7 by the rule.  (512 items: 50.2 and 1,001 ms; 8,192: 54.7
+// and 992.)
+constexpr uint32_t WORDS_FEW = 8, WORD_ITEMS = 2048;
+__device__ __forceinline__ uint32_t word_chunk(uint32_t words, uint32_t edges) {
+  return words > 512 || (uint64_t)edges * chunks_of(words) >= WORD_ITEMS / 2 ? CHUNK : WORDS_FEW;
+}
+// A level jump finds its edges as it marks them.  8 words, unless the list could
+// run over by them.
+__device__ __forceinline__ uint32_t word_chunk_edges(const Dev& d) {
+  const uint64_t rows = 2ull * d.ctl->live;
+  return rows * ((d.ctl->words + WORDS_FEW - 1) / WORDS_FEW) > d.itcap ? d.ctl->live : 0;
+}
 
 // Item number `chunk` of a group (nv entries, `size` an item).
 template <int MODE>
@@ -635,8 +651,8 @@ __device__ __forceinline__ uint32_t reserve_wave(uint32_t* counter, uint32_t tot
 template <int MODE>
 __device__ void emit_items_wave(const Dev& d, uint32_t p, uint32_t list, uint32_t first, uint32_t total,
                                 uint32_t excl, uint32_t cnt, uint32_t kind, uint32_t extra,
-                                uint32_t x, uint32_t y, uint32_t base, uint32_t nv) {
-  const uint32_t size = MODE == ITEM_WORDS ? word_chunk(d.ctl->words) : CHUNK;
+                                uint32_t x, uint32_t y, uint32_t base, uint32_t nv,
+                                uint32_t size = CHUNK) {
   if (!__ballot(cnt > 1)) {
     // at most one item per lane (most rows fit one chunk): no owner to look up
     const uint32_t idx = first + excl;
@@ -671,14 +687,14 @@ __device__ void emit_items_wave(const Dev& d, uint32_t p, uint32_t list, uint32_
 // One group per lane with its own reservation.
 template <int MODE, bool TEAM>
 __device__ void emit_group(const Dev& d, uint32_t p, uint32_t list, uint32_t kind, uint32_t extra,
-                           uint32_t x, uint32_t y, uint32_t base, uint32_t nv) {
-  const uint32_t size = MODE == ITEM_WORDS ? word_chunk(d.ctl->words) : CHUNK;
+                           uint32_t x, uint32_t y, uint32_t base, uint32_t nv,
+                           uint32_t size = CHUNK) {
   const uint32_t cnt = (nv + size - 1) / size;
   uint32_t total;
   const uint32_t excl = wave_excl_scan(cnt, &total);
   if (!total) return;
   const uint32_t first = reserve_wave<TEAM>(&d.ctl->cnt[list][p].nit, total);
-  emit_items_wave<MODE>(d, p, list, first, total, excl, cnt, kind, extra, x, y, base, nv);
+  emit_items_wave<MODE>(d, p, list, first, total, excl, cnt, kind, extra, x, y, base, nv, size);
 }
 
 // Support items of event (a -> w): the live edges (a,b), CHUNK slots per item.
@@ -694,8 +710,9 @@ __device__ void emit_support_items(const Dev& d, uint32_t p, bool active, uint32
 
 // Items over z's old (j-1)-ball words for candidates (x, w), j >= 3.
 template <bool TEAM>
-__device__ void emit_word_items(const Dev& d, uint32_t p, uint32_t j, bool active, uint32_t x, uint32_t z) {
-  emit_group<ITEM_WORDS, TEAM>(d, p, j, 0, 0, x, z, 0, active ? d.ctl->words : 0u);
+__device__ void emit_word_items(const Dev& d, uint32_t p, uint32_t j, bool active, uint32_t x, uint32_t z,
+                                uint32_t size) {
+  emit_group<ITEM_WORDS, TEAM>(d, p, j, 0, 0, x, z, 0, active ? d.ctl->words : 0u, size);
 }
 
 // ---- level-jump minimum ----------------------------------------------------
@@ -895,9 +912,11 @@ __device__ void mark_edge(const Dev& d, const RoundCtx& rc, bool valid, uint32_t
   emit_items_wave<ITEM_ROW>(d, rc.p, 2, first + t0 + t1, t2, e2, n2, KIND_B_SLOTS, 0, a, b, ba, v2);
   emit_items_wave<ITEM_ROW>(d, rc.p, 2, first + t0 + t1 + t2, t3, e3, n3, KIND_B_SLOTS, 0, b, a, bb,
                             v3);
+  if (d.h < 3) return;
+  const uint32_t wc = word_chunk(d.ctl->words, rc.edges);
   for (uint32_t j = 3; j <= d.h; ++j) {
-    emit_word_items<TEAM>(d, rc.p, j, valid, a, b);
-    emit_word_items<TEAM>(d, rc.p, j, valid, b, a);
+    emit_word_items<TEAM>(d, rc.p, j, valid, a, b, wc);
+    emit_word_items<TEAM>(d, rc.p, j, valid, b, a, wc);
   }
 }
 
@@ -932,7 +951,7 @@ __device__ void mark_edge_wave(const Dev& d, const RoundCtx& rc, uint32_t e, uin
   const uint32_t v0 = d.h == 1 ? da : db + 1, v1 = d.h == 1 ? db : da + 1;
   const uint32_t n0 = chunks_of(v0), n1 = chunks_of(v1);
   const uint32_t n2 = d.h == 1 ? 0 : chunks_of(da), n3 = d.h == 1 ? 0 : chunks_of(db);
-  const uint32_t words = d.ctl->words, wc = word_chunk(words), nw = (words + wc - 1) / wc;
+  const uint32_t words = d.ctl->words, wc = word_chunk(words, rc.edges), nw = (words + wc - 1) / wc;
   const uint32_t rows = n0 + n1 + n2 + n3;
   uint32_t base = 0;
   if (lane == 0 || lane + 2 <= d.h)  // lane l reserves the items of list l + 2
@@ -1004,6 +1023,7 @@ k_mark(const Dev* __restrict__ devs) {
     for (uint32_t i = lane; i < d.nminpart; i += WAVE) mn = min(mn, d.minpart[i]);
     mn = wave_min(mn);
     rc.k = mn + 2;
+    if (d.h >= 3) rc.edges = word_chunk_edges(d);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       c->k = rc.k;
       c->levels += 1;
@@ -1018,7 +1038,7 @@ k_mark(const Dev* __restrict__ devs) {
       mark_edge<false>(d, rc, take, e, i);
     }
   } else {
-    const uint32_t nR = c->nRc.v;
+    const uint32_t nR = rc.edges = c->nRc.v;
     if (nR <= wstride / WAVE) {
       // no more peeled edges than wavefronts: one edge per wavefront, so the
       // 64 lanes share the writing of its work items -- the rows of a hub
@@ -1943,7 +1963,8 @@ __global__ void __launch_bounds__(256) k_fill_level(const Dev* __restrict__ dp, 
       emit_items_wave<ITEM_ROW>(d, rc.p, 2, first, t0, e0, n0, KIND_A_SLOTS, 1, x, z, bz, v0);
       emit_items_wave<ITEM_ROW>(d, rc.p, 2, first + t0, t1, e1, n1, KIND_B_SLOTS, 0, x, z, bx, v1);
     } else {
-      emit_word_items<false>(d, rc.p, j, a, x, z);  // (x, w), w in z's old (j-1)-ball
+      // (x, w), w in z's old (j-1)-ball
+      emit_word_items<false>(d, rc.p, j, a, x, z, word_chunk(c->words, c->nRc.v));
     }
   }
   // the level-(j-1) events (x -> w): (y, w), y a live neighbour of x, and (x, w)

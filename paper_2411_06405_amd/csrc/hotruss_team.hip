@@ -289,7 +289,7 @@ __device__ void team_run(const Dev& d, uint32_t me, uint32_t n, const TeamLimits
         phase = 0;
         break;
       }
-      const RoundCtx rc{r, k, p};
+      const RoundCtx rc{r, k, p, nR};
       const uint32_t* R = d.R[p];
       // one edge per wavefront, dealt to workgroups first; in large rounds one
       // per lane
