@@ -105,6 +105,8 @@ typedef struct {
                                         re-created from their sources in windows, host-driven) */
 #define HO_FLAG_SERIAL_SUPPORT 0x8u  /* testing: the same for the support update step       */
 #define HO_FLAG_COMPACT_EACH 0x10u   /* testing: compact the adjacency rows at every chance  */
+#define HO_FLAG_DECOMPOSE_LAYOUT 0x20u /* hoTrussHSupport: lay the graph out (renumbered or not) as
+                                          hoTrussDecompose does, to time or test its initial pass */
 
 /* Work counters of the last decomposition on this host thread. */
 typedef struct {

@@ -25,6 +25,7 @@ HO_FLAG_STATS = 0x2
 HO_FLAG_SERIAL_LEVELS = 0x4
 HO_FLAG_SERIAL_SUPPORT = 0x8
 HO_FLAG_COMPACT_EACH = 0x10
+HO_FLAG_DECOMPOSE_LAYOUT = 0x20
 
 
 class HotrussError(RuntimeError):

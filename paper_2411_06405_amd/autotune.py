@@ -8,11 +8,11 @@ h-support of every edge) has three knobs that change speed, never results:
 * ``word_bits`` -- bitset load width per lane in the h-support pass (64/128);
 * ``edges_per_wave`` -- edges sharing one wavefront in that pass (1..16).
 
-``autotune`` times ``hoTrussHSupport`` (which runs exactly that pass) on the
-caller's graph for each candidate setting, one knob group at a time, and
-keeps the fastest.  ``autotune_rounds`` adds the knob of the peel rounds,
+``autotune`` times ``hoTrussHSupport``, laid out as a decomposition lays the
+graph out (it then runs exactly that pass), on the caller's graph for each
+candidate setting, one knob group at a time, and keeps the fastest.  ``autotune_rounds`` adds the knob of the peel rounds,
 which take almost all of a decomposition's time: ``grid_blocks``, the
-workgroups of the round kernels (the ball-change kernel uses a quarter as
+workgroups of the round kernels (the ball-change kernel uses an eighth as
 many, of four times the size), timed on whole decompositions.  Results are cached in a JSON file keyed by the device
 name and a bucket of the graph's shape (vertices, average degree, degree
 skew, h), so graphs of a similar shape reuse a measurement.  The timing runs
@@ -29,10 +29,14 @@ from typing import Callable, Iterable
 
 import numpy as np
 
-DENSE_THRESHOLDS = (4, 32, 256, 1 << 30)   # 1 << 30: never bottom-up
+DENSE_THRESHOLDS = (0, 4, 32, 256, 1 << 30)   # 0: the library's own rule; 1 << 30: never bottom-up
 WIDTHS = (64, 128)
 EDGES_PER_WAVE = (1, 4, 16)
 GRID_PER_CU = (4, 8, 16)   # round-kernel workgroups per CU
+# Which pass a cached choice was measured on: choices from before the pass
+# changed (rows of a frontier each their own way, renumbered graphs, supports by
+# slices) carry another one and are measured again.
+PASS = 2
 DEFAULT_CACHE = Path(os.environ.get("HOTRUSS_TUNE_CACHE",
                                     Path.home() / ".cache" / "hotruss_autotune.json"))
 
@@ -42,7 +46,7 @@ def shape_key(device_name: str, n: int, m: int, h: int, max_deg: int) -> str:
     avg = 2.0 * m / max(n, 1)
     skew = max_deg / max(avg, 1e-9)
     b = lambda v: int(math.floor(math.log2(max(v, 1.0))))  # noqa: E731
-    return f"{device_name}|n2^{b(n)}|d2^{b(avg)}|s2^{b(skew)}|h{h}"
+    return f"{device_name}|n2^{b(n)}|d2^{b(avg)}|s2^{b(skew)}|h{h}|pass{PASS}"
 
 
 def choose(timings: dict) -> tuple:
@@ -108,7 +112,8 @@ class Cache:
 
 def autotune(row_ptr, col_idx, n: int, h: int, device="cuda", cache=None, refresh=False,
              repeats: int = 3) -> dict:
-    """Tuning dict for hoTrussDecompose / hoTrussHSupport on this graph.
+    """Tuning dict for hoTrussDecompose on this graph, and for hoTrussHSupport
+    where that lays the graph out the same.
 
     row_ptr / col_idx: the graph's CSR (device tensors or host arrays)."""
     import torch
@@ -136,7 +141,8 @@ def autotune(row_ptr, col_idx, n: int, h: int, device="cuda", cache=None, refres
         stream.synchronize()
         t0 = time.perf_counter()
         rc = _lib.lib.hoTrussHSupport(rp.data_ptr(), ci.data_ptr(), n, m, h, out.data_ptr(),
-                                     ws.data_ptr(), ws.numel(), _lib._tuning(tune),
+                                     ws.data_ptr(), ws.numel(),
+                                     _lib._tuning(dict(tune, flags=_lib.HO_FLAG_DECOMPOSE_LAYOUT)),
                                      stream.cuda_stream)
         _lib._check(rc, "hoTrussHSupport")
         return time.perf_counter() - t0

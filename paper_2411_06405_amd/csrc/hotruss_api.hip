@@ -72,8 +72,9 @@ bool make_plan(uint32_t n, uint64_t m, uint32_t h, const hoTuning* tune, bool fu
   Plan p;
   p.n = n; p.m = m; p.h = h; p.full = full;
   p.W = words_per_row(n);
+  const bool as_full = full || (tune && (tune->flags & HO_FLAG_DECOMPOSE_LAYOUT));
   p.renumber = may_renumber && h >= 2 && n >= RENUMBER_MIN_N &&
-               (full || m * p.W >= RENUMBER_MIN_WORDS);
+               (as_full || m * p.W >= RENUMBER_MIN_WORDS);
   // Lists are sized so that a round rarely overflows them (a round that does
   // re-runs the overflowed step from the host in windows that fit).
   p.evcap = tune && tune->event_capacity ? tune->event_capacity
