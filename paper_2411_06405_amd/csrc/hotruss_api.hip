@@ -294,7 +294,6 @@ struct EventGuard {
     if (st_ != HO_OK) return st_;     \
   } while (0)
 
-// Canonical edge ids, ball build and initial h-support into out_sup.
 // Exclusive prefix sum of up_cnt.
 void run_scan(const Dev& d, uint32_t* out, hipStream_t s) {
   const uint32_t nb = (d.n + 1023) / 1024;
@@ -328,6 +327,7 @@ void run_renumber(const Dev& d, hipStream_t s) {
   if (d.ce) hipLaunchKernelGGL(k_rows_edges, dim3(grid_for(d.nnz, 256)), dim3(256), 0, s, d);
 }
 
+// Canonical edge ids, ball build and initial h-support into out_sup.
 hoStatus run_init(const Dev& d, uint32_t* out_sup, const hoTuning* tune, hipStream_t s,
                   hipEvent_t sup0 = nullptr, hipEvent_t sup1 = nullptr) {
   const unsigned T = 256;
@@ -598,8 +598,8 @@ hoStatus steps_host(const Dev& d, const RoundGrid& g, hipStream_t s, uint32_t fr
 
 // ----------------------------------------------------------------- engine
 // A pool of device memory, S slots and a queue of decompositions.  Every
-// replay of the captured step graph advances each active slot by one of its
-// own peel rounds; finished slots are retired and queued graphs admitted
+// replay of a captured graph advances each active slot by some of its own peel
+// rounds (see graph_shape); finished slots are retired and queued graphs admitted
 // between graph launches (continuous batching).  The plain entry point is the
 // same engine with one slot and a full-GPU grid.
 
@@ -802,7 +802,6 @@ class Engine {
   uint32_t S = 1, hmax = 1;
   uint64_t cap_factor = 128;
   RoundGrid g{};
-  bool plain = false;
   bool host_rounds = false;  // every round driven from the host, without the team kernel
   Dev* devs_d = nullptr;
   uint32_t* status_d = nullptr;
@@ -842,7 +841,7 @@ class Engine {
   }
 
   hoStatus init(void* ws, size_t ws_bytes, uint32_t slots, uint32_t hmax_, const RoundGrid& grid,
-                hipStream_t stream, bool plain_, bool borrow_host = false) {
+                hipStream_t stream, bool borrow_host = false) {
     s = stream;
     base = ((uintptr_t)ws + ALIGN - 1) / ALIGN * ALIGN;
     if (ws_bytes < ALIGN + engine_header_bytes(slots)) return HO_ERR_WORKSPACE;
@@ -850,7 +849,6 @@ class Engine {
     S = slots;
     hmax = hmax_;
     g = grid;
-    plain = plain_;
     devs_d = (Dev*)base;
     status_d = (uint32_t*)(base + up(sizeof(Dev) * S));
     spart_d = (uint32_t*)(base + up(sizeof(Dev) * S) + up(4ull * HO_STATUS_WORDS * S));
@@ -1431,7 +1429,7 @@ hoStatus hoTrussDecompose(const uint32_t* row_ptr, const uint32_t* col_idx, uint
   const bool host_loop = stats || (tune && (tune->flags & HO_FLAG_HOST_LOOP));
   const RoundGrid g = plain_grid(m, tune);
   Engine eng;
-  HOCHK(eng.init(workspace, workspace_bytes, 1, p.h, g, stream, true, true));
+  HOCHK(eng.init(workspace, workspace_bytes, 1, p.h, g, stream, true));
   Request r;
   r.rp = row_ptr; r.ci = col_idx; r.n = n; r.m = m; r.h = h;
   r.t = out_trussness; r.rho = out_round;
@@ -1633,7 +1631,7 @@ hoStatus hoTrussDecomposeBatched(const uint32_t* row_ptr_cat, const uint32_t* co
   if (workspace_bytes < largest + engine_header_bytes(S) + ALIGN) return HO_ERR_WORKSPACE;
   Engine eng;
   eng.cap_factor = 16;
-  HOCHK(eng.init(workspace, workspace_bytes, S, hmax, batch_grid(S, tune), stream, false));
+  HOCHK(eng.init(workspace, workspace_bytes, S, hmax, batch_grid(S, tune), stream));
   std::sort(order.begin(), order.end(), std::greater<std::pair<size_t, uint32_t>>());
   std::vector<size_t> ids;
   for (auto& og : order) {
@@ -1671,7 +1669,7 @@ hoStatus hoSessionCreate(void* pool, size_t pool_bytes, uint32_t max_slots, uint
   if (!ss) return HO_ERR_INVALID_ARG;
   ss->eng.cap_factor = 16;
   hoStatus st = ss->eng.init(pool, pool_bytes, max_slots, max_h, batch_grid(max_slots, nullptr),
-                             stream, false);
+                             stream);
   if (st != HO_OK) {
     delete ss;
     return st;

@@ -274,10 +274,6 @@ __device__ __forceinline__ const uint64_t* row(const uint64_t* base, uint32_t W,
   return base + (size_t)x * W;
 }
 
-__device__ __forceinline__ bool getbit(const uint64_t* base, uint32_t W, uint32_t x, uint32_t w) {
-  return (base[(size_t)x * W + (w >> 6)] >> (w & 63)) & 1ull;
-}
-
 // Wave-wide scans and reductions on DPP moves (row shifts inside the rows of
 // 16 lanes, then row broadcasts 15 and 31): six VALU steps of a few cycles
 // each, where a __shfl step goes through the LDS crossbar and takes over 50.

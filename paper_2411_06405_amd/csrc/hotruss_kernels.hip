@@ -1086,36 +1086,6 @@ constexpr uint32_t LV_NARROW_THREADS = 256, LV_NARROW_CAP = 1024; // batched slo
 constexpr uint32_t LV_FIRST = 32;  // witness probes of a pair before it is looked at again
 constexpr uint32_t LV_DENSE = 256; // of those, most tested on bitset rows per flush
 
-// Block-wide exclusive scan of v[0..n) (n <= LV_CAP) into out; returns the total.
-template <uint32_t LV_THREADS, uint32_t LV_CAP>
-__device__ uint32_t block_scan_cap(const uint32_t* v, uint32_t* out, uint32_t n, uint32_t* wsum) {
-  constexpr uint32_t LV_WAVES = LV_THREADS / WAVE;
-  const uint32_t per = LV_CAP / LV_THREADS;  // entries per thread
-  const uint32_t b0 = threadIdx.x * per;
-  uint32_t loc[per];
-  uint32_t s = 0;
-  for (uint32_t i = 0; i < per; ++i) {
-    loc[i] = (b0 + i < n) ? v[b0 + i] : 0u;
-    s += loc[i];
-  }
-  uint32_t wtot;
-  const uint32_t wex = wave_excl_scan(s, &wtot);
-  if (lane_id() == 0) wsum[threadIdx.x / WAVE] = wtot;
-  __syncthreads();
-  uint32_t off = 0, tot = 0;
-  for (uint32_t w = 0; w < LV_WAVES; ++w) {
-    if (w < threadIdx.x / WAVE) off += wsum[w];
-    tot += wsum[w];
-  }
-  uint32_t run = off + wex;
-  for (uint32_t i = 0; i < per; ++i) {
-    if (b0 + i < n) out[b0 + i] = run;
-    run += loc[i];
-  }
-  __syncthreads();
-  return tot;
-}
-
 // LDS of one workgroup of the ball-change step.  flag[] is all zero between
 // steps.
 template <uint32_t LV_THREADS, uint32_t LV_CAP>
