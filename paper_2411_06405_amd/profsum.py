@@ -24,14 +24,21 @@ from pathlib import Path
 import numpy as np
 
 COPY_BYTES = 256 << 20
-# kernels whose HBM traffic is recorded, and the source file each is built from
-KERNEL_SOURCES = {"k_level": "hotruss_kernels.hip", "k_support": "hotruss_kernels.hip",
-                  "k_hx_paths": "hotruss_hindex.hip", "k_hx_edges": "hotruss_hindex.hip"}
+# kernels whose HBM traffic is recorded, and the files that decide what each
+# moves: its source, the data layout, and for the round kernels the team kernel,
+# which takes rounds from them
+ROUND_SOURCES = ("hotruss_kernels.hip", "hotruss_team.hip", "hotruss_dev.h")
+HINDEX_SOURCES = ("hotruss_hindex.hip", "hotruss_dev.h")
+KERNEL_SOURCES = {"k_level": ROUND_SOURCES, "k_support": ROUND_SOURCES,
+                  "k_hx_paths": HINDEX_SOURCES, "k_hx_edges": HINDEX_SOURCES}
 
 
-def source_sha(srcname: str) -> str:
-    src = Path(__file__).resolve().parent / "csrc" / srcname
-    return hashlib.sha256(src.read_bytes()).hexdigest()[:16]
+def source_sha(names, csrc=None) -> str:
+    csrc = Path(csrc) if csrc else Path(__file__).resolve().parent / "csrc"
+    sha = hashlib.sha256()
+    for name in names:
+        sha.update((csrc / name).read_bytes())
+    return sha.hexdigest()[:16]
 
 
 def short(name: str) -> str:
@@ -101,11 +108,11 @@ def main(trace_db, fetch_db, write_db, outdir, tag, cmd):
         ndec = sum(len(fetch[n]) for n in fetch if short(n) == "k_init_ctl")
         if ndec:
             (outdir / f"traffic_whole_{tag}.txt").write_text(json.dumps({
-                "source_sha": source_sha("hotruss_kernels.hip"), "decompositions": ndec,
+                "source_sha": source_sha(ROUND_SOURCES), "decompositions": ndec,
                 "bytes_per_decomposition": tot / ndec, "fetch_scale": sf, "write_scale": sw,
                 "command": cmd}, indent=1) + "\n")
-    for kname, srcname in KERNEL_SOURCES.items():
-        sha = source_sha(srcname)
+    for kname, sources in KERNEL_SOURCES.items():
+        sha = source_sha(sources)
         full = [n for n in fetch if short(n) == kname]
         if not full or sf is None or sw is None:
             continue
