@@ -153,7 +153,10 @@ typedef struct {
 /* Bytes of device workspace hoTrussDecompose / hoTrussHSupport need for a
  * graph with n vertices, m undirected edges and hop threshold h.  Dominated by
  * 2h bitset arrays of n x ceil(n/64) words (the h-hop balls at every level and
- * the per-round change marks).  Returns 0 on invalid arguments. */
+ * the per-round change marks).  Returns 0 on invalid arguments.  (Both also
+ * accept less, down to what the graph takes in the caller's vertex order: from
+ * 32,768 vertices on, the size returned has room for renumbering it by degree,
+ * which is faster where hubs hold the edges.) */
 size_t hoTrussWorkspaceBytes(uint32_t n, uint64_t m, uint32_t h, const hoTuning *tune);
 
 /* h-support of every edge in the whole graph, sup_G(e,h) (Def. 3).
@@ -183,8 +186,10 @@ hoStatus hoTrussDecompose(const uint32_t *row_ptr, const uint32_t *col_idx,
  * and status words live in a fixed 256 MiB device array inside the library
  * (one per GPU, held until the process ends); a graph whose workspace does
  * not fit it returns HO_ERR_WORKSPACE before any device work (h = 2 fits up
- * to about n = 20,000 with m = 10^5).  Rounds are driven from the host, one
- * synchronisation per step, so it is slower per round than hoTrussDecompose.
+ * to about n = 20,000 with m = 10^5).  The host looks in after every launch of
+ * the kernel that runs small rounds back to back, and drives each round too
+ * large for it (h = 1: every round) step by step, one synchronisation per step;
+ * so it is slower than hoTrussDecompose.
  * Inputs and outputs as for hoTrussDecompose (device pointers); returns after
  * the work has completed on `stream`.  The array keeps the last call's
  * contents; each call initialises what it reads.  Calls on one GPU share
@@ -211,8 +216,8 @@ hoStatus hoTrussLastStats(hoStats *out);
  * B separate hoTrussDecompose calls (components never interact).
  *
  * Execution: graphs are admitted largest workspace first into up to 256
- * concurrent slots carved from the workspace; one replay of a captured step
- * graph advances every active slot by one of its own peel rounds, and finished
+ * concurrent slots carved from the workspace; one replay of a captured graph
+ * advances every active slot by some of its own peel rounds, and finished
  * slots are refilled between replays.  Any workspace at least as large as the
  * largest single graph's share works; more lets more graphs run together.
  * hoTrussBatchedWorkspaceBytes returns the size that lets the 64 largest

@@ -50,12 +50,20 @@ uint32_t clamp_cap(uint64_t want, uint64_t lo, uint64_t hi) {
   return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(want, lo), hi);
 }
 
-// Renumbering pays once a ball row is many cache lines and rows are read in
-// work items (h >= 2): R-MAT 18 h = 2 5.46 -> 4.96 s, the h-support of R-MAT 17
-// 11.1 -> 8.8 ms.  BA 12,345 (1.5 KiB a row) lost 5%, Chung-Lu 100k at h = 1 4%.
+// Renumbering pays where rows are read in work items (h >= 2), hubs hold the
+// edges and a ball row is many cache lines.  Without and with, ms: R-MAT 18 h = 2
+// 5,460 and 4,960, Chung-Lu 100,000 222.5 and 218.4, 35,000 of exponent 2.2 153.1
+// and 135.3, R-MAT 16 992 and 983.  Graphs without strong hubs lose the 0.1 ms it
+// takes, or 1 to 2%: uniform 33,000 deg 10 7.11 and 7.25, 100,000 deg 15 25.3 and
+// 25.9, 100,000 deg 4 6.77 and 6.74, Chung-Lu 50,000 of exponent 2.8 42.3 and
+// 43.1, BA 40,000 32.2 and 32.9.  From 8,192 vertices on instead, the graphs
+// between go either way: Chung-Lu 20,000 h = 3 631 and 557, R-MAT 13 106.6 and
+// 100.7, but BA 12,345 19.1 and 19.7, 30,000 29.2 and 30.0, uniform 20,000 deg 30
+// 16.6 and 16.9.  At h = 1 Chung-Lu 100k lost 4%.
 constexpr uint32_t RENUMBER_MIN_N = 32768;
 // A support query alone has no rounds to win the renumbering's 0.1 ms back, so
-// there the edges' rows must hold this many words in all.  Without and with, ms:
+// there the edges' rows must hold this many words in all.  (By size alone, too: a
+// large uniform graph loses 3% by it, the last one here.)  Without and with, ms:
 // uniform random 53,443 (176 Mi words) 0.52, 0.61; 100,000 deg 6 (411 Mi) 1.31,
 // 1.45; Chung-Lu 84,075 (436 Mi) 1.44, 1.46; 100,000 (686 Mi) 2.13, 2.02; R-MAT
 // 16 (819 Mi) 3.31, 2.05; uniform random 100,000 deg 15 (1,029 Mi) 2.30, 2.37.
@@ -757,7 +765,12 @@ enum { GR_ONE, GR_FEW, GR_MANY, GR_LONG, GR_SHORT, GR_CHIP, GR_CHIPS, GR_N };
 // round, so team steps that run many rounds each are never doubted; if they
 // run `few`, the other kind is tried for three launches (two are known when
 // the fourth is picked), and the better one stays for a number of launches
-// that doubles as long as it wins.
+// that doubles as long as it wins.  Few: under 16 rounds a step for one slot, 29
+// of 32 or 128 of 256 for several.  With half of each, and twice (all but the
+// longest steps doubted): three uniform graphs of 12,000 in a batch 15.2 ms, so
+// 10.9 and 15.2; six Chung-Lu of 12,000 to 16,500 h = 3 994, 1,112 and 992; eight
+// uniform graphs of 20,000 22.8, 22.8 and 24.0; 30 requests through one slot 58.7,
+// 59.0 and 64.8; Chung-Lu 100k and R-MAT 16 alone all alike.
 struct Pace {
   double rate[2] = {0, 0};  // 0 team steps, 1 whole-chip rounds
   bool chip = false, trial = false, few = false, last = false;
@@ -968,9 +981,9 @@ class Engine {
   // decomposition: a launch of the team kernel runs to the next large step;
   // many: short enough that finished slots are refilled in time.  Whole-chip
   // rounds: the team kernel at the head does no more than open the first round
-  // (and close one that the last team step left open).  h = 1 is always that: its
-  // round is three kernels (Chung-Lu 2,000: 0.81 ms, by a team 1.19; 100k: 6.5
-  // and 7.5).
+  // (and close one that the last team step left open).  One decomposition at
+  // h = 1 is always that: its round is three kernels (Chung-Lu 2,000: 0.80 ms, by a
+  // team 1.35; 100k: 5.03 and 5.31).
   struct GraphShape {
     bool chip;
     uint32_t steps, rounds;  // rounds: of each team step, at most
@@ -1093,9 +1106,6 @@ class Engine {
     return HO_OK;
   }
 
-  // Replay the step graph until no slot is active and the queue is empty
-  // (or max_launches replays have been launched), two replays in flight, the
-  // slots' status words copied to pinned memory after each.
   // Progress on stderr for long calls (environment HOTRUSS_PROGRESS set): at
   // most every 10 s, from the host loop that drives the work.
   void report_progress(std::chrono::steady_clock::time_point& last) {
@@ -1148,6 +1158,9 @@ class Engine {
     return !pace.few ? GR_LONG : steps < 6 || !queue.empty() ? GR_FEW : GR_MANY;
   }
 
+  // Replay graphs until no slot is active and the queue is empty (or
+  // max_launches replays have been launched), two replays in flight, the slots'
+  // status words copied to pinned memory after each.
   hoStatus run(uint64_t max_launches = UINT64_MAX) {
     HOCHK(admit());
     if (!busy()) return HO_OK;

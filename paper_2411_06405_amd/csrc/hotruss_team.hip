@@ -14,14 +14,15 @@
 // round kernels that follow in the same graph.
 //
 // A team's round takes 15 to 25 us on such graphs (Chung-Lu 100k h = 2: level
-// scan 3.4, marking 2.6, ball change 7, support update 5.3, barriers 5), bound
-// by the chain of dependent accesses, now to the L2.  Before and after, ms a
-// call: uniform random 200 h = 2 1.8 and 1.4; Chung-Lu 5,001 h = 3 194 and 117;
-// 32 clique-planted graphs in one batch 216 and 108; a session of 24 mixed
-// requests 306 and 172; without allocations, where the host had to look at
-// every round, Chung-Lu 1,500 h = 2 44.6 and 9.  One graph whose rounds are
-// mostly large gains nothing from it (R-MAT 16 h = 2: 1,237 by teams alone, 990
-// by the chip); which of the two runs is decided by their progress (see Pace).
+// scan 3.4 over all rounds, of which 38% begin with one, marking 2.6, ball change
+// 7, support update 5.3, barriers 5), bound by the chain of dependent accesses,
+// now to the L2.  Before and after, ms a call: uniform random 200 h = 2 1.8 and
+// 1.2 to 1.5; Chung-Lu 5,001 h = 3 194 and 114; 32 clique-planted graphs in one
+// batch 216 and 116; a session of 24 mixed requests 306 and 166 to 175; without
+// allocations, where the host had to look at every round, Chung-Lu 1,500 h = 2
+// 44.6 and 8.7.  One graph whose rounds are mostly large gains nothing from it
+// (R-MAT 16 h = 2: 1,237 by teams alone, 987 by the chip); which of the two runs
+// is decided by their progress (see Pace).
 //
 // What makes it safe:
 //  * A team is whoever arrived: its workgroups join by a counter, the first
