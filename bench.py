@@ -593,6 +593,10 @@ def main(argv=None):
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-stats", action="store_true",
                     help="skip the stats-mode decomposition (profiling runs)")
+    ap.add_argument("--host-rounds", action="store_true",
+                    help="drive every round from the host (profiling runs: the launches that the "
+                         "stats mode times; the choice between teams and whole-chip rounds goes by "
+                         "the clock, which counters slow down)")
     ap.add_argument("--hx-h", type=int, default=2, help="hindex: hop threshold h")
     ap.add_argument("--hx-sync-only", action="store_true",
                     help="hindex: time the synchronous sweeps only (profiling runs)")
@@ -627,15 +631,16 @@ def main(argv=None):
     ci = torch.from_numpy(g.col_idx.view(np.int32)).to(dev)
     ws = ht.alloc_workspace(g.n, g.m, h, device=dev)
     stats_tune = {"flags": ht._lib.HO_FLAG_STATS}
+    tune = {"flags": ht._lib.HO_FLAG_HOST_LOOP} if args.host_rounds else None
 
     for _ in range(args.warmup):
-        ht.decompose(rp, ci, g.n, h, workspace=ws, device=dev)
+        ht.decompose(rp, ci, g.n, h, workspace=ws, device=dev, tune=tune)
     torch.cuda.synchronize()
     _log(f"{desc}: n={g.n} m={g.m}, timing {args.steps} decompositions")
     device_ms = []
     t0 = time.perf_counter()
     for _ in range(args.steps):
-        t, rho = ht.decompose(rp, ci, g.n, h, workspace=ws, device=dev)
+        t, rho = ht.decompose(rp, ci, g.n, h, workspace=ws, device=dev, tune=tune)
         device_ms.append(ht.last_stats()["device_ms"])  # the call has completed
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0

@@ -1,6 +1,6 @@
 """Summarise rocprofv3 databases of a bench run into short text files.
 
-    python -m paper_2411_06405_amd.profsum TRACE_DB FETCH_DB WRITE_DB OUTDIR TAG CMD
+    python -m paper_2411_06405_amd.profsum TRACE_DB FETCH_DB WRITE_DB OUTDIR TAG CMD [PMC_CMD]
     python -m paper_2411_06405_amd.profsum counters PMC_DB OUTDIR TAG CMD
 
 Writes OUTDIR/kernels_TAG.txt (per-kernel dispatch count and durations from
@@ -9,7 +9,8 @@ dispatch, KiB) and OUTDIR/traffic_KERNEL_TAG.txt for the kernels named in
 KERNEL_SOURCES (HBM bytes per launch, scaled by what the same counters read
 for a 256 MiB device-to-device copy), and OUTDIR/traffic_whole_TAG.txt: the
 scaled bytes of every library kernel (names starting with k_) per
-decomposition, a decomposition being one dispatch of k_init_ctl.  The
+decomposition, a decomposition being one dispatch of k_init_ctl.  PMC_CMD: the
+command of the two counter runs, where it is not the traced one.  The
 counters form writes OUTDIR/counters_TAG.txt: the mean per dispatch of every
 counter of one --pmc run, per kernel.
 """
@@ -71,8 +72,9 @@ def counter_table(db: str, counter: str):
     return {name: np.array(v) for name, v in rows.items()}
 
 
-def main(trace_db, fetch_db, write_db, outdir, tag, cmd):
+def main(trace_db, fetch_db, write_db, outdir, tag, cmd, pmc_cmd=None):
     outdir = Path(outdir)
+    pmc_cmd = pmc_cmd or cmd
     outdir.mkdir(parents=True, exist_ok=True)
     kt = kernel_table(trace_db)
     lines = [f"# rocprofv3 --kernel-trace --stats -- {cmd}",
@@ -90,7 +92,7 @@ def main(trace_db, fetch_db, write_db, outdir, tag, cmd):
     cf, cw = copy_kib(fetch), copy_kib(write)
     sf = (COPY_BYTES / 1024) / cf if cf else None
     sw = (COPY_BYTES / 1024) / cw if cw else None
-    lines = [f"# rocprofv3 --pmc FETCH_SIZE -- {cmd}", f"# rocprofv3 --pmc WRITE_SIZE -- {cmd}",
+    lines = [f"# rocprofv3 --pmc FETCH_SIZE -- {pmc_cmd}", f"# rocprofv3 --pmc WRITE_SIZE -- {pmc_cmd}",
              f"# calibration: 256 MiB device copy reads FETCH_SIZE {cf} KiB (scale {sf}), "
              f"WRITE_SIZE {cw} KiB (scale {sw})",
              "# kernel, dispatches, mean FETCH_SIZE KiB, mean WRITE_SIZE KiB"]
@@ -110,7 +112,7 @@ def main(trace_db, fetch_db, write_db, outdir, tag, cmd):
             (outdir / f"traffic_whole_{tag}.txt").write_text(json.dumps({
                 "source_sha": source_sha(ROUND_SOURCES), "decompositions": ndec,
                 "bytes_per_decomposition": tot / ndec, "fetch_scale": sf, "write_scale": sw,
-                "command": cmd}, indent=1) + "\n")
+                "command": pmc_cmd}, indent=1) + "\n")
     for kname, sources in KERNEL_SOURCES.items():
         sha = source_sha(sources)
         full = [n for n in fetch if short(n) == kname]
@@ -123,7 +125,7 @@ def main(trace_db, fetch_db, write_db, outdir, tag, cmd):
             "kernel": kname, "source_sha": sha, "launches": int(len(f)),
             "fetch_kib_per_launch": float(f.mean()), "write_kib_per_launch": float(w.mean()),
             "fetch_scale": sf, "write_scale": sw, "bytes_per_launch": per_launch,
-            "command": cmd}, indent=1) + "\n")
+            "command": pmc_cmd}, indent=1) + "\n")
 
 
 def counters_main(db, outdir, tag, cmd):
@@ -151,4 +153,4 @@ if __name__ == "__main__":
     if sys.argv[1] == "counters":
         counters_main(*sys.argv[2:6])
     else:
-        main(*sys.argv[1:7])
+        main(*sys.argv[1:8])
